@@ -23,7 +23,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0        # MI355X HBM3E
-BYTES_PER_LUP_F32 = 280.0    # 35 populations x 4 B, read and written once
+BYTES_PER_LUP_F32 = 280.0    # 35 populations x 4 B, read and written once per pass
 
 
 def _oracle_rate(params, f, steps):
@@ -459,6 +459,19 @@ def measured_traffic():
     return rec["traffic_bytes_per_launch"] if h.hexdigest() == rec["sources_sha256"] else None
 
 
+def passes(first, steps, diag_every):
+    """Passes over the state that lbm_step(steps, diag_every) makes from step `first`
+    on where it runs step pairs: two steps per pass from an odd step on, four steps at
+    a time, up to the next step with diagnostics; one step per pass otherwise."""
+    n, t, end = 0, first, first + steps
+    while t < end:
+        stop = end if not diag_every else min(end, t + diag_every - t % diag_every)
+        four = (stop - t) // 4 if t % 2 and not (diag_every and t % diag_every == 0) else 0
+        n += 2 * four if four else 1
+        t += 4 * four if four else 1
+    return n
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -575,7 +588,9 @@ def main():
     # lbm_step reduces the diagnostics on the steps t with t % diag_every == 0
     diag_timed = (sum(1 for t in range(args.warmup, args.warmup + args.steps) if t % args.diag_every == 0)
                   if args.diag_every > 0 else 0)
-    avg_launch_ms = ms / args.steps
+    paired = not args.fp16 and args.odd_lds
+    launches = passes(args.warmup, args.steps, args.diag_every) if paired else args.steps
+    avg_launch_ms = ms / launches
     achieved_gbs = bytes_per_lup * cells / (avg_launch_ms * 1e-3) / 1e9
 
     bw = None
@@ -605,9 +620,11 @@ def main():
                    "parallelism": "single GPU"},
         "roofline": {"bound": "hbm", "achieved": round(achieved_gbs, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(achieved_gbs / HBM_PEAK_GBS, 4),
-                     "traffic": None if args.fp16 or args.n != 256 else measured_traffic(),
+                     "traffic": None if args.fp16 or args.n != 256 or paired else measured_traffic(),
                      "traffic_unit": "bytes per launch",
-                     "bytes_per_lup": bytes_per_lup, "avg_launch_ms": round(avg_launch_ms, 5)},
+                     "bytes_per_lup": round(bytes_per_lup * launches / args.steps, 3),
+                     "steps_per_launch": round(args.steps / launches, 4),
+                     "avg_launch_ms": round(avg_launch_ms, 5)},
         "host_wall_s": round(t_host, 3),
         "copy_bw_gbs": None if bw is None else round(bw, 1),
         "frac_of_copy_bw": None if bw is None else round(achieved_gbs / bw, 4),

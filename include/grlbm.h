@@ -26,6 +26,13 @@
  * deviation f - w_i Q_ref from the equilibrium of a uniform reference state
  * (Sec. 2.2), Q_ref = (rho_ref, 0, 0, 0, E_ref).
  *
+ * Step pairs.  With FP32 storage a context also keeps a second buffer of the same
+ * size where the card has room to spare (it stays at least half free, and these
+ * buffers together below a quarter of it): lbm_step then makes two steps per pass
+ * over memory, alternating between the two buffers, and ends every call in the first.
+ * The results are bitwise those of single steps.  The second buffers are given up
+ * when an allocation of this library fails, and the contexts go on in single steps.
+ *
  * Threading.  A context is not internally locked: use one context per host thread
  * at a time.  lbm_last_error is thread-local.
  *
@@ -153,7 +160,9 @@ lbm_status lbm_init_fields_device(lbm_ctx* ctx, const double* Q_dev);
 /* Enqueue n >= 0 collide-and-stream steps on the context's stream (asynchronous).
  * If diag_every > 0, every step whose index t (completed steps before it) satisfies
  * t % diag_every == 0 also produces a diagnostic record (see lbm_diagnostics).
- * ESTATE before initialisation. */
+ * ESTATE before initialisation.  A call of four steps or more may make them in pairs
+ * (above): from a step of odd index on, four at a time, up to the next step with
+ * diagnostics.  On a stream under capture the steps are single. */
 lbm_status lbm_step(lbm_ctx* ctx, int64_t n, int32_t diag_every);
 
 /* Conserved fields of the current state (post-streaming, i.e. the state after the
@@ -196,6 +205,7 @@ lbm_status lbm_set_populations(lbm_ctx* ctx, const float* f, int64_t step);
  * 2^23 cells and more, a lane takes two consecutive cells (4-byte accesses) in the
  * even step when `block` <= 256 and the cell count is even, and in the LDS odd step
  * when nx is 384 or 512.
+ * These settings are those of single steps; with `odd_lds` = 0 all steps are single.
  * Results do not depend on any of these settings.  EINVAL otherwise. */
 lbm_status lbm_set_launch(lbm_ctx* ctx, int32_t block, int32_t nontemporal, int32_t blocks_per_cu,
                           int32_t odd_lds);
@@ -210,7 +220,8 @@ lbm_status lbm_get_launch(lbm_ctx* ctx, lbm_launch* out);
 
 /* Time candidate launch shapes on the context's live state and keep the fastest:
  * even-step blocks of 256 (capped at 4, 2 or no blocks per CU), 512 (2 or none) and
- * 1024 threads, each with nontemporal access on and off, the LDS odd step on.  Each
+ * 1024 threads, each with nontemporal access on and off, the LDS odd step on, all in
+ * single steps.  Each
  * trial runs 2 warm-up steps and trial_steps timed steps (rounded up to even) with
  * no diagnostics; the populations and the step count are restored from a device
  * snapshot after each trial, so the state after the call is bitwise the state

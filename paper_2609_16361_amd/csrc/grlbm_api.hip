@@ -198,7 +198,7 @@ InitCoef make_init_coef(const lbm_params* p) {
 lbm_status scales_from_fields(Coll& c, const Grid& g, const InitCoef& ic, const double* Q_dev, int64_t N,
                               hipStream_t s) {
   unsigned* d = nullptr;
-  if (hipMalloc((void**)&d, 5 * sizeof(unsigned)) != hipSuccess) return fail(LBM_ENOMEM, "hipMalloc failed");
+  if (dev_malloc((void**)&d, 5 * sizeof(unsigned)) != hipSuccess) return fail(LBM_ENOMEM, "hipMalloc failed");
   lbm_status st = LBM_OK;
   if (hipMemsetAsync(d, 0, 5 * sizeof(unsigned), s) != hipSuccess ||
       launch_init_maxabs(g, c, ic, Q_dev, N, d, s) != hipSuccess)
@@ -210,13 +210,24 @@ lbm_status scales_from_fields(Coll& c, const Grid& g, const InitCoef& ic, const 
 
 lbm_status scales_from_pops(Coll& c, const float* f_dev, int64_t N, hipStream_t s) {
   unsigned* d = nullptr;
-  if (hipMalloc((void**)&d, 5 * sizeof(unsigned)) != hipSuccess) return fail(LBM_ENOMEM, "hipMalloc failed");
+  if (dev_malloc((void**)&d, 5 * sizeof(unsigned)) != hipSuccess) return fail(LBM_ENOMEM, "hipMalloc failed");
   lbm_status st = LBM_OK;
   if (hipMemsetAsync(d, 0, 5 * sizeof(unsigned), s) != hipSuccess || launch_maxabs_pops(f_dev, N, d, s) != hipSuccess)
     st = fail(LBM_EDEVICE, "storage-scale reduction failed");
   if (st == LBM_OK) st = read_maxabs(c, d, s);
   (void)hipFree(d);
   return st;
+}
+
+static bool give_up_spares();
+
+hipError_t dev_malloc(void** p, size_t bytes) {
+  hipError_t e = hipMalloc(p, bytes);
+  if (e == hipErrorOutOfMemory && give_up_spares()) {
+    (void)hipGetLastError();
+    e = hipMalloc(p, bytes);
+  }
+  return e;
 }
 
 Grid make_grid(const lbm_params* p) {
@@ -272,6 +283,12 @@ struct lbm_ctx {
   void* F = nullptr;
   size_t F_bytes = 0;
   bool own_F = false;
+  // two steps per pass (launch_pair): the second population buffer, the grid's tiles,
+  // and the lock under which F2 is used or given up (give_up_spares)
+  void* F2 = nullptr;
+  std::mutex F2_mu;
+  grlbm::PairTiles pair{};
+  bool single_steps = false;  // lbm_autotune times the single-step kernels
   int64_t step = 0;
   bool ready = false;
   int block = 256;
@@ -306,10 +323,57 @@ lbm_status ensure_partials(lbm_ctx* c) {
   if (c->partials) HIP_TRY(hipFree(c->partials));
   c->partials = nullptr;
   c->partials_blocks = 0;
-  if (hipMalloc(&c->partials, (size_t)nb * kDiagVals * sizeof(float)) != hipSuccess)
+  if (grlbm::dev_malloc((void**)&c->partials, (size_t)nb * kDiagVals * sizeof(float)) != hipSuccess)
     return fail(LBM_ENOMEM, "hipMalloc of %lld diagnostic partials failed", (long long)nb);
   c->partials_blocks = nb;
   return LBM_OK;
+}
+
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone;
+}
+
+// Second population buffers.  They are workspace: a context steps the same without
+// one, only slower.  So a context takes one only while plenty of the card is free,
+// all of them together stay below a quarter of it, and where an allocation of this
+// library fails they are given up and the allocation is tried again.
+std::mutex g_spare_mu;
+std::vector<lbm_ctx*> g_spare_owners;  // contexts that hold an F2
+size_t g_spare_bytes = 0;
+
+// Grids that step in pairs: FP32 storage, and 32-bit byte offsets reach two slots.
+bool pairs_fit(const lbm_ctx* c) {
+  return c->p.storage == LBM_STORE_F32 && c->g.S < (int64_t(1) << 29) && grlbm::pair_worth(c->g);
+}
+
+void take_spare(lbm_ctx* c) {
+  size_t free_bytes = 0, total = 0;
+  std::lock_guard<std::mutex> lock(g_spare_mu);
+  if (hipMemGetInfo(&free_bytes, &total) != hipSuccess) {
+    (void)hipGetLastError();
+    return;
+  }
+  if (c->F_bytes > free_bytes || free_bytes - c->F_bytes < total / 2 || g_spare_bytes + c->F_bytes > total / 4) return;
+  int cus = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess) return;
+  void* b = nullptr;
+  if (hipMalloc(&b, c->F_bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    return;
+  }
+  c->F2 = b;
+  c->pair = grlbm::pair_tiles(c->g, cus);
+  g_spare_bytes += c->F_bytes;
+  g_spare_owners.push_back(c);
+}
+
+// Frees c's second buffer; the caller holds g_spare_mu and c's work is done.
+void drop_spare(lbm_ctx* c) {
+  (void)hipFree(c->F2);
+  c->F2 = nullptr;
+  g_spare_bytes -= c->F_bytes;
+  g_spare_owners.erase(std::find(g_spare_owners.begin(), g_spare_owners.end(), c));
 }
 
 lbm_status drain_ring(lbm_ctx* c) {
@@ -371,25 +435,47 @@ lbm_status create_common(const lbm_params* p, void* buf, size_t bytes, void* str
     if (((uintptr_t)buf) % 256 != 0) return bail(fail(LBM_EINVAL, "buffer is not 256-byte aligned"));
     c->F = buf;
   } else {
-    if (hipMalloc(&c->F, c->F_bytes) != hipSuccess)
+    if (grlbm::dev_malloc(&c->F, c->F_bytes) != hipSuccess)
       return bail(fail(LBM_ENOMEM, "hipMalloc of %zu population bytes failed", c->F_bytes));
     c->own_F = true;
   }
-  if (hipMalloc(&c->ring, (size_t)kRingCap * kDiagVals * sizeof(float)) != hipSuccess)
+  if (grlbm::dev_malloc((void**)&c->ring, (size_t)kRingCap * kDiagVals * sizeof(float)) != hipSuccess)
     return bail(fail(LBM_ENOMEM, "hipMalloc of the diagnostic ring failed"));
   c->ring_steps.reserve(kRingCap);
+  if (pairs_fit(c)) take_spare(c);
   *out = c;
   return LBM_OK;
 }
 
 template <typename T>
 lbm_status dev_alloc(T** p, size_t count, const char* what) {
-  if (hipMalloc((void**)p, count * sizeof(T)) != hipSuccess)
+  if (grlbm::dev_malloc((void**)p, count * sizeof(T)) != hipSuccess)
     return fail(LBM_ENOMEM, "hipMalloc of %zu bytes (%s) failed", count * sizeof(T), what);
   return LBM_OK;
 }
 
 }  // namespace
+
+namespace grlbm {
+// Gives up the second buffers of the current device's contexts, each after the work
+// on its stream (but not one whose stream is being captured: that must not be waited
+// for).  True if there were any.
+static bool give_up_spares() {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return false;
+  std::lock_guard<std::mutex> lock(g_spare_mu);
+  const std::vector<lbm_ctx*> owners = g_spare_owners;
+  bool any = false;
+  for (lbm_ctx* c : owners) {
+    if (c->device != dev) continue;
+    std::lock_guard<std::mutex> use(c->F2_mu);
+    if (capturing(c->stream) || hipStreamSynchronize(c->stream) != hipSuccess) continue;
+    drop_spare(c);
+    any = true;
+  }
+  return any;
+}
+}  // namespace grlbm
 
 extern "C" {
 
@@ -445,7 +531,7 @@ lbm_status lbm_autotune(lbm_ctx* c, int32_t trial_steps, lbm_launch* best, float
   trial_steps += trial_steps & 1;  // whole even/odd pairs
   // the trials advance the state; a device copy puts it back after each
   void* snap = nullptr;
-  if (hipMalloc(&snap, c->F_bytes) != hipSuccess) {
+  if (grlbm::dev_malloc(&snap, c->F_bytes) != hipSuccess) {
     (void)hipGetLastError();
     return fail(LBM_ENOMEM, "snapshot of %zu bytes for autotuning failed", c->F_bytes);
   }
@@ -470,6 +556,7 @@ lbm_status lbm_autotune(lbm_ctx* c, int32_t trial_steps, lbm_launch* best, float
   lbm_status st = LBM_OK;
   float best_time = 1e30f;
   lbm_launch best_t = orig;
+  c->single_steps = true;
   if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)
     st = fail(LBM_EDEVICE, "event creation failed");
   for (size_t ci = 0; st == LBM_OK && ci < cands.size(); ++ci) {
@@ -507,6 +594,7 @@ lbm_status lbm_autotune(lbm_ctx* c, int32_t trial_steps, lbm_launch* best, float
   }
   if (e0) (void)hipEventDestroy(e0);
   if (e1) (void)hipEventDestroy(e1);
+  c->single_steps = false;
   // the state must be back before the snapshot goes, whatever happened above
   if (hipMemcpyAsync(c->F, snap, c->F_bytes, hipMemcpyDeviceToDevice, c->stream) != hipSuccess ||
       hipStreamSynchronize(c->stream) != hipSuccess) {
@@ -588,9 +676,34 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n, int32_t diag_every) {
     lbm_status st = ensure_partials(c);
     if (st != LBM_OK) return st;
   }
+  // Steps run in pairs (launch_pair) where a second buffer is there, from an odd step
+  // up to the next one with diagnostics; two pairs at a time, so that the state is
+  // back in the context's own buffer.  Not with a source or with the direct odd step
+  // asked for, and not under capture: a captured launch would keep the address of a
+  // buffer that may be given up later.
+  std::unique_lock<std::mutex> use_F2(c->F2_mu, std::defer_lock);
+  bool pairs = false;
+  if (n >= 4 && !c->src && c->odd_lds && !c->single_steps && !capturing(c->stream)) {
+    use_F2.lock();
+    pairs = c->F2 != nullptr;
+  }
   for (int64_t s = 0; s < n; ++s) {
     const int64_t t = c->step;
     const bool diag = diag_every > 0 && (t % diag_every) == 0;
+    if (pairs && (t & 1) != 0 && !diag) {
+      int64_t m = n - s;
+      if (diag_every > 0) m = std::min<int64_t>(m, diag_every - t % diag_every);
+      m = m / 4 * 4;
+      for (int64_t i = 0; i < m; i += 4) {
+        HIP_TRY(grlbm::launch_pair(L, c->pair, c->F, c->F2, c->stream));
+        HIP_TRY(grlbm::launch_pair(L, c->pair, c->F2, c->F, c->stream));
+        c->step += 4;
+      }
+      if (m > 0) {
+        s += m - 1;
+        continue;
+      }
+    }
     L.odd = (t & 1) != 0;
     L.diag = diag;
     L.skey = grlbm::step_key(t);
@@ -709,6 +822,10 @@ lbm_status lbm_destroy(lbm_ctx* c) {
   lbm_status st = LBM_OK;
   if (c->stream && hipStreamSynchronize(c->stream) != hipSuccess)
     st = fail(LBM_EDEVICE, "stream synchronisation failed during destroy");
+  {
+    std::lock_guard<std::mutex> lock(g_spare_mu);
+    if (c->F2) drop_spare(c);
+  }
   if (c->own_F && c->F) (void)hipFree(c->F);
   if (c->partials) (void)hipFree(c->partials);
   if (c->ring) (void)hipFree(c->ring);
@@ -726,7 +843,7 @@ lbm_status lbm_bw_probe(size_t bytes, int32_t iters, double* gbps) {
   hipEvent_t e0 = nullptr, e1 = nullptr;
   lbm_status st = LBM_OK;
   float best = 1e30f;
-  if (hipMalloc(&a, bytes) != hipSuccess || hipMalloc(&b, bytes) != hipSuccess) {
+  if (grlbm::dev_malloc(&a, bytes) != hipSuccess || grlbm::dev_malloc(&b, bytes) != hipSuccess) {
     st = fail(LBM_ENOMEM, "hipMalloc of 2 x %zu bytes failed", bytes);
     goto done;
   }

@@ -451,16 +451,16 @@ lbm_status lbm_batch_create(size_t arena_bytes, int32_t max_instances, int32_t m
     b->own_stream = true;
   }
   b->arena_bytes = arena_bytes / 256 * 256;
-  if (hipMalloc((void**)&b->arena, b->arena_bytes) != hipSuccess)
+  if (grlbm::dev_malloc((void**)&b->arena, b->arena_bytes) != hipSuccess)
     return bail(fail(LBM_ENOMEM, "hipMalloc of a %zu-byte arena failed", b->arena_bytes));
   b->free_list[0] = b->arena_bytes;
   b->max_inst = max_instances;
   b->max_tiles = max_tiles;
-  if (hipMalloc((void**)&b->d_insts, sizeof(BatchInst) * (size_t)max_instances) != hipSuccess ||
-      hipMalloc((void**)&b->d_tiles, sizeof(BatchTile) * (size_t)max_tiles * kGroups) != hipSuccess ||
-      hipMalloc((void**)&b->d_ntiles, sizeof(int32_t) * kGroups) != hipSuccess ||
-      hipMalloc((void**)&b->d_clock, sizeof(int64_t)) != hipSuccess ||
-      hipMalloc((void**)&b->d_flags, sizeof(int32_t) * (size_t)max_instances) != hipSuccess)
+  if (grlbm::dev_malloc((void**)&b->d_insts, sizeof(BatchInst) * (size_t)max_instances) != hipSuccess ||
+      grlbm::dev_malloc((void**)&b->d_tiles, sizeof(BatchTile) * (size_t)max_tiles * kGroups) != hipSuccess ||
+      grlbm::dev_malloc((void**)&b->d_ntiles, sizeof(int32_t) * kGroups) != hipSuccess ||
+      grlbm::dev_malloc((void**)&b->d_clock, sizeof(int64_t)) != hipSuccess ||
+      grlbm::dev_malloc((void**)&b->d_flags, sizeof(int32_t) * (size_t)max_instances) != hipSuccess)
     return bail(fail(LBM_ENOMEM, "hipMalloc of the batch tables failed"));
   const int64_t zero = 0;
   const int32_t zeros[kGroups] = {0, 0, 0, 0};
@@ -526,7 +526,7 @@ lbm_status lbm_batch_add(lbm_batch* b, const lbm_params* p, const double* Q, int
   h.d.inv_px = 1.0 / h.d.g.px;
   h.d.inv_ny = 1.0 / p->ny;
   double* dq = nullptr;
-  if (hipMalloc((void**)&dq, sizeof(double) * 5 * (size_t)N) != hipSuccess) {
+  if (grlbm::dev_malloc((void**)&dq, sizeof(double) * 5 * (size_t)N) != hipSuccess) {
     arena_free(b, off, bytes);
     return fail(LBM_ENOMEM, "staging allocation for the initial fields failed");
   }
@@ -577,7 +577,7 @@ lbm_status lbm_batch_moments(lbm_batch* b, int32_t id, double* Q_out) {
   const int64_t N = (int64_t)h.p.nx * h.p.ny * h.p.nz;
   const int el = h.p.storage == LBM_STORE_F16 ? 2 : 4;
   double* d = nullptr;
-  if (hipMalloc((void**)&d, sizeof(double) * 5 * (size_t)N) != hipSuccess)
+  if (grlbm::dev_malloc((void**)&d, sizeof(double) * 5 * (size_t)N) != hipSuccess)
     return fail(LBM_ENOMEM, "staging allocation for the moments failed");
   hipError_t e = grlbm::launch_gather(b->arena + (size_t)h.d.off * el, h.p.storage == LBM_STORE_F16, h.d.g, h.d.c, N,
                                       (completed_steps(b, h) & 1) != 0, 1, nullptr, d, b->stream);
@@ -597,7 +597,7 @@ lbm_status lbm_batch_populations(lbm_batch* b, int32_t id, float* f_out, int64_t
   const int64_t N = (int64_t)h.p.nx * h.p.ny * h.p.nz;
   const int el = h.p.storage == LBM_STORE_F16 ? 2 : 4;
   float* d = nullptr;
-  if (hipMalloc((void**)&d, sizeof(float) * 35 * (size_t)N) != hipSuccess)
+  if (grlbm::dev_malloc((void**)&d, sizeof(float) * 35 * (size_t)N) != hipSuccess)
     return fail(LBM_ENOMEM, "staging allocation for the populations failed");
   const int64_t done = completed_steps(b, h);
   hipError_t e = grlbm::launch_gather(b->arena + (size_t)h.d.off * el, h.p.storage == LBM_STORE_F16, h.d.g, h.d.c, N,
@@ -634,7 +634,7 @@ lbm_status lbm_batch_nonfinite(lbm_batch* b, int32_t* ids, int32_t max, int32_t*
     if (b->d_check) (void)hipFree(b->d_check);
     b->d_check = nullptr;
     b->check_cap = 0;
-    if (hipMalloc((void**)&b->d_check, sizeof(grlbm::CheckItem) * want) != hipSuccess)
+    if (grlbm::dev_malloc((void**)&b->d_check, sizeof(grlbm::CheckItem) * want) != hipSuccess)
       return fail(LBM_ENOMEM, "hipMalloc of %zu check items failed", want);
     b->check_cap = want;
   }
@@ -731,7 +731,7 @@ lbm_status lbm_batch_autotune(lbm_batch* b, int32_t trial_steps, lbm_batch_tunin
   const size_t extent = used_extent(b);
   char* snap = nullptr;
   if (extent > 0) {
-    if (hipMalloc((void**)&snap, extent) != hipSuccess) return fail(LBM_ENOMEM, "snapshot of %zu bytes failed", extent);
+    if (grlbm::dev_malloc((void**)&snap, extent) != hipSuccess) return fail(LBM_ENOMEM, "snapshot of %zu bytes failed", extent);
     HIP_TRY(hipMemcpyAsync(snap, b->arena, extent, hipMemcpyDeviceToDevice, b->stream));
   }
   const lbm_batch_tuning orig = b->tune;

@@ -18,6 +18,8 @@ namespace grlbm {
 
 lbm_status fail(lbm_status st, const char* fmt, ...);
 lbm_status validate(const lbm_params* p);
+// hipMalloc; out of memory, it first gives up the contexts' second population buffers.
+hipError_t dev_malloc(void** p, size_t bytes);
 // Initial conserved fields Q[5][N] (host) describe a physical state: every value
 // finite, density and pressure positive in every cell; EINVAL names the first cell
 // that is not.
@@ -94,6 +96,20 @@ bool even_pairs(const StepLaunch& L);        // the even step runs k_step_even_p
 int64_t pair_blocks(const StepLaunch& L);    // its blocks
 bool odd_pairs(const StepLaunch& L);         // the odd step runs k_step_odd_row_pairs
 int odd_pair_lds(const Grid& g);             // its dynamic LDS bytes per block
+// Two steps per pass over memory (grlbm_pair.hip): the tiles a grid is cut into.
+constexpr int kPairCells = 512;    // cells of a tile's plane at most: 8 waves ...
+constexpr int kPairThreads = 832;  // ... and 5 for the halo around it
+struct PairTiles {
+  int w, h, lz;         // cells of a tile along x, y and z (the last ones may be cut)
+  int ntx, nty, nseg;   // tiles along each axis
+  int per_xcd;          // tiles an XCD takes, of one z segment if by_plane, else of all
+  int by_plane;
+};
+PairTiles pair_tiles(const Grid& g, int cus);
+bool pair_worth(const Grid& g);  // a pair beats two single steps
+// An odd and the following even step from A to B (FP32 storage, no source, no
+// diagnostics); both hold the odd-parity layout.  Bitwise two launch_step calls.
+hipError_t launch_pair(const StepLaunch& L, const PairTiles& p, const void* A, void* B, hipStream_t s);
 hipError_t launch_finalize(const float* partials, int64_t nblocks, float* rec, hipStream_t s);
 hipError_t launch_init(void* F, bool f16, const Grid& g, const Coll& c, const InitCoef& ic, const double* Q,
                        int64_t N, hipStream_t s);
