@@ -6,6 +6,8 @@ state, flux with the Newtonian stress and the Fourier flux at constant mu and
 kappa, T = p/rho) and the fields of eq. 8 in SymPy, differentiates symbolically,
 eliminates common subexpressions, and prints a HIP kernel that evaluates the five
 components of S at every cell of an n^3 lattice in FP64 and stores them as FP32.
+The subexpressions that depend on one coordinate alone (all the sines and cosines)
+are evaluated once per coordinate of a block's tile and kept in LDS.
 The constants (rho0, U, P0, a, K, W, gamma, mu, kappa, lattice units) stay
 symbolic, so one kernel serves every resolution.
 
@@ -51,17 +53,60 @@ def source_expressions():
     return (x, y, z, t), c, S
 
 
+def ccode(e) -> str:
+    # a square as a product: pow() evaluates a logarithm and an exponential
+    return sp.ccode(e, user_functions={"Pow": [(lambda b, n: n == 2, lambda b, n: f"sq({b})"),
+                                               (lambda b, n: n == -1, lambda b, n: f"(1.0/({b}))")]})
+
+
 def generate() -> str:
-    (x, y, z, t), c, S = source_expressions()
+    axes, c, S = source_expressions()
+    t = axes[3]
+    axes = axes[:3]
     subs, red = sp.cse(S, symbols=sp.numbered_symbols("e"), optimizations="basic")
-    lines = []
+    # the coordinates each subexpression depends on
+    dep = {v: {v} for v in axes}
+    dep.update({v: set() for v in list(c.values()) + [t]})
     for sym, ex in subs:
-        lines.append(f"  const double {sym} = {sp.ccode(ex)};")
-    outs = [f"  S[{f} * N + n] = (float)({sp.ccode(red[f])});" for f in range(5)]
-    body = "\n".join(lines + outs)
-    for n in CONSTS:
-        body = body.replace("m_" + n, "m." + n)
-    return TEMPLATE.replace("@BODY@", body)
+        dep[sym] = set().union(*(dep[f] for f in ex.free_symbols))
+    single = {v: [(s, e) for s, e in subs if dep[s] == {v}] for v in axes}
+    common = [(s, e) for s, e in subs if not dep[s]]
+    mixed = [(s, e) for s, e in subs if len(dep[s]) > 1]
+    # what the cells use of each coordinate's values
+    used = set().union(*(e.free_symbols for _, e in mixed), *(e.free_symbols for e in red))
+    keep = {v: [s for s, _ in single[v] if s in used] for v in axes}
+
+    def code(pairs, indent):
+        return "\n".join(f"{indent}const double {s} = {ccode(e)};" for s, e in pairs)
+
+    def needed(pairs, exprs):
+        """The pairs that the expressions need, directly or through one another."""
+        want = set().union(*(e.free_symbols for e in exprs)) if exprs else set()
+        out = []
+        for s, e in reversed(pairs):
+            if s in want:
+                out.append((s, e))
+                want |= e.free_symbols
+        return out[::-1]
+
+    parts = {}
+    for v in axes:
+        base = needed(common, [e for _, e in single[v]])
+        store = "\n".join(f"    v{v}[{i}][i] = {s};" for i, s in enumerate(keep[v]))
+        parts[f"AXIS_{v}"] = "\n".join(x for x in (code(base, "    "), code(single[v], "    "), store) if x)
+        parts[f"N{v}"] = str(len(keep[v]))
+    parts["COMMON"] = code(needed(common, [e for _, e in mixed] + list(red)), "  ")
+    parts["LOADX"] = "\n".join(f"  const double {s} = vx[{i}][lane];" for i, s in enumerate(keep[axes[0]]))
+    parts["LOADYZ"] = "\n".join(f"    const double {s} = v{v}[{i}][{'jy' if v == axes[1] else 'jz'}];"
+                                for v in axes[1:] for i, s in enumerate(keep[v]))
+    parts["MIXED"] = code(mixed, "    ")
+    parts["OUT"] = "\n".join(f"    S[{f} * N + n] = (float)({ccode(red[f])});" for f in range(5))
+    out = TEMPLATE
+    for k, body in parts.items():
+        for n in CONSTS:
+            body = body.replace("m_" + n, "m." + n)
+        out = out.replace(f"@{k}@", body)
+    return out
 
 
 TEMPLATE = r'''// grlbm_mms.hip -- GENERATED by paper_2609_16361_amd/mms_codegen.py; do not edit.
@@ -79,15 +124,47 @@ TEMPLATE = r'''// grlbm_mms.hip -- GENERATED by paper_2609_16361_amd/mms_codegen
 
 namespace {
 
-__global__ void __launch_bounds__(256) k_mms_source(lbm_mms m, int32_t nx, int32_t ny, int32_t nz, double t,
-                                                     float* __restrict__ S) {
+// A block of 4 waves takes a tile of 64 x 8 x tz cells, a wave one row of 64 at a time.
+// Every sine and cosine depends on one coordinate: one wave per axis evaluates the
+// tile's, into LDS, and a cell needs about 350 FP64 operations besides (squares are
+// products: pow(x, 2) is not simplified in FP64 and was half of the work).  Bound by
+// FP64 issue and its latency.  On MI355X 128^3 took 229 us with all of it evaluated per
+// cell, 130 us with pow, 36 us now; 64^3 35 and 9 us, 24^3 11 and 6 us.
+constexpr int TX = 64, TY = 8, TZ = 4;  // tz is at most TZ
+
+__device__ __forceinline__ double sq(double v) { return v * v; }
+
+__global__ void __launch_bounds__(256, 3) k_mms_source(lbm_mms m, int32_t nx, int32_t ny, int32_t nz, int32_t tz,
+                                                        double t, float* __restrict__ S) {
+  __shared__ double vx[@Nx@][TX], vy[@Ny@][TY], vz[@Nz@][TZ];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int ntx = (nx + TX - 1) / TX, nty = (ny + TY - 1) / TY;
+  const int r = (int)(blockIdx.x / ntx);
+  const int x0 = (int)(blockIdx.x % ntx) * TX, y0 = (r % nty) * TY, z0 = (r / nty) * tz;
+  const int i = lane;
+  if (wave == 0) {
+    const double x = (double)(x0 + i);
+@AXIS_x@
+  } else if (wave == 1 && i < TY) {
+    const double y = (double)(y0 + i);
+@AXIS_y@
+  } else if (wave == 2 && i < tz) {
+    const double z = (double)(z0 + i);
+@AXIS_z@
+  }
+  __syncthreads();
+  if (x0 + lane >= nx) return;
   const int64_t N = (int64_t)nx * ny * nz;
-  const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= N) return;
-  const double x = (double)(n % nx);
-  const double y = (double)((n / nx) % ny);
-  const double z = (double)(n / ((int64_t)nx * ny));
-@BODY@
+@COMMON@
+@LOADX@
+  for (int row = wave; row < TY * tz; row += 4) {
+    const int jy = row % TY, jz = row / TY;
+    if (y0 + jy >= ny || z0 + jz >= nz) continue;
+    const int64_t n = x0 + lane + (int64_t)nx * (y0 + jy + (int64_t)ny * (z0 + jz));
+@LOADYZ@
+@MIXED@
+@OUT@
+  }
 }
 
 }  // namespace
@@ -98,9 +175,15 @@ extern "C" lbm_status lbm_mms_source(const lbm_mms* m, int32_t nx, int32_t ny, i
   if (nx < 1 || ny < 1 || nz < 1) return grlbm::fail(LBM_EINVAL, "empty lattice %d x %d x %d", nx, ny, nz);
   const int64_t N = (int64_t)nx * ny * nz;
   if (N > ((int64_t)1 << 31)) return grlbm::fail(LBM_EINVAL, "%lld cells exceed 2^31", (long long)N);
-  const unsigned blocks = (unsigned)((N + 255) / 256);
-  hipLaunchKernelGGL(k_mms_source, dim3(blocks), dim3(256), 0, (hipStream_t)hip_stream, *m, nx, ny, nz, t,
-                     S_dev);
+  // the thickest tiles that still give 512 blocks: thicker ones share more of the
+  // sines and cosines (128^3: 36 us with 4 planes, 40 with 2), thinner ones leave a
+  // wave fewer rows to do one after another (64^3: 8.9 us with 2 planes, 12.4 with 4)
+  const int64_t xy = (((int64_t)nx + TX - 1) / TX) * (((int64_t)ny + TY - 1) / TY);
+  int tz = TZ;
+  while (tz > 1 && xy * (((int64_t)nz + tz - 1) / tz) < 512) tz /= 2;
+  const int64_t tiles = xy * (((int64_t)nz + tz - 1) / tz);
+  hipLaunchKernelGGL(k_mms_source, dim3((unsigned)tiles), dim3(256), 0, (hipStream_t)hip_stream, *m, nx, ny, nz, tz,
+                     t, S_dev);
   HIP_TRY(hipGetLastError());
   return LBM_OK;
 }
