@@ -26,12 +26,14 @@
  * deviation f - w_i Q_ref from the equilibrium of a uniform reference state
  * (Sec. 2.2), Q_ref = (rho_ref, 0, 0, 0, E_ref).
  *
- * Step pairs.  With FP32 storage a context also keeps a second buffer of the same
- * size where the card has room to spare (it stays at least half free, and these
- * buffers together below a quarter of it): lbm_step then makes two steps per pass
- * over memory, alternating between the two buffers, and ends every call in the first.
- * The results are bitwise those of single steps.  The second buffers are given up
- * when an allocation of this library fails, and the contexts go on in single steps.
+ * Several steps per pass.  A context also keeps a second buffer of the same size where
+ * the card has room to spare (it stays at least half free, and these buffers together
+ * below a quarter of it), if its grid gains from it: with FP32 storage lbm_step then
+ * makes two steps per pass over memory, and on tubes (a cross-section of at most 25
+ * cells, FP32 or FP16) up to ten, alternating between the two buffers and ending every
+ * call in the first.  The results are bitwise those of single steps.  The second buffers
+ * are given up when an allocation of this library fails, and the contexts go on in
+ * single steps.
  *
  * Threading.  A context is not internally locked: use one context per host thread
  * at a time.  lbm_last_error is thread-local.
@@ -160,9 +162,9 @@ lbm_status lbm_init_fields_device(lbm_ctx* ctx, const double* Q_dev);
 /* Enqueue n >= 0 collide-and-stream steps on the context's stream (asynchronous).
  * If diag_every > 0, every step whose index t (completed steps before it) satisfies
  * t % diag_every == 0 also produces a diagnostic record (see lbm_diagnostics).
- * ESTATE before initialisation.  A call of four steps or more may make them in pairs
- * (above): from a step of odd index on, four at a time, up to the next step with
- * diagnostics.  On a stream under capture the steps are single. */
+ * ESTATE before initialisation.  A call of four steps or more may make several per
+ * pass (above), up to the next step with diagnostics.  On a stream under capture the
+ * steps are single. */
 lbm_status lbm_step(lbm_ctx* ctx, int64_t n, int32_t diag_every);
 
 /* Conserved fields of the current state (post-streaming, i.e. the state after the

@@ -283,10 +283,13 @@ struct lbm_ctx {
   void* F = nullptr;
   size_t F_bytes = 0;
   bool own_F = false;
-  // two steps per pass (launch_pair): the second population buffer, the grid's tiles,
-  // and the lock under which F2 is used or given up (give_up_spares)
+  // several steps per pass: the second population buffer, the lock under which it is
+  // used or given up (give_up_spares), the tube's windows (launch_tube) or else the
+  // grid's tiles (launch_pair)
   void* F2 = nullptr;
   std::mutex F2_mu;
+  int cus = 0;
+  grlbm::TubeShape tube{};
   grlbm::PairTiles pair{};
   bool single_steps = false;  // lbm_autotune times the single-step kernels
   int64_t step = 0;
@@ -342,9 +345,17 @@ std::mutex g_spare_mu;
 std::vector<lbm_ctx*> g_spare_owners;  // contexts that hold an F2
 size_t g_spare_bytes = 0;
 
-// Grids that step in pairs: FP32 storage, and 32-bit byte offsets reach two slots.
-bool pairs_fit(const lbm_ctx* c) {
-  return c->p.storage == LBM_STORE_F32 && c->g.S < (int64_t(1) << 29) && grlbm::pair_worth(c->g);
+// Picks the context's way to make several steps per pass, if it has one: tubes, and
+// pairs with FP32 storage where 32-bit byte offsets reach two slots.
+bool plan_passes(lbm_ctx* c) {
+  if (hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess || c->cus < 1)
+    return false;
+  const bool f16 = c->p.storage == LBM_STORE_F16;
+  c->tube = grlbm::tube_shape(c->g, f16, c->cus);
+  if (c->tube.lanes) return true;
+  if (f16 || c->g.S >= (int64_t(1) << 29) || !grlbm::pair_worth(c->g)) return false;
+  c->pair = grlbm::pair_tiles(c->g, c->cus);
+  return true;
 }
 
 void take_spare(lbm_ctx* c) {
@@ -355,15 +366,12 @@ void take_spare(lbm_ctx* c) {
     return;
   }
   if (c->F_bytes > free_bytes || free_bytes - c->F_bytes < total / 2 || g_spare_bytes + c->F_bytes > total / 4) return;
-  int cus = 0;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess) return;
   void* b = nullptr;
   if (hipMalloc(&b, c->F_bytes) != hipSuccess) {
     (void)hipGetLastError();
     return;
   }
   c->F2 = b;
-  c->pair = grlbm::pair_tiles(c->g, cus);
   g_spare_bytes += c->F_bytes;
   g_spare_owners.push_back(c);
 }
@@ -442,7 +450,7 @@ lbm_status create_common(const lbm_params* p, void* buf, size_t bytes, void* str
   if (grlbm::dev_malloc((void**)&c->ring, (size_t)kRingCap * kDiagVals * sizeof(float)) != hipSuccess)
     return bail(fail(LBM_ENOMEM, "hipMalloc of the diagnostic ring failed"));
   c->ring_steps.reserve(kRingCap);
-  if (pairs_fit(c)) take_spare(c);
+  if (plan_passes(c)) take_spare(c);
   *out = c;
   return LBM_OK;
 }
@@ -676,28 +684,43 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n, int32_t diag_every) {
     lbm_status st = ensure_partials(c);
     if (st != LBM_OK) return st;
   }
-  // Steps run in pairs (launch_pair) where a second buffer is there, from an odd step
-  // up to the next one with diagnostics; two pairs at a time, so that the state is
-  // back in the context's own buffer.  Not with a source or with the direct odd step
-  // asked for, and not under capture: a captured launch would keep the address of a
-  // buffer that may be given up later.
+  // Steps run several to a pass where a second buffer is there, up to the next step with
+  // diagnostics: tubes from an even step on, pairs from an odd one.  The passes of a run
+  // are even in number, so that the state is back in the context's own buffer.  Not with
+  // a source or with the direct odd step asked for, and not under capture: a captured
+  // launch would keep the address of a buffer that may be given up later.
   std::unique_lock<std::mutex> use_F2(c->F2_mu, std::defer_lock);
-  bool pairs = false;
+  bool passes = false;
   if (n >= 4 && !c->src && c->odd_lds && !c->single_steps && !capturing(c->stream)) {
     use_F2.lock();
-    pairs = c->F2 != nullptr;
+    passes = c->F2 != nullptr;
   }
   for (int64_t s = 0; s < n; ++s) {
     const int64_t t = c->step;
     const bool diag = diag_every > 0 && (t % diag_every) == 0;
-    if (pairs && (t & 1) != 0 && !diag) {
+    if (passes && !diag && ((t & 1) == 0) == (c->tube.lanes > 0)) {
       int64_t m = n - s;
       if (diag_every > 0) m = std::min<int64_t>(m, diag_every - t % diag_every);
-      m = m / 4 * 4;
-      for (int64_t i = 0; i < m; i += 4) {
-        HIP_TRY(grlbm::launch_pair(L, c->pair, c->F, c->F2, c->stream));
-        HIP_TRY(grlbm::launch_pair(L, c->pair, c->F2, c->F, c->stream));
-        c->step += 4;
+      if (c->tube.lanes) {
+        m = c->tube.steps > 2 ? m / 2 * 2 : m / 4 * 4;  // at least two steps a launch
+        const int64_t launches = m >= 4 ? (m + 2 * c->tube.steps - 1) / (2 * c->tube.steps) * 2 : 0;
+        void *from = c->F, *to = c->F2;
+        int64_t left = m / 2;  // in steps of two, dealt evenly
+        for (int64_t i = launches; i > 0; --i) {
+          const int two = (int)(left / i);
+          left -= two;
+          HIP_TRY(grlbm::launch_tube(L, c->tube, c->cus, from, to, 2 * two, t + m - 2 * (left + two), c->stream));
+          std::swap(from, to);
+        }
+        if (launches == 0) m = 0;
+        c->step += m;
+      } else {
+        m = m / 4 * 4;
+        for (int64_t i = 0; i < m; i += 4) {
+          HIP_TRY(grlbm::launch_pair(L, c->pair, c->F, c->F2, c->stream));
+          HIP_TRY(grlbm::launch_pair(L, c->pair, c->F2, c->F, c->stream));
+          c->step += 4;
+        }
       }
       if (m > 0) {
         s += m - 1;

@@ -110,6 +110,19 @@ bool pair_worth(const Grid& g);  // a pair beats two single steps
 // An odd and the following even step from A to B (FP32 storage, no source, no
 // diagnostics); both hold the odd-parity layout.  Bitwise two launch_step calls.
 hipError_t launch_pair(const StepLaunch& L, const PairTiles& p, const void* A, void* B, hipStream_t s);
+// Several steps per pass for tubes (grlbm_tube.hip): windows of `width` columns, of which
+// `inner` are stored, up to `steps` steps per launch (inner = width - 2 steps).
+constexpr int kTubeCross = 25;  // most cells of a cross-section
+constexpr int kTubeSteps = 10;  // most steps per launch
+struct TubeShape {
+  int lanes, width, inner, steps;
+};
+TubeShape tube_shape(const Grid& g, bool f16, int cus);
+int tube_lds(const TubeShape& sh, int64_t blocks, int cus);
+// `steps` (even, at most sh.steps) steps from the even step t0 on, from A to B; both hold
+// the even-parity layout.  Bitwise that many launch_step calls.
+hipError_t launch_tube(const StepLaunch& L, const TubeShape& sh, int cus, const void* A, void* B, int steps,
+                       int64_t t0, hipStream_t s);
 hipError_t launch_finalize(const float* partials, int64_t nblocks, float* rec, hipStream_t s);
 hipError_t launch_init(void* F, bool f16, const Grid& g, const Coll& c, const InitCoef& ic, const double* Q,
                        int64_t N, hipStream_t s);

@@ -1,0 +1,95 @@
+// grlbm_tube.hip -- k_step_tube, up to ten time steps of a tube per launch, and the rule
+// that picks its window and step count.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "grlbm_tube.hpp"
+
+namespace grlbm {
+
+// One block per window of a tube (tube_update).  On a long tube bound by VALU issue (the
+// window's ends are computed and dropped) and HBM together, on a short one by the
+// latency of a step in one wave per SIMD and of the launch.  Measured on MI355X, us per
+// step of a context on its own stream, 4 x 4 cross-section, single steps before -> now:
+// FP32 256 columns 4.3 -> 1.8, 4097 7.7 -> 3.0, 283000 (4.5 M cells) 230 -> 98; FP16 256
+// columns 4.4 -> 2.7, 4097 5.8 -> 4.1, 283000 117 -> 106.
+template <int COLL, typename T, int L>
+__global__ void __launch_bounds__(L, 4) k_step_tube(const T* __restrict__ A, T* __restrict__ B, Grid g, Coll c,
+                                                     TubeShape sh, int steps, int64_t t0) {
+  extern __shared__ float xs[];
+  tube_update<COLL, T, L>(A, B, g, c, (int)blockIdx.x * sh.inner, sh.width, sh.inner, steps, t0, xs);
+}
+
+// The window and the most steps per launch of a tube, by the estimated time per step
+// (lanes = 0: none, the grid is no tube or steps faster otherwise).  Blocks have 256 or
+// 512 lanes (4 or 2 on a CU at 92-111 registers and 30 or 60 KB of LDS).  A step takes
+// 0.55 + 0.56 w us with w waves per SIMD (FP16, whose stores round: 1.45 + 0.65 w), a
+// launch 3.6 us besides, and on a full card a turn of blocks moves its window through
+// HBM at 8 TB/s, counted in whole lines, partly under the other blocks' arithmetic.  More steps per launch share the
+// launch but drop more columns.  The estimates were within 20% of the timings over
+// tubes of 256 to 283000 columns with cross-sections of 1 to 25 cells, and the choice
+// within 10% of the best.  Against them stand the other ways to step: pairs (FP32,
+// about 4.5 us + cells / 28500 us) and single steps (FP16, 4.4 us + cells / 58000 us, or cells /
+// 37500 us beyond the caches; a tenth is left for the estimate's error).
+// Windows of cross-sections over 25 cells lose too much to their ends (FP32 8 x 4 cells,
+// 4097 columns: 11.4 us per step, 9.4 in pairs).
+TubeShape tube_shape(const Grid& g, bool f16, int cus) {
+  TubeShape best{};
+  const int64_t cross = (int64_t)g.ny * g.nz;
+  if (cross > kTubeCross) return best;
+  const double cells = (double)cross * g.nx;
+  double best_cost = f16 ? 0.9 * std::max(4.4 + cells / 58000.0, cells / 37500.0) : 4.5 + cells / 28500.0;
+  for (int lanes : {256, 512}) {
+    const int width = (int)(lanes / cross), resident = 1024 / lanes;
+    for (int steps = 2; steps <= kTubeSteps; steps += 2) {
+      const int inner = width - 2 * steps;
+      if (inner < 2) break;
+      const int64_t blocks = (g.nx + inner - 1) / inner;
+      const int64_t slots = (int64_t)cus * resident;
+      const double turns = (double)((blocks + slots - 1) / slots);
+      const double waves = (double)std::min<int64_t>(resident, (blocks + cus - 1) / cus) * lanes / 256.0;
+      const double issue = steps * (f16 ? 1.45 + 0.65 * waves : 0.55 + 0.56 * waves);
+      const double el = f16 ? 2.0 : 4.0, line = (width - 1) * el + 128.0;  // bytes of a row's lines
+      const double memory = 70.0 * cross * line * (double)std::min<int64_t>(blocks, slots) / 8.0e6;
+      const double cost =
+          (3.6 + turns * (std::max(issue, memory) + 0.25 * std::min(issue, memory))) / steps;
+      if (cost < best_cost) {
+        best_cost = cost;
+        best.lanes = lanes;
+        best.width = width;
+        best.inner = inner;
+        best.steps = steps;
+      }
+    }
+  }
+  return best;
+}
+
+// Dynamic LDS of a block.  Up to two blocks per CU, the reservation keeps the hardware
+// from putting more on a CU than even dealing gives.
+int tube_lds(const TubeShape& sh, int64_t blocks, int cus) {
+  const int need = 30 * (int)sizeof(float) * sh.lanes;
+  const int apart = blocks <= cus ? 82 * 1024 : (blocks <= 2 * cus ? 55 * 1024 : 0);
+  return std::max(need, apart);
+}
+
+hipError_t launch_tube(const StepLaunch& L, const TubeShape& sh, int cus, const void* A, void* B, int steps,
+                       int64_t t0, hipStream_t s) {
+  const int64_t blocks = (L.g.nx + sh.inner - 1) / sh.inner;
+  auto go = [&](auto kernel, auto* a, auto* b) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(sh.lanes), tube_lds(sh, blocks, cus), s, a, b, L.g, L.c,
+                       sh, steps, t0);
+    return hipGetLastError();
+  };
+  auto typed = [&](auto* a, auto* b) {
+    using T = std::remove_pointer_t<decltype(b)>;
+    if (sh.lanes == 256)
+      return L.coll == 0 ? go(k_step_tube<0, T, 256>, a, b) : go(k_step_tube<1, T, 256>, a, b);
+    return L.coll == 0 ? go(k_step_tube<0, T, 512>, a, b) : go(k_step_tube<1, T, 512>, a, b);
+  };
+  if (L.f16) return typed((const _Float16*)A, (_Float16*)B);
+  return typed((const float*)A, (float*)B);
+}
+
+}  // namespace grlbm
