@@ -281,7 +281,9 @@ lbm_status lbm_step_noalloc(const lbm_params* p, void* F_dev, int64_t step, int6
  * consecutive cells of one instance), and time loops of `graph_steps` steps replay one captured
  * HIP graph.  Every instance keeps its own step count: it is at its step 0 when
  * added, advances with each lbm_batch_run step until it has made the number of
- * steps it was added with, then stays frozen until removed.  Results are bitwise
+ * steps it was added with, then stays frozen until removed.  As in a context, tubes and
+ * FP32 grids make several steps per pass where a second arena (of at most 4 GiB, for
+ * the front of the first) could be had.  Results are bitwise
  * those of the same instance run alone in a context (lbm_create/lbm_step).  All
  * calls use the batch's stream; calls that touch host memory synchronise it. */
 typedef struct lbm_batch lbm_batch; /* opaque */

@@ -219,7 +219,63 @@ lbm_status scales_from_pops(Coll& c, const float* f_dev, int64_t N, hipStream_t 
   return st;
 }
 
-static bool give_up_spares();
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone;
+}
+
+static std::mutex g_spare_mu;           // taken before any Spare::mu
+static std::vector<Spare*> g_spares;    // those that hold a buffer
+static size_t g_spare_bytes = 0;
+
+void take_spare(Spare& s, size_t bytes) {
+  size_t free_bytes = 0, total = 0;
+  std::lock_guard<std::mutex> lock(g_spare_mu);
+  if (hipMemGetInfo(&free_bytes, &total) != hipSuccess) {
+    (void)hipGetLastError();
+    return;
+  }
+  if (bytes > free_bytes || g_spare_bytes + bytes > total / 4 ||
+      (free_bytes - bytes < total / 2 && bytes > free_bytes / 8))
+    return;
+  void* b = nullptr;
+  if (hipMalloc(&b, bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    return;
+  }
+  s.buf = b;
+  s.bytes = bytes;
+  g_spare_bytes += bytes;
+  g_spares.push_back(&s);
+}
+
+static void drop_spare_locked(Spare& s) {
+  (void)hipFree(s.buf);
+  s.buf = nullptr;
+  g_spare_bytes -= s.bytes;
+  g_spares.erase(std::find(g_spares.begin(), g_spares.end(), &s));
+}
+
+void drop_spare(Spare& s) {
+  std::lock_guard<std::mutex> lock(g_spare_mu);
+  if (s.buf) drop_spare_locked(s);
+}
+
+static bool give_up_spares() {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return false;
+  std::lock_guard<std::mutex> lock(g_spare_mu);
+  const std::vector<Spare*> all = g_spares;
+  bool any = false;
+  for (Spare* s : all) {
+    if (s->device != dev) continue;
+    std::lock_guard<std::mutex> use(s->mu);
+    if (capturing(s->stream) || hipStreamSynchronize(s->stream) != hipSuccess) continue;
+    drop_spare_locked(*s);
+    any = true;
+  }
+  return any;
+}
 
 hipError_t dev_malloc(void** p, size_t bytes) {
   hipError_t e = hipMalloc(p, bytes);
@@ -283,11 +339,9 @@ struct lbm_ctx {
   void* F = nullptr;
   size_t F_bytes = 0;
   bool own_F = false;
-  // several steps per pass: the second population buffer, the lock under which it is
-  // used or given up (give_up_spares), the tube's windows (launch_tube) or else the
-  // grid's tiles (launch_pair)
-  void* F2 = nullptr;
-  std::mutex F2_mu;
+  // several steps per pass: the second population buffer, the tube's windows
+  // (launch_tube) or else the grid's tiles (launch_pair)
+  grlbm::Spare spare;
   int cus = 0;
   grlbm::TubeShape tube{};
   grlbm::PairTiles pair{};
@@ -332,19 +386,6 @@ lbm_status ensure_partials(lbm_ctx* c) {
   return LBM_OK;
 }
 
-bool capturing(hipStream_t s) {
-  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  return hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone;
-}
-
-// Second population buffers.  They are workspace: a context steps the same without
-// one, only slower.  So a context takes one only while plenty of the card is free,
-// all of them together stay below a quarter of it, and where an allocation of this
-// library fails they are given up and the allocation is tried again.
-std::mutex g_spare_mu;
-std::vector<lbm_ctx*> g_spare_owners;  // contexts that hold an F2
-size_t g_spare_bytes = 0;
-
 // Picks the context's way to make several steps per pass, if it has one: tubes, and
 // pairs with FP32 storage where 32-bit byte offsets reach two slots.
 bool plan_passes(lbm_ctx* c) {
@@ -356,32 +397,6 @@ bool plan_passes(lbm_ctx* c) {
   if (f16 || c->g.S >= (int64_t(1) << 29) || !grlbm::pair_worth(c->g)) return false;
   c->pair = grlbm::pair_tiles(c->g, c->cus);
   return true;
-}
-
-void take_spare(lbm_ctx* c) {
-  size_t free_bytes = 0, total = 0;
-  std::lock_guard<std::mutex> lock(g_spare_mu);
-  if (hipMemGetInfo(&free_bytes, &total) != hipSuccess) {
-    (void)hipGetLastError();
-    return;
-  }
-  if (c->F_bytes > free_bytes || free_bytes - c->F_bytes < total / 2 || g_spare_bytes + c->F_bytes > total / 4) return;
-  void* b = nullptr;
-  if (hipMalloc(&b, c->F_bytes) != hipSuccess) {
-    (void)hipGetLastError();
-    return;
-  }
-  c->F2 = b;
-  g_spare_bytes += c->F_bytes;
-  g_spare_owners.push_back(c);
-}
-
-// Frees c's second buffer; the caller holds g_spare_mu and c's work is done.
-void drop_spare(lbm_ctx* c) {
-  (void)hipFree(c->F2);
-  c->F2 = nullptr;
-  g_spare_bytes -= c->F_bytes;
-  g_spare_owners.erase(std::find(g_spare_owners.begin(), g_spare_owners.end(), c));
 }
 
 lbm_status drain_ring(lbm_ctx* c) {
@@ -450,7 +465,9 @@ lbm_status create_common(const lbm_params* p, void* buf, size_t bytes, void* str
   if (grlbm::dev_malloc((void**)&c->ring, (size_t)kRingCap * kDiagVals * sizeof(float)) != hipSuccess)
     return bail(fail(LBM_ENOMEM, "hipMalloc of the diagnostic ring failed"));
   c->ring_steps.reserve(kRingCap);
-  if (plan_passes(c)) take_spare(c);
+  c->spare.device = c->device;
+  c->spare.stream = c->stream;
+  if (plan_passes(c)) grlbm::take_spare(c->spare, c->F_bytes);
   *out = c;
   return LBM_OK;
 }
@@ -463,27 +480,6 @@ lbm_status dev_alloc(T** p, size_t count, const char* what) {
 }
 
 }  // namespace
-
-namespace grlbm {
-// Gives up the second buffers of the current device's contexts, each after the work
-// on its stream (but not one whose stream is being captured: that must not be waited
-// for).  True if there were any.
-static bool give_up_spares() {
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return false;
-  std::lock_guard<std::mutex> lock(g_spare_mu);
-  const std::vector<lbm_ctx*> owners = g_spare_owners;
-  bool any = false;
-  for (lbm_ctx* c : owners) {
-    if (c->device != dev) continue;
-    std::lock_guard<std::mutex> use(c->F2_mu);
-    if (capturing(c->stream) || hipStreamSynchronize(c->stream) != hipSuccess) continue;
-    drop_spare(c);
-    any = true;
-  }
-  return any;
-}
-}  // namespace grlbm
 
 extern "C" {
 
@@ -689,11 +685,11 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n, int32_t diag_every) {
   // are even in number, so that the state is back in the context's own buffer.  Not with
   // a source or with the direct odd step asked for, and not under capture: a captured
   // launch would keep the address of a buffer that may be given up later.
-  std::unique_lock<std::mutex> use_F2(c->F2_mu, std::defer_lock);
+  std::unique_lock<std::mutex> use_spare(c->spare.mu, std::defer_lock);
   bool passes = false;
-  if (n >= 4 && !c->src && c->odd_lds && !c->single_steps && !capturing(c->stream)) {
-    use_F2.lock();
-    passes = c->F2 != nullptr;
+  if (n >= 4 && !c->src && c->odd_lds && !c->single_steps && !grlbm::capturing(c->stream)) {
+    use_spare.lock();
+    passes = c->spare.buf != nullptr;
   }
   for (int64_t s = 0; s < n; ++s) {
     const int64_t t = c->step;
@@ -704,7 +700,7 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n, int32_t diag_every) {
       if (c->tube.lanes) {
         m = c->tube.steps > 2 ? m / 2 * 2 : m / 4 * 4;  // at least two steps a launch
         const int64_t launches = m >= 4 ? (m + 2 * c->tube.steps - 1) / (2 * c->tube.steps) * 2 : 0;
-        void *from = c->F, *to = c->F2;
+        void *from = c->F, *to = c->spare.buf;
         int64_t left = m / 2;  // in steps of two, dealt evenly
         for (int64_t i = launches; i > 0; --i) {
           const int two = (int)(left / i);
@@ -717,8 +713,8 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n, int32_t diag_every) {
       } else {
         m = m / 4 * 4;
         for (int64_t i = 0; i < m; i += 4) {
-          HIP_TRY(grlbm::launch_pair(L, c->pair, c->F, c->F2, c->stream));
-          HIP_TRY(grlbm::launch_pair(L, c->pair, c->F2, c->F, c->stream));
+          HIP_TRY(grlbm::launch_pair(L, c->pair, c->F, c->spare.buf, c->stream));
+          HIP_TRY(grlbm::launch_pair(L, c->pair, c->spare.buf, c->F, c->stream));
           c->step += 4;
         }
       }
@@ -845,10 +841,7 @@ lbm_status lbm_destroy(lbm_ctx* c) {
   lbm_status st = LBM_OK;
   if (c->stream && hipStreamSynchronize(c->stream) != hipSuccess)
     st = fail(LBM_EDEVICE, "stream synchronisation failed during destroy");
-  {
-    std::lock_guard<std::mutex> lock(g_spare_mu);
-    if (c->F2) drop_spare(c);
-  }
+  grlbm::drop_spare(c->spare);
   if (c->own_F && c->F) (void)hipFree(c->F);
   if (c->partials) (void)hipFree(c->partials);
   if (c->ring) (void)hipFree(c->ring);

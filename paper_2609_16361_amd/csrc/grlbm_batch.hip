@@ -19,12 +19,17 @@
 #include <algorithm>
 #include <cstring>
 #include <map>
+#include <mutex>
 #include <new>
+#include <type_traits>
+#include <utility>
 #include <vector>
 
 #include "../../include/grlbm.h"
 #include "grlbm_device.hpp"
 #include "grlbm_internal.h"
+#include "grlbm_pair.hpp"
+#include "grlbm_tube.hpp"
 
 namespace grlbm {
 
@@ -38,6 +43,8 @@ struct BatchInst {
   double inv_ny;
   int32_t cells;    // px * ny * nz: the elements the instance's rows span
   int32_t pad_;
+  TubeShape tube;   // windows of k_batch_tube, or
+  PairTiles pair;   // tiles of k_batch_pair, where the instance makes several steps a pass
 };
 
 // A tile is `blockDim.x` consecutive element indices of one instance (it may span
@@ -45,6 +52,12 @@ struct BatchInst {
 struct BatchTile {
   int32_t inst;
   int32_t tile;  // tile index within the instance: cells [tile * blockDim.x, ...)
+};
+
+// A run of a tile list.
+struct TileRun {
+  int32_t start;
+  int32_t count;
 };
 
 // q = n / d and r = n % d for 0 <= n < 2^31: the FP64 product is within one of the
@@ -65,11 +78,12 @@ __device__ __forceinline__ int div_exact(int n, int d, double inv_d, int& r) {
 template <int COLL, typename T, bool NT>
 __global__ void __launch_bounds__(1024) k_batch_step(T* __restrict__ arena, const BatchInst* __restrict__ insts,
                                                       const BatchTile* __restrict__ tiles,
-                                                      const int32_t* __restrict__ ntiles,
+                                                      const TileRun* __restrict__ run,
                                                       const int64_t* __restrict__ clock, int32_t j) {
   extern __shared__ float xs[];  // x slots of an odd-step tile (tile_update_odd)
-  const int32_t nt = *ntiles;
+  const int32_t nt = run->count;
   const int64_t t = *clock + j;
+  tiles += run->start;
   for (int32_t tile = blockIdx.x; tile < nt; tile += gridDim.x) {
     const BatchTile bt = tiles[tile];
     const BatchInst* I = insts + bt.inst;
@@ -107,6 +121,66 @@ __global__ void __launch_bounds__(1024) k_batch_step(T* __restrict__ arena, cons
       cell_update<false, COLL, T, true, false, NT>(F, g, c, x, y, z, nullptr, skey);
     }
   }
+}
+
+// The tile of this block: neighbouring tiles, which share halo lines, on one XCD (blocks
+// are dealt to the 8 XCDs in turn).  -1: none.
+__device__ __forceinline__ int32_t xcd_tile(int32_t count) {
+  const int32_t per = (count + 7) / 8, i = (int32_t)(blockIdx.x / 8);
+  const int32_t tile = (int32_t)(blockIdx.x % 8) * per + i;
+  return i < per && tile < count ? tile : -1;
+}
+
+// An odd and the following even step (steps j and j + 1 after the clock) of the FP32
+// instances that step in pairs, one tile per block, from one arena to the other at the
+// same offsets.  The host lists only instances at even parity and with all the steps of
+// the run ahead of them; those that have finished since are skipped.  Every instance
+// takes the zero-gradient form, as in k_batch_step.  On a serving mix of 24 requests the
+// FP32 vortices (10 of 32^3-55^3) and tubes took 63 us per step in single steps; the
+// vortices now take 33 and the tubes 9 (k_batch_tube).
+template <int COLL>
+__global__ void __launch_bounds__(kPairThreads) k_batch_pair(const char* __restrict__ from, char* __restrict__ to,
+                                                              const BatchInst* __restrict__ insts,
+                                                              const BatchTile* __restrict__ tiles,
+                                                              const TileRun* __restrict__ run,
+                                                              const int64_t* __restrict__ clock, int32_t j) {
+  extern __shared__ float xs[];
+  const int32_t i = xcd_tile(run->count);
+  if (i < 0) return;
+  const BatchTile bt = tiles[run->start + i];
+  const BatchInst* I = insts + bt.inst;
+  if (*clock + j >= I->t_end) return;
+  const Grid g = I->g;
+  const Coll c = I->c;
+  const PairTiles pt = I->pair;
+  const int nxy = pt.ntx * pt.nty;
+  const int seg = bt.tile / nxy;
+  pair_update<COLL, true, false>(reinterpret_cast<const float*>(from) + I->off, reinterpret_cast<float*>(to) + I->off,
+                                 g, c, pt, seg, bt.tile - seg * nxy, xs);
+}
+
+// `steps` (even) steps from step j after the clock on of the instances that are tubes,
+// one window per block, from one arena to the other.  The batch of 64 Becker tubes
+// (4.5 M cells, FP32) took 237 us per step in single steps and takes 85 now; the FP16
+// tubes of the serving mix 17 and 10.
+template <int COLL, typename T, int L>
+__global__ void __launch_bounds__(L, 4) k_batch_tube(const char* __restrict__ from, char* __restrict__ to,
+                                                      const BatchInst* __restrict__ insts,
+                                                      const BatchTile* __restrict__ tiles,
+                                                      const TileRun* __restrict__ run,
+                                                      const int64_t* __restrict__ clock, int32_t j, int32_t steps) {
+  extern __shared__ float xs[];
+  const int32_t i = xcd_tile(run->count);
+  if (i < 0) return;
+  const BatchTile bt = tiles[run->start + i];
+  const BatchInst* I = insts + bt.inst;
+  const int64_t t = *clock + j;
+  if (t >= I->t_end) return;
+  const Grid g = I->g;
+  const Coll c = I->c;
+  const TubeShape sh = I->tube;
+  tube_update<COLL, T, L>(reinterpret_cast<const T*>(from) + I->off, reinterpret_cast<T*>(to) + I->off, g, c,
+                          bt.tile * sh.inner, sh.width, sh.inner, steps, t - I->t_start, xs);
 }
 
 __global__ void k_batch_advance(int64_t* clock, int32_t n) {
@@ -159,13 +233,20 @@ __global__ void __launch_bounds__(256) k_batch_nonfinite(const char* __restrict_
 
 using grlbm::BatchInst;
 using grlbm::BatchTile;
+using grlbm::TileRun;
 using grlbm::fail;
 
 namespace {
 
 constexpr int kGroups = 4;  // (collision, storage) pairs
+constexpr size_t kSpareArena = size_t(4) << 30;  // most of the arena that has a second one
 
 int group_of(const lbm_params* p) { return p->collision * 2 + (p->storage == LBM_STORE_F16 ? 1 : 0); }
+
+// The runs of a group's tile lists: the tiles of single steps, ordered by how their
+// instance steps in a fast run (singly, in pairs, as a tube), and the tiles of pairs and
+// the windows of tubes.
+enum { kAll, kSingle, kPaired, kPairTiles, kWindows, kRuns };
 
 struct HostInst {
   bool live = false;
@@ -173,6 +254,8 @@ struct HostInst {
   BatchInst d{};
   size_t bytes = 0;
   int group = 0;
+  int pair_cus = 0;  // the share of the card that d.pair was chosen for
+  int how = kSingle; // its steps in fast runs: kSingle, kPaired or kWindows
 };
 
 }  // namespace
@@ -187,8 +270,9 @@ struct lbm_batch {
   int32_t max_inst = 0;
   int32_t max_tiles = 0;
   BatchInst* d_insts = nullptr;
-  BatchTile* d_tiles = nullptr;      // kGroups segments of max_tiles
-  int32_t* d_ntiles = nullptr;       // kGroups counts
+  BatchTile* d_tiles = nullptr;      // kGroups segments of max_tiles: tiles of single steps
+  BatchTile* d_multi = nullptr;      // the same for pair tiles and tube windows
+  TileRun* d_runs = nullptr;         // kGroups times kRuns
   int64_t* d_clock = nullptr;
   grlbm::CheckItem* d_check = nullptr;  // items of the divergence check (grown on demand)
   size_t check_cap = 0;
@@ -198,10 +282,17 @@ struct lbm_batch {
   int32_t graph_steps = 16;
   lbm_batch_tuning tune{};
   bool dirty = true;
-  int32_t ntiles_host[kGroups] = {0, 0, 0, 0};
-  hipGraphExec_t graph = nullptr;
-  unsigned graph_groups = 0;  // bitmask of groups captured
-  int32_t graph_grid[kGroups] = {0, 0, 0, 0};  // launch grids baked into the graph
+  TileRun runs[kGroups][kRuns] = {};
+  // the second arena, for the instances that lie in its reach, and the tube passes of
+  // each group: lanes (0: no tubes) and most steps per launch
+  grlbm::Spare spare;
+  int32_t tube_lanes[kGroups] = {}, tube_steps[kGroups] = {};
+  bool single_steps = false;  // lbm_batch_autotune times the single-step kernels
+  // captured graphs of graph_steps steps, all single and fast, and what they hold
+  struct Graph {
+    hipGraphExec_t exec = nullptr;
+    int32_t plan[kGroups * (kRuns + 2)] = {};
+  } graphs[2];
 };
 
 namespace {
@@ -211,32 +302,125 @@ int64_t inst_tiles(const lbm_params* p, int block) {
   return (n + block - 1) / block;
 }
 
-lbm_status upload(lbm_batch* b) {
-  if (!b->dirty) return LBM_OK;
-  std::vector<BatchTile> tiles[kGroups];
+// Chooses how each live instance makes its steps in fast runs.  Tubes and FP32 grids do
+// several per pass if they lie in reach of the second arena and are at an even step now
+// (runs of an odd number of steps list the instances anew).
+void plan_passes(lbm_batch* b) {
+  for (HostInst& h : b->insts) h.how = kSingle;
+  for (int g = 0; g < kGroups; ++g) b->tube_lanes[g] = 0;
+  if (!b->spare.buf) return;
+  double pair_cells[kGroups] = {}, tube_cells[kGroups] = {};
+  std::vector<int32_t> tubes[kGroups];
   for (int32_t id = 0; id < (int32_t)b->insts.size(); ++id) {
     HostInst& h = b->insts[id];
-    if (!h.live) continue;
-    // an instance that has completed its steps keeps its slot but no tiles
-    if (h.d.t_end <= b->clock) continue;
-    const int64_t n = inst_tiles(&h.p, b->tune.block);
-    for (int64_t t = 0; t < n; ++t) tiles[h.group].push_back({id, (int32_t)t});
+    if (!h.live || h.d.t_end <= b->clock || ((b->clock - h.d.t_start) & 1) != 0) continue;
+    const bool f16 = h.p.storage == LBM_STORE_F16;
+    if ((size_t)h.d.off * (f16 ? 2 : 4) + h.bytes > b->spare.bytes) continue;
+    const double cells = (double)h.p.nx * h.p.ny * h.p.nz;
+    if ((int64_t)h.p.ny * h.p.nz <= grlbm::kTubeCross) {
+      tubes[h.group].push_back(id);
+      tube_cells[h.group] += cells;
+    } else if (!f16 && h.d.g.S < (int64_t(1) << 29) && grlbm::pair_worth(h.d.g)) {
+      h.how = kPaired;
+      pair_cells[h.group] += cells;
+    }
   }
-  for (int g = 0; g < kGroups; ++g)
+  for (int g = 0; g < kGroups; ++g) {
+    // the tubes of a group share a launch, hence its lanes and steps: the cheapest for
+    // their windows together.  Against them stand single steps, about 4 us + cells /
+    // 18000 us (FP32) or / 24000 us (FP16) in a batch.
+    const bool f16 = (g & 1) != 0;
+    double best = 4.0 + tube_cells[g] / (f16 ? 24000.0 : 18000.0);
+    for (int lanes : {256, 512})
+      for (int steps = 2; steps <= grlbm::kTubeSteps; steps += 2) {
+        int64_t blocks = 0, cross = 0;
+        for (int32_t id : tubes[g]) {
+          const lbm_params& p = b->insts[id].p;
+          cross = (int64_t)p.ny * p.nz;
+          const int inner = (int)(lanes / cross) - 2 * steps;
+          if (inner < 2) blocks = INT32_MAX;
+          if (blocks < INT32_MAX) blocks += (p.nx + inner - 1) / inner;
+        }
+        if (blocks == 0 || blocks >= INT32_MAX) continue;
+        const int width = (int)(lanes / cross);
+        const double cost = grlbm::tube_price({lanes, width, width - 2 * steps, steps}, cross, blocks, f16, b->num_cus);
+        if (cost < best) {
+          best = cost;
+          b->tube_lanes[g] = lanes;
+          b->tube_steps[g] = steps;
+        }
+      }
+    for (int32_t id : tubes[g]) {
+      HostInst& h = b->insts[id];
+      if (!b->tube_lanes[g]) continue;
+      const int width = b->tube_lanes[g] / (h.p.ny * h.p.nz);
+      h.d.tube = {b->tube_lanes[g], width, width - 2 * b->tube_steps[g], b->tube_steps[g]};
+      h.how = kWindows;
+    }
+  }
+  for (HostInst& h : b->insts) {
+    if (h.how != kPaired) continue;
+    // tiles for the instance's share of the card, rounded down (the shares must not add up
+    // to more than the card, or its last tiles run alone) to three binary digits, so that
+    // small changes of the batch keep them
+    const double cells = (double)h.p.nx * h.p.ny * h.p.nz;
+    int cus = std::max(1, (int)(b->num_cus * (cells / pair_cells[h.group])));
+    for (int drop = 1; cus / drop >= 8; drop *= 2) cus = cus / drop * drop;
+    if (h.pair_cus != cus) {
+      h.d.pair = grlbm::pair_tiles(h.d.g, cus, true);
+      h.pair_cus = cus;
+    }
+  }
+}
+
+lbm_status upload(lbm_batch* b) {
+  if (!b->dirty) return LBM_OK;
+  plan_passes(b);
+  std::vector<BatchTile> tiles[kGroups], multi[kGroups];
+  for (int g = 0; g < kGroups; ++g) {
+    TileRun* runs = b->runs[g];
+    for (int pass : {kSingle, kPaired, kWindows}) {
+      const int32_t t0 = (int32_t)tiles[g].size(), m0 = (int32_t)multi[g].size();
+      for (int32_t id = 0; id < (int32_t)b->insts.size(); ++id) {
+        const HostInst& h = b->insts[id];
+        // an instance that has completed its steps keeps its slot but no tiles
+        if (!h.live || h.group != g || h.how != pass || h.d.t_end <= b->clock) continue;
+        const int64_t n = inst_tiles(&h.p, b->tune.block);
+        for (int64_t t = 0; t < n; ++t) tiles[g].push_back({id, (int32_t)t});
+        int64_t m = 0;
+        if (pass == kPaired) m = (int64_t)h.d.pair.ntx * h.d.pair.nty * h.d.pair.nseg;
+        if (pass == kWindows) m = ((int64_t)h.p.nx + h.d.tube.inner - 1) / h.d.tube.inner;
+        for (int64_t t = 0; t < m; ++t) multi[g].push_back({id, (int32_t)t});
+      }
+      const int32_t tn = (int32_t)tiles[g].size() - t0, mn = (int32_t)multi[g].size() - m0;
+      if (pass == kSingle) runs[kSingle] = {t0, tn};
+      if (pass == kPaired) runs[kPaired] = {t0, tn};
+      if (pass == kPaired) runs[kPairTiles] = {m0, mn};
+      if (pass == kWindows) runs[kWindows] = {m0, mn};
+    }
+    runs[kAll] = {0, (int32_t)tiles[g].size()};
     if ((int64_t)tiles[g].size() > b->max_tiles)
       return fail(LBM_ENOMEM, "tile list of %zu exceeds the batch capacity %d", tiles[g].size(), b->max_tiles);
+    if ((int64_t)multi[g].size() > b->max_tiles) {  // no room for their tiles: single steps
+      runs[kSingle] = runs[kAll];
+      runs[kPaired] = runs[kPairTiles] = runs[kWindows] = {0, 0};
+      multi[g].clear();
+    }
+  }
   std::vector<BatchInst> desc(b->insts.size());
   for (size_t i = 0; i < b->insts.size(); ++i) desc[i] = b->insts[i].d;
   if (!desc.empty())
     HIP_TRY(hipMemcpyAsync(b->d_insts, desc.data(), desc.size() * sizeof(BatchInst), hipMemcpyHostToDevice,
                            b->stream));
   for (int g = 0; g < kGroups; ++g) {
-    b->ntiles_host[g] = (int32_t)tiles[g].size();
     if (!tiles[g].empty())
       HIP_TRY(hipMemcpyAsync(b->d_tiles + (size_t)g * b->max_tiles, tiles[g].data(),
                              tiles[g].size() * sizeof(BatchTile), hipMemcpyHostToDevice, b->stream));
+    if (!multi[g].empty())
+      HIP_TRY(hipMemcpyAsync(b->d_multi + (size_t)g * b->max_tiles, multi[g].data(),
+                             multi[g].size() * sizeof(BatchTile), hipMemcpyHostToDevice, b->stream));
   }
-  HIP_TRY(hipMemcpyAsync(b->d_ntiles, b->ntiles_host, sizeof(b->ntiles_host), hipMemcpyHostToDevice, b->stream));
+  HIP_TRY(hipMemcpyAsync(b->d_runs, b->runs, sizeof(b->runs), hipMemcpyHostToDevice, b->stream));
   // the host arrays above must outlive the copies
   HIP_TRY(hipStreamSynchronize(b->stream));
   b->dirty = false;
@@ -246,7 +430,7 @@ lbm_status upload(lbm_batch* b) {
 unsigned active_groups(const lbm_batch* b) {
   unsigned m = 0;
   for (int g = 0; g < kGroups; ++g)
-    if (b->ntiles_host[g] > 0) m |= 1u << g;
+    if (b->runs[g][kAll].count > 0) m |= 1u << g;
   return m;
 }
 
@@ -256,116 +440,221 @@ unsigned active_groups(const lbm_batch* b) {
 // find no tile and exit).
 constexpr int32_t kGridQuantum = 256;
 
-int32_t launch_grid(const lbm_batch* b, int g) {
-  if (b->tune.grid > 0) return b->tune.grid;
-  const int32_t n = std::max<int32_t>(b->ntiles_host[g], 1);
-  return (n + kGridQuantum - 1) / kGridQuantum * kGridQuantum;
+int32_t rounded(int32_t tiles) { return (std::max<int32_t>(tiles, 1) + kGridQuantum - 1) / kGridQuantum * kGridQuantum; }
+
+int32_t launch_grid(const lbm_batch* b, int g, int run) {
+  return b->tune.grid > 0 ? b->tune.grid : rounded(b->runs[g][run].count);
 }
 
-template <int COLL, typename T>
-hipError_t launch_group_t(lbm_batch* b, int g, int32_t j) {
-  const dim3 grid((unsigned)launch_grid(b, g)), block((unsigned)b->tune.block);
-  T* arena = reinterpret_cast<T*>(b->arena);
-  const BatchTile* tiles = b->d_tiles + (size_t)g * b->max_tiles;
-  const int32_t* nt = b->d_ntiles + g;
-  int lds = b->tune.blocks_per_cu > 0 ? (int)(grlbm::kLdsPerCU / (b->tune.blocks_per_cu + 1)) + 256 : 0;
-  if (lds > 65536) lds = 65536;
-  const int need = 15 * (int)sizeof(float) * b->tune.block;  // odd-step x slots of one tile
-  if (lds < need) lds = need;
-  if (b->tune.nontemporal)
-    hipLaunchKernelGGL((grlbm::k_batch_step<COLL, T, true>), grid, block, lds, b->stream, arena, b->d_insts, tiles,
-                       nt, b->d_clock, j);
-  else
-    hipLaunchKernelGGL((grlbm::k_batch_step<COLL, T, false>), grid, block, lds, b->stream, arena, b->d_insts, tiles,
-                       nt, b->d_clock, j);
-  return hipGetLastError();
-}
-
-hipError_t launch_group(lbm_batch* b, int g, int32_t j) {
+// Calls fn with a kernel-selecting tag of group g: its collision and storage type.
+template <typename F>
+hipError_t for_group(int g, F fn) {
   switch (g) {
-    case 0: return launch_group_t<0, float>(b, g, j);
-    case 1: return launch_group_t<0, _Float16>(b, g, j);
-    case 2: return launch_group_t<1, float>(b, g, j);
-    default: return launch_group_t<1, _Float16>(b, g, j);
+    case 0: return fn(std::integral_constant<int, 0>(), float());
+    case 1: return fn(std::integral_constant<int, 0>(), _Float16());
+    case 2: return fn(std::integral_constant<int, 1>(), float());
+    default: return fn(std::integral_constant<int, 1>(), _Float16());
   }
 }
 
-// Enqueue n steps directly (no graph).
-lbm_status enqueue_steps(lbm_batch* b, int32_t n, unsigned groups) {
+// One step of the tiles of a run of group g, in the arena.
+hipError_t launch_single(lbm_batch* b, int g, int run, int32_t j) {
+  return for_group(g, [&](auto coll, auto zero) {
+    using T = decltype(zero);
+    constexpr int C = decltype(coll)::value;
+    int lds = b->tune.blocks_per_cu > 0 ? (int)(grlbm::kLdsPerCU / (b->tune.blocks_per_cu + 1)) + 256 : 0;
+    if (lds > 65536) lds = 65536;
+    const int need = 15 * (int)sizeof(float) * b->tune.block;  // odd-step x slots of one tile
+    if (lds < need) lds = need;
+    auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3((unsigned)launch_grid(b, g, run)), dim3((unsigned)b->tune.block), lds, b->stream,
+                         reinterpret_cast<T*>(b->arena), b->d_insts, b->d_tiles + (size_t)g * b->max_tiles,
+                         b->d_runs + g * kRuns + run, b->d_clock, j);
+      return hipGetLastError();
+    };
+    return b->tune.nontemporal ? go(grlbm::k_batch_step<C, T, true>) : go(grlbm::k_batch_step<C, T, false>);
+  });
+}
+
+hipError_t launch_pairs(lbm_batch* b, int g, const void* from, void* to, int32_t j) {
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)rounded(b->runs[g][kPairTiles].count)), dim3(grlbm::kPairThreads),
+                       grlbm::kPairLds, b->stream, (const char*)from, (char*)to, b->d_insts,
+                       b->d_multi + (size_t)g * b->max_tiles, b->d_runs + g * kRuns + kPairTiles, b->d_clock, j);
+    return hipGetLastError();
+  };
+  return g < 2 ? go(grlbm::k_batch_pair<0>) : go(grlbm::k_batch_pair<1>);
+}
+
+hipError_t launch_tubes(lbm_batch* b, int g, const void* from, void* to, int32_t j, int32_t steps) {
+  return for_group(g, [&](auto coll, auto zero) {
+    using T = decltype(zero);
+    constexpr int C = decltype(coll)::value;
+    const int32_t count = b->runs[g][kWindows].count;
+    const grlbm::TubeShape sh{b->tube_lanes[g], 0, 0, 0};
+    auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3((unsigned)rounded(count)), dim3(sh.lanes),
+                         grlbm::tube_lds(sh, rounded(count), b->num_cus), b->stream, (const char*)from, (char*)to,
+                         b->d_insts, b->d_multi + (size_t)g * b->max_tiles, b->d_runs + g * kRuns + kWindows,
+                         b->d_clock, j, steps);
+      return hipGetLastError();
+    };
+    return sh.lanes == 256 ? go(grlbm::k_batch_tube<C, T, 256>) : go(grlbm::k_batch_tube<C, T, 512>);
+  });
+}
+
+hipError_t launch_advance(lbm_batch* b, int32_t n) {
+  hipLaunchKernelGGL(grlbm::k_batch_advance, dim3(1), dim3(64), 0, b->stream, b->d_clock, n);
+  return hipGetLastError();
+}
+
+// Enqueue n single steps of every instance.
+lbm_status enqueue_steps(lbm_batch* b, int32_t n) {
   for (int32_t j = 0; j < n; ++j)
     for (int g = 0; g < kGroups; ++g)
-      if (groups & (1u << g)) HIP_TRY(launch_group(b, g, j));
-  hipLaunchKernelGGL(grlbm::k_batch_advance, dim3(1), dim3(64), 0, b->stream, b->d_clock, n);
-  HIP_TRY(hipGetLastError());
+      if (b->runs[g][kAll].count > 0) HIP_TRY(launch_single(b, g, kAll, j));
+  HIP_TRY(launch_advance(b, n));
   return LBM_OK;
 }
 
-void drop_graph(lbm_batch* b) {
-  if (b->graph) (void)hipGraphExecDestroy(b->graph);
-  b->graph = nullptr;
-  b->graph_groups = 0;
+// Enqueue n (even, >= 4) steps, several per pass where the instances can: tubes in an
+// even number of launches, the rest of FP32 as one step, pairs and the odd steps left.
+// The passes of each are even in number, so that all states end in the arena.
+lbm_status enqueue_fast(lbm_batch* b, int32_t n) {
+  for (int g = 0; g < kGroups; ++g) {
+    const TileRun* runs = b->runs[g];
+    void *from = b->arena, *to = b->spare.buf;
+    if (runs[kWindows].count > 0) {
+      const int32_t most = b->tube_steps[g];
+      const int32_t m = most > 2 ? n : n / 4 * 4;
+      int32_t left = m / 2;  // in steps of two, dealt evenly
+      for (int32_t i = (m + 2 * most - 1) / (2 * most) * 2; i > 0; --i) {
+        const int32_t two = left / i;
+        HIP_TRY(launch_tubes(b, g, from, to, m - 2 * left, 2 * two));
+        left -= two;
+        std::swap(from, to);
+      }
+      if (m < n) {  // two steps a launch and two left: once there, and copied back
+        HIP_TRY(launch_tubes(b, g, from, to, m, 2));
+        HIP_TRY(launch_tubes(b, g, to, from, m, 0));
+      }
+    }
+    if (runs[kPairTiles].count > 0) {
+      int32_t j = 0;
+      HIP_TRY(launch_single(b, g, kPaired, j++));
+      for (; j + 4 < n; j += 4) {
+        HIP_TRY(launch_pairs(b, g, from, to, j));
+        HIP_TRY(launch_pairs(b, g, to, from, j + 2));
+      }
+      for (; j < n; ++j) HIP_TRY(launch_single(b, g, kPaired, j));
+    }
+    if (runs[kSingle].count > 0)
+      for (int32_t j = 0; j < n; ++j) HIP_TRY(launch_single(b, g, kSingle, j));
+  }
+  HIP_TRY(launch_advance(b, n));
+  return LBM_OK;
 }
 
-lbm_status capture_graph(lbm_batch* b, unsigned groups) {
-  drop_graph(b);
+void drop_graphs(lbm_batch* b) {
+  for (auto& gr : b->graphs) {
+    if (gr.exec) (void)hipGraphExecDestroy(gr.exec);
+    gr.exec = nullptr;
+  }
+}
+
+// The graph of graph_steps steps, captured anew if the launches it holds have changed.
+lbm_status ready_graph(lbm_batch* b, bool fast) {
+  lbm_batch::Graph& gr = b->graphs[fast ? 1 : 0];
+  int32_t plan[kGroups * (kRuns + 2)] = {};
+  for (int g = 0, i = 0; g < kGroups; ++g) {
+    for (int r = 0; r < kRuns; ++r) {
+      const bool used = b->runs[g][r].count > 0 && (fast ? r != kAll : r == kAll);
+      plan[i++] = !used ? 0 : (r == kPairTiles || r == kWindows ? rounded(b->runs[g][r].count) : launch_grid(b, g, r));
+    }
+    if (fast) {
+      plan[i] = b->tube_lanes[g];
+      plan[i + 1] = b->tube_steps[g];
+    }
+    i += 2;
+  }
+  if (gr.exec && std::memcmp(plan, gr.plan, sizeof plan) == 0) return LBM_OK;
+  if (gr.exec) (void)hipGraphExecDestroy(gr.exec);
+  gr.exec = nullptr;
   hipGraph_t g = nullptr;
   HIP_TRY(hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
-  lbm_status st = enqueue_steps(b, b->graph_steps, groups);
+  lbm_status st = fast ? enqueue_fast(b, b->graph_steps) : enqueue_steps(b, b->graph_steps);
   hipError_t e = hipStreamEndCapture(b->stream, &g);
   if (st != LBM_OK) {
     if (g) (void)hipGraphDestroy(g);
     return st;
   }
   if (e != hipSuccess) return fail(LBM_EDEVICE, "hipStreamEndCapture failed: %s", hipGetErrorString(e));
-  e = hipGraphInstantiate(&b->graph, g, nullptr, nullptr, 0);
+  e = hipGraphInstantiate(&gr.exec, g, nullptr, nullptr, 0);
   (void)hipGraphDestroy(g);
   if (e != hipSuccess) {
-    b->graph = nullptr;
+    gr.exec = nullptr;
     return fail(LBM_EDEVICE, "hipGraphInstantiate failed: %s", hipGetErrorString(e));
   }
-  b->graph_groups = groups;
-  for (int k = 0; k < kGroups; ++k) b->graph_grid[k] = launch_grid(b, k);
+  std::memcpy(gr.plan, plan, sizeof plan);
   return LBM_OK;
 }
 
-// The captured graph no longer matches the groups to step or their launch grids.
-bool graph_stale(const lbm_batch* b, unsigned groups) {
-  if (!b->graph || b->graph_groups != groups) return true;
-  for (int k = 0; k < kGroups; ++k)
-    if ((groups & (1u << k)) && b->graph_grid[k] != launch_grid(b, k)) return true;
-  return false;
+// Steps from the current clock on for which every instance that makes several per pass
+// still has steps to make (finished ones are skipped on the device): up to the first
+// that finishes.
+int64_t fast_reach(const lbm_batch* b, int64_t clock) {
+  bool any = false;
+  for (int g = 0; g < kGroups; ++g) any |= b->runs[g][kPairTiles].count > 0 || b->runs[g][kWindows].count > 0;
+  if (!any || !b->spare.buf || b->single_steps) return 0;
+  int64_t reach = INT64_MAX;
+  for (const HostInst& h : b->insts)
+    if (h.live && h.how != kSingle && h.d.t_end > clock) reach = std::min(reach, h.d.t_end - clock);
+  return reach;
 }
 
 lbm_status run_steps(lbm_batch* b, int64_t n) {
+  // the second arena stays where it is until everything that uses it is enqueued; where
+  // it has been given up the lists and the graph that name it are made anew
+  std::lock_guard<std::mutex> use(b->spare.mu);
+  if (b->graphs[1].exec && !b->spare.buf) {
+    (void)hipGraphExecDestroy(b->graphs[1].exec);
+    b->graphs[1].exec = nullptr;
+    b->dirty = true;
+  }
   lbm_status st = upload(b);
   if (st != LBM_OK) return st;
-  const unsigned groups = active_groups(b);
-  if (groups == 0 || n == 0) {
+  if (active_groups(b) == 0 || n == 0) {
     // nothing to update: the clock still moves so instance windows stay consistent
-    if (n > 0) {
-      hipLaunchKernelGGL(grlbm::k_batch_advance, dim3(1), dim3(64), 0, b->stream, b->d_clock, (int32_t)n);
-      HIP_TRY(hipGetLastError());
-    }
+    if (n > 0) HIP_TRY(launch_advance(b, (int32_t)n));
     b->clock += n;
     return LBM_OK;
   }
+  // Fast steps while no instance finishes within them; an instance that makes several
+  // steps per pass is at an even step here, and fast runs are even, so an odd single
+  // run ends them (odd_since).
   int64_t left = n;
-  if (b->graph_steps > 1 && left >= b->graph_steps) {
-    if (graph_stale(b, groups)) {
-      st = capture_graph(b, groups);
-      if (st != LBM_OK) return st;
-    }
-    while (left >= b->graph_steps) {
-      HIP_TRY(hipGraphLaunch(b->graph, b->stream));
-      left -= b->graph_steps;
-    }
-  }
+  bool odd_since = false;
   while (left > 0) {
-    const int32_t chunk = (int32_t)std::min<int64_t>(left, 1 << 20);
-    st = enqueue_steps(b, chunk, groups);
+    const int64_t clock = b->clock + (n - left);
+    const int64_t reach = odd_since ? 0 : fast_reach(b, clock);
+    const bool graph = b->graph_steps > 1 && left >= b->graph_steps;
+    int64_t m = graph ? b->graph_steps : std::min<int64_t>(left, 1 << 20);
+    bool fast = reach >= 4 && m >= 4 && (graph ? m % 2 == 0 && m <= reach : true);
+    if (graph) {
+      st = ready_graph(b, fast);
+      if (st != LBM_OK) return st;
+      HIP_TRY(hipGraphLaunch(b->graphs[fast ? 1 : 0].exec, b->stream));
+    } else if (fast) {
+      m = std::min(m, reach) / 2 * 2;
+      st = enqueue_fast(b, (int32_t)m);
+    } else {
+      st = enqueue_steps(b, (int32_t)m);
+    }
     if (st != LBM_OK) return st;
-    left -= chunk;
+    if (m % 2 != 0) odd_since = !odd_since;
+    left -= m;
   }
+  if (odd_since) b->dirty = true;
   b->clock += n;
   // instances finished inside this run drop out of the tile list next time
   for (const HostInst& h : b->insts)
@@ -458,14 +747,14 @@ lbm_status lbm_batch_create(size_t arena_bytes, int32_t max_instances, int32_t m
   b->max_tiles = max_tiles;
   if (grlbm::dev_malloc((void**)&b->d_insts, sizeof(BatchInst) * (size_t)max_instances) != hipSuccess ||
       grlbm::dev_malloc((void**)&b->d_tiles, sizeof(BatchTile) * (size_t)max_tiles * kGroups) != hipSuccess ||
-      grlbm::dev_malloc((void**)&b->d_ntiles, sizeof(int32_t) * kGroups) != hipSuccess ||
+      grlbm::dev_malloc((void**)&b->d_multi, sizeof(BatchTile) * (size_t)max_tiles * kGroups) != hipSuccess ||
+      grlbm::dev_malloc((void**)&b->d_runs, sizeof(b->runs)) != hipSuccess ||
       grlbm::dev_malloc((void**)&b->d_clock, sizeof(int64_t)) != hipSuccess ||
       grlbm::dev_malloc((void**)&b->d_flags, sizeof(int32_t) * (size_t)max_instances) != hipSuccess)
     return bail(fail(LBM_ENOMEM, "hipMalloc of the batch tables failed"));
   const int64_t zero = 0;
-  const int32_t zeros[kGroups] = {0, 0, 0, 0};
   if (hipMemcpyAsync(b->d_clock, &zero, sizeof zero, hipMemcpyHostToDevice, b->stream) != hipSuccess ||
-      hipMemcpyAsync(b->d_ntiles, zeros, sizeof zeros, hipMemcpyHostToDevice, b->stream) != hipSuccess ||
+      hipMemcpyAsync(b->d_runs, b->runs, sizeof(b->runs), hipMemcpyHostToDevice, b->stream) != hipSuccess ||
       hipStreamSynchronize(b->stream) != hipSuccess)
     return bail(fail(LBM_EDEVICE, "batch table initialisation failed"));
   b->graph_steps = graph_steps;
@@ -478,6 +767,10 @@ lbm_status lbm_batch_create(size_t arena_bytes, int32_t max_instances, int32_t m
   b->tune.nontemporal = 0;
   b->tune.blocks_per_cu = 2;
   b->tune.grid = 0;
+  // a second arena for what lies at the front of the first, where instances go first
+  b->spare.device = dev;
+  b->spare.stream = b->stream;
+  grlbm::take_spare(b->spare, std::min(b->arena_bytes, kSpareArena));
   *out = b;
   return LBM_OK;
 }
@@ -549,6 +842,7 @@ lbm_status lbm_batch_add(lbm_batch* b, const lbm_params* p, const double* Q, int
     return fail(LBM_EDEVICE, "instance initialisation failed: %s", hipGetErrorString(e));
   }
   h.live = true;
+  h.pair_cus = 0;
   b->dirty = true;
   *id = slot;
   return LBM_OK;
@@ -716,7 +1010,7 @@ lbm_status lbm_batch_set_tuning(lbm_batch* b, const lbm_batch_tuning* t) {
   b->tune = *t;
   b->tune.nontemporal = t->nontemporal ? 1 : 0;
   b->dirty = true;
-  drop_graph(b);
+  drop_graphs(b);
   return LBM_OK;
 }
 
@@ -772,6 +1066,7 @@ lbm_status lbm_batch_autotune(lbm_batch* b, int32_t trial_steps, lbm_batch_tunin
   if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) {
     st = fail(LBM_EDEVICE, "event creation failed");
   }
+  b->single_steps = true;
   for (size_t ci = 0; st == LBM_OK && ci < cands.size(); ++ci) {
     st = lbm_batch_set_tuning(b, &cands[ci]);
     if (st == LBM_ENOMEM) {  // this block width does not fit the tile capacity
@@ -815,6 +1110,7 @@ lbm_status lbm_batch_autotune(lbm_batch* b, int32_t trial_steps, lbm_batch_tunin
     }
     b->dirty = true;
   }
+  b->single_steps = false;
   if (e0) (void)hipEventDestroy(e0);
   if (e1) (void)hipEventDestroy(e1);
   if (snap) {
@@ -834,11 +1130,13 @@ lbm_status lbm_batch_destroy(lbm_batch* b) {
   lbm_status st = LBM_OK;
   if (b->stream && hipStreamSynchronize(b->stream) != hipSuccess)
     st = fail(LBM_EDEVICE, "stream synchronisation failed during destroy");
-  drop_graph(b);
+  drop_graphs(b);
+  grlbm::drop_spare(b->spare);
   if (b->arena) (void)hipFree(b->arena);
   if (b->d_insts) (void)hipFree(b->d_insts);
   if (b->d_tiles) (void)hipFree(b->d_tiles);
-  if (b->d_ntiles) (void)hipFree(b->d_ntiles);
+  if (b->d_multi) (void)hipFree(b->d_multi);
+  if (b->d_runs) (void)hipFree(b->d_runs);
   if (b->d_clock) (void)hipFree(b->d_clock);
   if (b->d_check) (void)hipFree(b->d_check);
   if (b->d_flags) (void)hipFree(b->d_flags);

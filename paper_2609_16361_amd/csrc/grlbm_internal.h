@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <mutex>
+
 #include "../../include/grlbm.h"
 #include "grlbm_device.hpp"
 
@@ -18,7 +20,23 @@ namespace grlbm {
 
 lbm_status fail(lbm_status st, const char* fmt, ...);
 lbm_status validate(const lbm_params* p);
-// hipMalloc; out of memory, it first gives up the contexts' second population buffers.
+// The second population buffer of a context or a batch: workspace, without which its
+// owner makes one step per pass.  The owner uses it with mu held, in work on its stream.
+struct Spare {
+  std::mutex mu;
+  void* buf = nullptr;
+  size_t bytes = 0;
+  int device = 0;
+  hipStream_t stream = nullptr;
+};
+// Takes a buffer for s (device and stream are set) if the card has room to spare: at
+// least half of it stays free or the buffer is at most an eighth of what is free, and
+// all second buffers together stay below a quarter of the card.
+void take_spare(Spare& s, size_t bytes);
+void drop_spare(Spare& s);  // frees it, if s has one; its owner's work is done
+bool capturing(hipStream_t s);
+// hipMalloc; out of memory, it first gives up the second buffers of the current device
+// (each after the work on its stream, but not where the stream is being captured).
 hipError_t dev_malloc(void** p, size_t bytes);
 // Initial conserved fields Q[5][N] (host) describe a physical state: every value
 // finite, density and pressure positive in every cell; EINVAL names the first cell
@@ -99,13 +117,14 @@ int odd_pair_lds(const Grid& g);             // its dynamic LDS bytes per block
 // Two steps per pass over memory (grlbm_pair.hip): the tiles a grid is cut into.
 constexpr int kPairCells = 512;    // cells of a tile's plane at most: 8 waves ...
 constexpr int kPairThreads = 832;  // ... and 5 for the halo around it
+constexpr int kPairLds = 2 * 20 * (kPairCells + 64) * 4;  // dynamic LDS of a block
 struct PairTiles {
   int w, h, lz;         // cells of a tile along x, y and z (the last ones may be cut)
   int ntx, nty, nseg;   // tiles along each axis
   int per_xcd;          // tiles an XCD takes, of one z segment if by_plane, else of all
   int by_plane;
 };
-PairTiles pair_tiles(const Grid& g, int cus);
+PairTiles pair_tiles(const Grid& g, int cus, bool share = false);
 bool pair_worth(const Grid& g);  // a pair beats two single steps
 // An odd and the following even step from A to B (FP32 storage, no source, no
 // diagnostics); both hold the odd-parity layout.  Bitwise two launch_step calls.
@@ -118,6 +137,8 @@ struct TubeShape {
   int lanes, width, inner, steps;
 };
 TubeShape tube_shape(const Grid& g, bool f16, int cus);
+// Estimated us per step of tubes cut into `blocks` windows of sh, from one launch.
+double tube_price(const TubeShape& sh, int64_t cross, int64_t blocks, bool f16, int cus);
 int tube_lds(const TubeShape& sh, int64_t blocks, int cus);
 // `steps` (even, at most sh.steps) steps from the even step t0 on, from A to B; both hold
 // the even-parity layout.  Bitwise that many launch_step calls.

@@ -21,19 +21,30 @@ __global__ void __launch_bounds__(L, 4) k_step_tube(const T* __restrict__ A, T* 
   tube_update<COLL, T, L>(A, B, g, c, (int)blockIdx.x * sh.inner, sh.width, sh.inner, steps, t0, xs);
 }
 
+// Blocks have 256 or 512 lanes (4 or 2 on a CU at 92-111 registers and 30 or 60 KB of
+// LDS).  A step takes 0.55 + 0.56 w us with w waves per SIMD (FP16, whose stores round:
+// 1.45 + 0.65 w), a launch 3.6 us besides, and on a full card a turn of blocks moves its
+// windows through HBM at 8 TB/s, counted in whole lines, partly under the other blocks'
+// arithmetic.  Within 20% of the timings over tubes of 256 to 283000 columns with
+// cross-sections of 1 to 25 cells.
+double tube_price(const TubeShape& sh, int64_t cross, int64_t blocks, bool f16, int cus) {
+  const int resident = 1024 / sh.lanes;
+  const int64_t slots = (int64_t)cus * resident;
+  const double turns = (double)((blocks + slots - 1) / slots);
+  const double waves = (double)std::min<int64_t>(resident, (blocks + cus - 1) / cus) * sh.lanes / 256.0;
+  const double issue = sh.steps * (f16 ? 1.45 + 0.65 * waves : 0.55 + 0.56 * waves);
+  const double el = f16 ? 2.0 : 4.0, line = (sh.width - 1) * el + 128.0;  // bytes of a row's lines
+  const double memory = 70.0 * cross * line * (double)std::min<int64_t>(blocks, slots) / 8.0e6;
+  return (3.6 + turns * (std::max(issue, memory) + 0.25 * std::min(issue, memory))) / sh.steps;
+}
+
 // The window and the most steps per launch of a tube, by the estimated time per step
-// (lanes = 0: none, the grid is no tube or steps faster otherwise).  Blocks have 256 or
-// 512 lanes (4 or 2 on a CU at 92-111 registers and 30 or 60 KB of LDS).  A step takes
-// 0.55 + 0.56 w us with w waves per SIMD (FP16, whose stores round: 1.45 + 0.65 w), a
-// launch 3.6 us besides, and on a full card a turn of blocks moves its window through
-// HBM at 8 TB/s, counted in whole lines, partly under the other blocks' arithmetic.  More steps per launch share the
-// launch but drop more columns.  The estimates were within 20% of the timings over
-// tubes of 256 to 283000 columns with cross-sections of 1 to 25 cells, and the choice
-// within 10% of the best.  Against them stand the other ways to step: pairs (FP32,
-// about 4.5 us + cells / 28500 us) and single steps (FP16, 4.4 us + cells / 58000 us, or cells /
-// 37500 us beyond the caches; a tenth is left for the estimate's error).
-// Windows of cross-sections over 25 cells lose too much to their ends (FP32 8 x 4 cells,
-// 4097 columns: 11.4 us per step, 9.4 in pairs).
+// (lanes = 0: none, the grid is no tube or steps faster otherwise).  More steps per
+// launch share the launch but drop more columns.  Against them stand the other ways to
+// step: pairs (FP32, about 4.5 us + cells / 28500 us) and single steps (FP16, 4.4 us +
+// cells / 58000 us, or cells / 37500 us beyond the caches; a tenth is left for the
+// estimate's error).  Windows of cross-sections over 25 cells lose too much to their
+// ends (FP32 8 x 4 cells, 4097 columns: 11.4 us per step, 8.7 in pairs).
 TubeShape tube_shape(const Grid& g, bool f16, int cus) {
   TubeShape best{};
   const int64_t cross = (int64_t)g.ny * g.nz;
@@ -41,25 +52,13 @@ TubeShape tube_shape(const Grid& g, bool f16, int cus) {
   const double cells = (double)cross * g.nx;
   double best_cost = f16 ? 0.9 * std::max(4.4 + cells / 58000.0, cells / 37500.0) : 4.5 + cells / 28500.0;
   for (int lanes : {256, 512}) {
-    const int width = (int)(lanes / cross), resident = 1024 / lanes;
-    for (int steps = 2; steps <= kTubeSteps; steps += 2) {
-      const int inner = width - 2 * steps;
-      if (inner < 2) break;
-      const int64_t blocks = (g.nx + inner - 1) / inner;
-      const int64_t slots = (int64_t)cus * resident;
-      const double turns = (double)((blocks + slots - 1) / slots);
-      const double waves = (double)std::min<int64_t>(resident, (blocks + cus - 1) / cus) * lanes / 256.0;
-      const double issue = steps * (f16 ? 1.45 + 0.65 * waves : 0.55 + 0.56 * waves);
-      const double el = f16 ? 2.0 : 4.0, line = (width - 1) * el + 128.0;  // bytes of a row's lines
-      const double memory = 70.0 * cross * line * (double)std::min<int64_t>(blocks, slots) / 8.0e6;
-      const double cost =
-          (3.6 + turns * (std::max(issue, memory) + 0.25 * std::min(issue, memory))) / steps;
+    const int width = (int)(lanes / cross);
+    for (int steps = 2; steps <= kTubeSteps && width - 2 * steps >= 2; steps += 2) {
+      const TubeShape sh{lanes, width, width - 2 * steps, steps};
+      const double cost = tube_price(sh, cross, (g.nx + sh.inner - 1) / sh.inner, f16, cus);
       if (cost < best_cost) {
         best_cost = cost;
-        best.lanes = lanes;
-        best.width = width;
-        best.inner = inner;
-        best.steps = steps;
+        best = sh;
       }
     }
   }
