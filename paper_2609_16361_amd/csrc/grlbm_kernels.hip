@@ -20,6 +20,8 @@
 // MFMA).
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "grlbm_device.hpp"
 #include "grlbm_internal.h"
 
@@ -210,21 +212,31 @@ __global__ void __launch_bounds__(1024) k_finalize(const float* __restrict__ par
 
 // Largest |v| per field, as the bit pattern of a non-negative float (which orders
 // like the value); the result does not depend on the order of the atomics.  The
-// wave reduces first and issues one atomic per field: one atomic per cell on the
-// same five words serialised and took 15 ms at 256^3.  Every lane of the wave must
-// call it; lanes without a cell pass 0.  A NaN does not win the maximum.
-__device__ __forceinline__ void wave_field_max(unsigned* maxabs, int k, float v) {
-  float m = fabsf(v);
+// block reduces first and issues one atomic per field: one atomic per cell on the
+// same five words serialised and took 15 ms at 256^3, one per wave of 2048 blocks
+// 0.5 ms whatever the grid.  Every lane of the block must call it; lanes without a cell
+// pass 0.  A NaN does not win the maximum.
+__device__ __forceinline__ void block_field_max(unsigned* maxabs, const float mx[kFields]) {
+  __shared__ float sm[4][kFields];  // blocks of 256 lanes
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-  if ((threadIdx.x & 63) == 0) atomicMax(maxabs + k, __float_as_uint(m));
+  for (int k = 0; k < kFields; ++k) {
+    float m = fabsf(mx[k]);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6][k] = m;
+  }
+  __syncthreads();
+  if (threadIdx.x < kFields) {
+    const float m = fmaxf(fmaxf(sm[0][threadIdx.x], sm[1][threadIdx.x]), fmaxf(sm[2][threadIdx.x], sm[3][threadIdx.x]));
+    atomicMax(maxabs + threadIdx.x, __float_as_uint(m));
+  }
 }
 
 // Neighbour index along one axis for a central difference: periodic wrap, or the
 // cell itself beyond a zero-gradient face (the ghost holds a copy of the cell).
 __device__ __forceinline__ int64_t fd_neighbour(int64_t n, int x, int d, int len, int zg, int64_t stride) {
   int xx = x + d;
-  if (xx < 0 || xx >= len) xx = zg ? x : (xx + len) % len;
+  if (xx < 0 || xx >= len) xx = zg ? x : (xx < 0 ? len - 1 : 0);
   return n + (int64_t)(xx - x) * stride;
 }
 
@@ -239,30 +251,33 @@ __device__ __forceinline__ int64_t fd_neighbour(int64_t n, int x, int d, int len
 // the non-equilibrium part the first streaming leaves J - Phi = -c_s^2 grad Q, omega
 // times too large, and the difference oscillates from step to step undamped as
 // omega -> 2.  Computed in FP64, stored as g_i = w_i (Q - Q_ref + 4 c_i . J) times
-// the field's storage scale.  With ic.equilibrium (initial data with jumps, where a
+// the field's storage scale.  With EQ (initial data with jumps, where a
 // difference across a jump is no gradient) grad Q is taken as zero, which leaves
-// the equilibrium of Q with the advective flux.  With mx set, nothing is stored and
+// the equilibrium of Q with the advective flux.  (With EQ a template argument the loads of
+// the five fields are not serialised behind its tests, and nontemporal stores leave the
+// caches to the neighbours' reads: 256^3 985 -> 887 us, 128^3 127 -> 74.)  With mx set, nothing is stored and
 // mx[k] receives the cell's largest |g| of field k (used to pick the FP16 scales).
-template <typename T>
+template <typename T, bool EQ>
 __device__ __forceinline__ void init_cell(T* __restrict__ F, const Grid& g, const Coll& c, const InitCoef& ic,
-                                          const double* __restrict__ Q, int64_t N, int64_t n, float* mx) {
-  const int64_t row = n / g.nx;
-  const int x = (int)(n - row * g.nx);
-  const int y = (int)(row % g.ny);
-  const int z = (int)(row / g.ny);
+                                          const double* __restrict__ Q, int64_t N, int n, float* mx) {
+  const int row = n / g.nx;  // below 2^31: the element count is capped
+  const int x = n - row * g.nx;
+  const int z = row / g.ny;
+  const int y = row - z * g.ny;
   const int64_t plane = (int64_t)g.nx * g.ny;
   const int64_t ns = x + (int64_t)g.px * row;  // the cell's element in the padded rows
   const int64_t xm = fd_neighbour(n, x, -1, g.nx, g.zg_x, 1), xp = fd_neighbour(n, x, 1, g.nx, g.zg_x, 1);
   const int64_t ym = fd_neighbour(n, y, -1, g.ny, g.zg_y, g.nx), yp = fd_neighbour(n, y, 1, g.ny, g.zg_y, g.nx);
   const int64_t zm = fd_neighbour(n, z, -1, g.nz, g.zg_z, plane), zp = fd_neighbour(n, z, 1, g.nz, g.zg_z, plane);
   double q[5], G[5][3];
+#pragma unroll
   for (int k = 0; k < 5; ++k) {
     const double* Qk = Q + k * N;
     q[k] = Qk[n];
     // the equilibrium start (data with jumps) takes no gradient
-    G[k][0] = ic.equilibrium ? 0.0 : 0.5 * (Qk[xp] - Qk[xm]);
-    G[k][1] = ic.equilibrium ? 0.0 : 0.5 * (Qk[yp] - Qk[ym]);
-    G[k][2] = ic.equilibrium ? 0.0 : 0.5 * (Qk[zp] - Qk[zm]);
+    G[k][0] = EQ ? 0.0 : 0.5 * (Qk[xp] - Qk[xm]);
+    G[k][1] = EQ ? 0.0 : 0.5 * (Qk[yp] - Qk[ym]);
+    G[k][2] = EQ ? 0.0 : 0.5 * (Qk[zp] - Qk[zm]);
   }
   const double rf = fmax(q[0], ic.rho_min);
   const double u[3] = {q[1] / rf, q[2] / rf, q[3] / rf};
@@ -312,34 +327,34 @@ __device__ __forceinline__ void init_cell(T* __restrict__ F, const Grid& g, cons
       mx[k] = m;
     } else {
       T* Fk = F + (int64_t)(7 * k) * g.S + ns;
-      for (int i = 0; i < kQ; ++i) Fk[(int64_t)i * g.S] = static_cast<T>(v[i] * c.sc[k]);
+      for (int i = 0; i < kQ; ++i) __builtin_nontemporal_store(static_cast<T>(v[i] * c.sc[k]), Fk + (int64_t)i * g.S);
     }
   }
 }
 
 // Largest |f| per field of a canonical population array f[35][N].
-template <typename T>
+template <typename T, bool EQ>
 __global__ void __launch_bounds__(256) k_init(T* __restrict__ F, Grid g, Coll c, InitCoef ic,
                                                const double* __restrict__ Q, int64_t N) {
   const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (n < N) init_cell<T>(F, g, c, ic, Q, N, n, nullptr);
+  if (n < N) init_cell<T, EQ>(F, g, c, ic, Q, N, (int)n, nullptr);
 }
 
 // The largest |g| of each field over the initial populations k_init would store,
-// without storing them (picks the FP16 scales).  A fixed grid of at most 2048
-// blocks strides over the cells, so the atomics number a few per wave and not
-// one per wave of cells.
+// without storing them (picks the FP16 scales).  A fixed grid of at most 1024
+// blocks strides over the cells, so the atomics number five per block and not
+// per wave of cells.
+template <bool EQ>
 __global__ void __launch_bounds__(256) k_init_maxabs(Grid g, Coll c, InitCoef ic, const double* __restrict__ Q,
                                                       int64_t N, unsigned* __restrict__ maxabs) {
   float mx[kFields] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
   for (int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; n < N; n += (int64_t)gridDim.x * blockDim.x) {
     float m[kFields];
-    init_cell<float>(nullptr, g, c, ic, Q, N, n, m);
+    init_cell<float, EQ>(nullptr, g, c, ic, Q, N, (int)n, m);
 #pragma unroll
     for (int k = 0; k < kFields; ++k) mx[k] = fmaxf(mx[k], m[k]);
   }
-#pragma unroll
-  for (int k = 0; k < kFields; ++k) wave_field_max(maxabs, k, mx[k]);
+  block_field_max(maxabs, mx);
 }
 
 // The same over populations handed in by the caller (canonical layout, N cells).
@@ -349,66 +364,72 @@ __global__ void __launch_bounds__(256) k_maxabs_pops(const float* __restrict__ f
   for (int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; n < N; n += (int64_t)gridDim.x * blockDim.x) {
 #pragma unroll
     for (int k = 0; k < kFields; ++k)
+#pragma unroll
       for (int i = 0; i < kQ; ++i) mx[k] = fmaxf(mx[k], fabsf(f[(int64_t)(7 * k + i) * N + n]));
   }
-#pragma unroll
-  for (int k = 0; k < kFields; ++k) wave_field_max(maxabs, k, mx[k]);
+  block_field_max(maxabs, mx);
 }
 
 // Element offset of canonical f_i of field k at the lane's cell for a state of
 // the given parity.
-template <typename T>
-__device__ __forceinline__ int64_t canon_off(const Grid& g, const Nbr& b, int k, int i, bool odd) {
+template <bool ODD>
+__device__ __forceinline__ int64_t canon_off(const Grid& g, const Nbr& b, int k, int i) {
   const int64_t base = (int64_t)(7 * k) * g.S;
-  if (!odd) return base + (int64_t)i * g.S + b.n;
+  if constexpr (!ODD) return base + (int64_t)i * g.S + b.n;
   return base + odd_src<true>(g, b, i);
 }
 
-__device__ __forceinline__ void cell_of(const Grid& g, int64_t n, int& x, int& y, int& z) {
-  x = (int)(n % g.nx);
-  const int64_t r = n / g.nx;
-  y = (int)(r % g.ny);
-  z = (int)(r / g.ny);
+// The neighbourhood of cell n; the element count, and with it n, is below 2^31.
+__device__ __forceinline__ Nbr nbr_of(const Grid& g, int n) {
+  const int row = n / g.nx;
+  const int z = row / g.ny;
+  return make_nbr(g, n - row * g.nx, row - z * g.ny, z);
 }
 
-// mode 0: canonical populations -> out_f[35][N] (float)
-// mode 1: conserved moments Q_ref + sum_i g -> out_q[5][N] (double)
-template <typename T>
-__global__ void __launch_bounds__(256) k_gather(const T* __restrict__ F, Grid g, Coll c,
-                                                 int64_t N, int odd, int mode,
-                                                 float* __restrict__ out_f,
-                                                 double* __restrict__ out_q) {
+// Readout of a state of the given parity.  POPS: canonical populations -> out_f[35][N]
+// (float); else conserved moments Q_ref + sum_i g -> out_q[5][N] (double).  HBM bound:
+// 140 + 140 or 140 + 40 B per cell in FP32.  The parity is a template argument and the
+// index 32-bit so that all 35 loads of a cell are in flight together: the moments of
+// 256^3 took 765 us with both at run time (4.0 TB/s) and take 530 (5.7 TB/s), FP16 715 and
+// 327.
+template <typename T, bool ODD, bool POPS>
+__global__ void __launch_bounds__(256) k_gather(const T* __restrict__ F, Grid g, Coll c, int64_t N,
+                                                 float* __restrict__ out_f, double* __restrict__ out_q) {
   const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (n >= N) return;
-  int x, y, z;
-  cell_of(g, n, x, y, z);
-  const Nbr b = make_nbr(g, x, y, z);
-  for (int k = 0; k < 5; ++k) {
+  const Nbr b = nbr_of(g, (int)n);
+  float f[kPop];
+#pragma unroll
+  for (int k = 0; k < kFields; ++k)
+#pragma unroll
+    for (int i = 0; i < kQ; ++i) f[7 * k + i] = static_cast<float>(F[canon_off<ODD>(g, b, k, i)]);
+#pragma unroll
+  for (int k = 0; k < kFields; ++k) {
     float s = 0.0f;
+#pragma unroll
     for (int i = 0; i < kQ; ++i) {
-      const float v = static_cast<float>(F[canon_off<T>(g, b, k, i, odd != 0)]) * c.isc[k];
-      if (mode == 0) out_f[(int64_t)(7 * k + i) * N + n] = v;
+      const float v = f[7 * k + i] * c.isc[k];
+      if constexpr (POPS) __builtin_nontemporal_store(v, out_f + (int64_t)(7 * k + i) * N + n);
       s += v;
     }
-    if (mode == 1) {
+    if constexpr (!POPS) {
       const double ref = (k == 0) ? (double)c.rho_ref : (k == 4 ? (double)c.E_ref : 0.0);
-      out_q[(int64_t)k * N + n] = ref + (double)s;
+      __builtin_nontemporal_store(ref + (double)s, out_q + (int64_t)k * N + n);
     }
   }
 }
 
-template <typename T>
-__global__ void __launch_bounds__(256) k_scatter(T* __restrict__ F, Grid g, Coll c, int64_t N, int odd,
+template <typename T, bool ODD>
+__global__ void __launch_bounds__(256) k_scatter(T* __restrict__ F, Grid g, Coll c, int64_t N,
                                                   const float* __restrict__ in_f) {
   const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (n >= N) return;
-  int x, y, z;
-  cell_of(g, n, x, y, z);
-  const Nbr b = make_nbr(g, x, y, z);
-  for (int k = 0; k < 5; ++k)
+  const Nbr b = nbr_of(g, (int)n);
+#pragma unroll
+  for (int k = 0; k < kFields; ++k)
+#pragma unroll
     for (int i = 0; i < kQ; ++i)
-      F[canon_off<T>(g, b, k, i, odd != 0)] =
-          static_cast<T>(in_f[(int64_t)(7 * k + i) * N + n] * c.sc[k]);
+      F[canon_off<ODD>(g, b, k, i)] = static_cast<T>(in_f[(int64_t)(7 * k + i) * N + n] * c.sc[k]);
 }
 
 typedef float v4f __attribute__((ext_vector_type(4)));
@@ -596,25 +617,35 @@ hipError_t launch_finalize(const float* partials, int64_t nblocks, float* rec, h
   return hipGetLastError();
 }
 
-hipError_t launch_init(void* F, bool f16, const Grid& g, const Coll& c, const InitCoef& ic, const double* Q,
-                       int64_t N, hipStream_t s) {
-  const unsigned blocks = (unsigned)((N + 255) / 256);
-  if (f16)
-    hipLaunchKernelGGL(k_init<_Float16>, dim3(blocks), dim3(256), 0, s, (_Float16*)F, g, c, ic, Q, N);
-  else
-    hipLaunchKernelGGL(k_init<float>, dim3(blocks), dim3(256), 0, s, (float*)F, g, c, ic, Q, N);
-  return hipGetLastError();
+// Calls fn with the storage type and a flag as template arguments.
+template <typename Fn>
+static hipError_t typed(bool f16, bool flag, Fn fn) {
+  if (f16) return flag ? fn(_Float16(), std::true_type()) : fn(_Float16(), std::false_type());
+  return flag ? fn(float(), std::true_type()) : fn(float(), std::false_type());
 }
 
-// Blocks of the striding max-abs reductions: 8 per CU, a few thousand atomics.
+hipError_t launch_init(void* F, bool f16, const Grid& g, const Coll& c, const InitCoef& ic, const double* Q,
+                       int64_t N, hipStream_t s) {
+  const dim3 blocks((unsigned)((N + 255) / 256));
+  return typed(f16, ic.equilibrium != 0, [&](auto zero, auto eq) {
+    using T = decltype(zero);
+    hipLaunchKernelGGL((k_init<T, decltype(eq)::value>), blocks, dim3(256), 0, s, (T*)F, g, c, ic, Q, N);
+    return hipGetLastError();
+  });
+}
+
+// Blocks of the striding max-abs reductions: 4 per CU, a few thousand atomics.
 static unsigned maxabs_blocks(int64_t N) {
   const int64_t b = (N + 255) / 256;
-  return (unsigned)(b < 2048 ? (b > 0 ? b : 1) : 2048);
+  return (unsigned)(b < 1024 ? (b > 0 ? b : 1) : 1024);
 }
 
 hipError_t launch_init_maxabs(const Grid& g, const Coll& c, const InitCoef& ic, const double* Q, int64_t N,
                               unsigned* maxabs, hipStream_t s) {
-  hipLaunchKernelGGL(k_init_maxabs, dim3(maxabs_blocks(N)), dim3(256), 0, s, g, c, ic, Q, N, maxabs);
+  if (ic.equilibrium)
+    hipLaunchKernelGGL(k_init_maxabs<true>, dim3(maxabs_blocks(N)), dim3(256), 0, s, g, c, ic, Q, N, maxabs);
+  else
+    hipLaunchKernelGGL(k_init_maxabs<false>, dim3(maxabs_blocks(N)), dim3(256), 0, s, g, c, ic, Q, N, maxabs);
   return hipGetLastError();
 }
 
@@ -625,25 +656,26 @@ hipError_t launch_maxabs_pops(const float* f, int64_t N, unsigned* maxabs, hipSt
 
 hipError_t launch_gather(const void* F, bool f16, const Grid& g, const Coll& c, int64_t N, bool odd,
                          int mode, float* out_f, double* out_q, hipStream_t s) {
-  const unsigned blocks = (unsigned)((N + 255) / 256);
-  if (f16)
-    hipLaunchKernelGGL(k_gather<_Float16>, dim3(blocks), dim3(256), 0, s, (const _Float16*)F, g, c, N,
-                       (int)odd, mode, out_f, out_q);
-  else
-    hipLaunchKernelGGL(k_gather<float>, dim3(blocks), dim3(256), 0, s, (const float*)F, g, c, N,
-                       (int)odd, mode, out_f, out_q);
-  return hipGetLastError();
+  const dim3 blocks((unsigned)((N + 255) / 256));
+  return typed(f16, odd, [&](auto zero, auto parity) {
+    using T = decltype(zero);
+    constexpr bool ODD = decltype(parity)::value;
+    if (mode == 0)
+      hipLaunchKernelGGL((k_gather<T, ODD, true>), blocks, dim3(256), 0, s, (const T*)F, g, c, N, out_f, out_q);
+    else
+      hipLaunchKernelGGL((k_gather<T, ODD, false>), blocks, dim3(256), 0, s, (const T*)F, g, c, N, out_f, out_q);
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_scatter(void* F, bool f16, const Grid& g, const Coll& c, int64_t N, bool odd,
                           const float* in_f, hipStream_t s) {
-  const unsigned blocks = (unsigned)((N + 255) / 256);
-  if (f16)
-    hipLaunchKernelGGL(k_scatter<_Float16>, dim3(blocks), dim3(256), 0, s, (_Float16*)F, g, c, N, (int)odd,
-                       in_f);
-  else
-    hipLaunchKernelGGL(k_scatter<float>, dim3(blocks), dim3(256), 0, s, (float*)F, g, c, N, (int)odd, in_f);
-  return hipGetLastError();
+  const dim3 blocks((unsigned)((N + 255) / 256));
+  return typed(f16, odd, [&](auto zero, auto parity) {
+    using T = decltype(zero);
+    hipLaunchKernelGGL((k_scatter<T, decltype(parity)::value>), blocks, dim3(256), 0, s, (T*)F, g, c, N, in_f);
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_copy(const void* a, void* b, int64_t bytes, hipStream_t s) {
