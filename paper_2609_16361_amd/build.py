@@ -15,7 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libgrlbm.so")
 SOURCES = ["grlbm_kernels.hip", "grlbm_api.hip", "grlbm_batch.hip", "grlbm_mms.hip",
-           "grlbm_pair.hip", "grlbm_tube.hip"]
+           "grlbm_pair.hip", "grlbm_tube.hip", "grlbm_copy.hip"]
 ARCH = "gfx950"
 
 

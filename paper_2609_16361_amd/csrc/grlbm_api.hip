@@ -87,20 +87,6 @@ lbm_status validate(const lbm_params* p) {
   return LBM_OK;
 }
 
-lbm_status check_fields(const lbm_params* p, const double* Q) {
-  const int64_t N = (int64_t)p->nx * p->ny * p->nz;
-  const double g1 = p->gamma - 1.0;
-  for (int64_t n = 0; n < N; ++n) {
-    const double rho = Q[n], m0 = Q[N + n], m1 = Q[2 * N + n], m2 = Q[3 * N + n], E = Q[4 * N + n];
-    if (!(std::isfinite(rho) && std::isfinite(m0) && std::isfinite(m1) && std::isfinite(m2) && std::isfinite(E)))
-      return fail(LBM_EINVAL, "initial fields are not finite at cell %lld", (long long)n);
-    if (!(rho > 0.0)) return fail(LBM_EINVAL, "initial density %g at cell %lld is not positive", rho, (long long)n);
-    const double pr = g1 * (E - 0.5 * (m0 * m0 + m1 * m1 + m2 * m2) / rho);
-    if (!(pr > 0.0)) return fail(LBM_EINVAL, "initial pressure %g at cell %lld is not positive", pr, (long long)n);
-  }
-  return LBM_OK;
-}
-
 int64_t row_pitch(const lbm_params* p) {
   // rows padded to whole 128-byte lines when the padding is at most a sixteenth of
   // the row (a grid of one row has no +-y or +-z neighbours to align) ...
@@ -196,27 +182,17 @@ InitCoef make_init_coef(const lbm_params* p) {
 }
 
 lbm_status scales_from_fields(Coll& c, const Grid& g, const InitCoef& ic, const double* Q_dev, int64_t N,
-                              hipStream_t s) {
-  unsigned* d = nullptr;
-  if (dev_malloc((void**)&d, 5 * sizeof(unsigned)) != hipSuccess) return fail(LBM_ENOMEM, "hipMalloc failed");
-  lbm_status st = LBM_OK;
+                              unsigned* d, hipStream_t s) {
   if (hipMemsetAsync(d, 0, 5 * sizeof(unsigned), s) != hipSuccess ||
       launch_init_maxabs(g, c, ic, Q_dev, N, d, s) != hipSuccess)
-    st = fail(LBM_EDEVICE, "storage-scale reduction failed");
-  if (st == LBM_OK) st = read_maxabs(c, d, s);
-  (void)hipFree(d);
-  return st;
+    return fail(LBM_EDEVICE, "storage-scale reduction failed");
+  return read_maxabs(c, d, s);
 }
 
-lbm_status scales_from_pops(Coll& c, const float* f_dev, int64_t N, hipStream_t s) {
-  unsigned* d = nullptr;
-  if (dev_malloc((void**)&d, 5 * sizeof(unsigned)) != hipSuccess) return fail(LBM_ENOMEM, "hipMalloc failed");
-  lbm_status st = LBM_OK;
+lbm_status scales_from_pops(Coll& c, const float* f_dev, int64_t N, unsigned* d, hipStream_t s) {
   if (hipMemsetAsync(d, 0, 5 * sizeof(unsigned), s) != hipSuccess || launch_maxabs_pops(f_dev, N, d, s) != hipSuccess)
-    st = fail(LBM_EDEVICE, "storage-scale reduction failed");
-  if (st == LBM_OK) st = read_maxabs(c, d, s);
-  (void)hipFree(d);
-  return st;
+    return fail(LBM_EDEVICE, "storage-scale reduction failed");
+  return read_maxabs(c, d, s);
 }
 
 bool capturing(hipStream_t s) {
@@ -284,6 +260,20 @@ hipError_t dev_malloc(void** p, size_t bytes) {
     e = hipMalloc(p, bytes);
   }
   return e;
+}
+
+Scratch::Scratch(Spare& spare, size_t bytes) : lock(spare.mu) {
+  if (spare.buf && bytes <= spare.bytes) {
+    p = spare.buf;
+    return;
+  }
+  lock.unlock();  // dev_malloc may give the buffer up
+  own = dev_malloc(&p, bytes) == hipSuccess;
+  if (!own) p = nullptr;
+}
+
+Scratch::~Scratch() {
+  if (own) (void)hipFree(p);
 }
 
 Grid make_grid(const lbm_params* p) {
@@ -356,7 +346,7 @@ struct lbm_ctx {
   const float* src = nullptr;  // caller-owned source of eq. 1, [5][N] FP32, or nullptr
   float* partials = nullptr;
   int64_t partials_blocks = 0;
-  float* ring = nullptr;
+  float* ring = nullptr;  // and five words for the FP16 scales behind it
   int32_t ring_used = 0;
   std::vector<int64_t> ring_steps;
   std::deque<lbm_diag> done;
@@ -399,6 +389,8 @@ bool plan_passes(lbm_ctx* c) {
   return true;
 }
 
+unsigned* scale_words(lbm_ctx* c) { return reinterpret_cast<unsigned*>(c->ring + (size_t)kRingCap * kDiagVals); }
+
 lbm_status drain_ring(lbm_ctx* c) {
   if (c->ring_used == 0) return LBM_OK;
   std::vector<float> h((size_t)c->ring_used * kDiagVals);
@@ -427,6 +419,7 @@ lbm_status create_common(const lbm_params* p, void* buf, size_t bytes, void* str
   if (st != LBM_OK) return st;
   lbm_ctx* c = new (std::nothrow) lbm_ctx();
   if (!c) return fail(LBM_ENOMEM, "host allocation of the context failed");
+  grlbm::copy_users(1);
   c->p = *p;
   c->N = (int64_t)p->nx * p->ny * p->nz;
   c->g = make_grid(p);
@@ -462,20 +455,13 @@ lbm_status create_common(const lbm_params* p, void* buf, size_t bytes, void* str
       return bail(fail(LBM_ENOMEM, "hipMalloc of %zu population bytes failed", c->F_bytes));
     c->own_F = true;
   }
-  if (grlbm::dev_malloc((void**)&c->ring, (size_t)kRingCap * kDiagVals * sizeof(float)) != hipSuccess)
+  if (grlbm::dev_malloc((void**)&c->ring, ((size_t)kRingCap * kDiagVals + 5) * sizeof(float)) != hipSuccess)
     return bail(fail(LBM_ENOMEM, "hipMalloc of the diagnostic ring failed"));
   c->ring_steps.reserve(kRingCap);
   c->spare.device = c->device;
   c->spare.stream = c->stream;
   if (plan_passes(c)) grlbm::take_spare(c->spare, c->F_bytes);
   *out = c;
-  return LBM_OK;
-}
-
-template <typename T>
-lbm_status dev_alloc(T** p, size_t count, const char* what) {
-  if (grlbm::dev_malloc((void**)p, count * sizeof(T)) != hipSuccess)
-    return fail(LBM_ENOMEM, "hipMalloc of %zu bytes (%s) failed", count * sizeof(T), what);
   return LBM_OK;
 }
 
@@ -629,7 +615,8 @@ lbm_status lbm_set_source(lbm_ctx* c, const float* S_dev) {
 lbm_status lbm_init_fields_device(lbm_ctx* c, const double* Q_dev) {
   if (!c || !Q_dev) return fail(LBM_EINVAL, "ctx or Q is NULL");
   if (c->p.storage == LBM_STORE_F16) {
-    lbm_status st = grlbm::scales_from_fields(c->c, c->g, grlbm::make_init_coef(&c->p), Q_dev, c->N, c->stream);
+    lbm_status st = grlbm::scales_from_fields(c->c, c->g, grlbm::make_init_coef(&c->p), Q_dev, c->N,
+                                              scale_words(c), c->stream);
     if (st != LBM_OK) return st;
   }
   HIP_TRY(grlbm::launch_init(c->F, c->p.storage == LBM_STORE_F16, c->g, c->c, grlbm::make_init_coef(&c->p), Q_dev,
@@ -646,15 +633,15 @@ lbm_status lbm_init_fields(lbm_ctx* c, const double* Q) {
   if (!c || !Q) return fail(LBM_EINVAL, "ctx or Q is NULL");
   lbm_status st0 = grlbm::check_fields(&c->p, Q);
   if (st0 != LBM_OK) return st0;
-  double* d = nullptr;
-  lbm_status st = dev_alloc(&d, (size_t)5 * c->N, "initial fields");
-  if (st != LBM_OK) return st;
-  hipError_t e = hipMemcpyAsync(d, Q, (size_t)5 * c->N * sizeof(double), hipMemcpyHostToDevice, c->stream);
+  const size_t bytes = (size_t)5 * c->N * sizeof(double);
+  grlbm::Scratch d(c->spare, bytes);
+  if (!d.p) return fail(LBM_ENOMEM, "hipMalloc of %zu bytes (initial fields) failed", bytes);
+  lbm_status st = LBM_OK;
+  hipError_t e = grlbm::copy_in(d.p, Q, bytes, c->stream);
   if (e == hipSuccess) {
-    st = lbm_init_fields_device(c, d);
+    st = lbm_init_fields_device(c, (const double*)d.p);
     e = hipStreamSynchronize(c->stream);
   }
-  (void)hipFree(d);
   if (e != hipSuccess) return fail(LBM_EDEVICE, "initialisation failed: %s", hipGetErrorString(e));
   return st;
 }
@@ -755,18 +742,14 @@ lbm_status lbm_moments_device(lbm_ctx* c, double* Q_dev) {
 lbm_status lbm_moments(lbm_ctx* c, double* Q_out) {
   if (!c || !Q_out) return fail(LBM_EINVAL, "ctx or Q_out is NULL");
   if (!c->ready) return fail(LBM_ESTATE, "no state yet");
-  double* d = nullptr;
-  lbm_status st = dev_alloc(&d, (size_t)5 * c->N, "moments");
+  const size_t bytes = (size_t)5 * c->N * sizeof(double);
+  grlbm::Scratch d(c->spare, bytes);
+  if (!d.p) return fail(LBM_ENOMEM, "hipMalloc of %zu bytes (moments) failed", bytes);
+  lbm_status st = lbm_moments_device(c, (double*)d.p);
   if (st != LBM_OK) return st;
-  st = lbm_moments_device(c, d);
-  hipError_t e = hipSuccess;
-  if (st == LBM_OK) {
-    e = hipMemcpyAsync(Q_out, d, (size_t)5 * c->N * sizeof(double), hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-  }
-  (void)hipFree(d);
+  hipError_t e = grlbm::copy_out(Q_out, d.p, bytes, c->stream);
   if (e != hipSuccess) return fail(LBM_EDEVICE, "moments readout failed: %s", hipGetErrorString(e));
-  return st;
+  return LBM_OK;
 }
 
 lbm_status lbm_diagnostics(lbm_ctx* c, lbm_diag* out, int32_t max, int32_t* count) {
@@ -788,15 +771,12 @@ lbm_status lbm_diagnostics(lbm_ctx* c, lbm_diag* out, int32_t max, int32_t* coun
 lbm_status lbm_get_populations(lbm_ctx* c, float* f, int64_t* step) {
   if (!c || !f) return fail(LBM_EINVAL, "ctx or f is NULL");
   if (!c->ready) return fail(LBM_ESTATE, "no state yet");
-  float* d = nullptr;
-  lbm_status st = dev_alloc(&d, (size_t)35 * c->N, "populations");
-  if (st != LBM_OK) return st;
+  const size_t bytes = (size_t)35 * c->N * sizeof(float);
+  grlbm::Scratch d(c->spare, bytes);
+  if (!d.p) return fail(LBM_ENOMEM, "hipMalloc of %zu bytes (populations) failed", bytes);
   hipError_t e = grlbm::launch_gather(c->F, c->p.storage == LBM_STORE_F16, c->g, c->c, c->N,
-                                      (c->step & 1) != 0, 0, d, nullptr, c->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(f, d, (size_t)35 * c->N * sizeof(float), hipMemcpyDeviceToHost, c->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-  (void)hipFree(d);
+                                      (c->step & 1) != 0, 0, (float*)d.p, nullptr, c->stream);
+  if (e == hipSuccess) e = grlbm::copy_out(f, d.p, bytes, c->stream);
   if (e != hipSuccess) return fail(LBM_EDEVICE, "population readout failed: %s", hipGetErrorString(e));
   if (step) *step = c->step;
   return LBM_OK;
@@ -805,22 +785,18 @@ lbm_status lbm_get_populations(lbm_ctx* c, float* f, int64_t* step) {
 lbm_status lbm_set_populations(lbm_ctx* c, const float* f, int64_t step) {
   if (!c || !f) return fail(LBM_EINVAL, "ctx or f is NULL");
   if (step < 0) return fail(LBM_EINVAL, "step < 0");
-  float* d = nullptr;
-  lbm_status st = dev_alloc(&d, (size_t)35 * c->N, "populations");
-  if (st != LBM_OK) return st;
-  hipError_t e = hipMemcpyAsync(d, f, (size_t)35 * c->N * sizeof(float), hipMemcpyHostToDevice, c->stream);
+  const size_t bytes = (size_t)35 * c->N * sizeof(float);
+  grlbm::Scratch d(c->spare, bytes);
+  if (!d.p) return fail(LBM_ENOMEM, "hipMalloc of %zu bytes (populations) failed", bytes);
+  hipError_t e = grlbm::copy_in(d.p, f, bytes, c->stream);
   if (e == hipSuccess && c->p.storage == LBM_STORE_F16) {
-    st = grlbm::scales_from_pops(c->c, d, c->N, c->stream);
-    if (st != LBM_OK) {
-      (void)hipFree(d);
-      return st;
-    }
+    lbm_status st = grlbm::scales_from_pops(c->c, (const float*)d.p, c->N, scale_words(c), c->stream);
+    if (st != LBM_OK) return st;
   }
   if (e == hipSuccess)
-    e = grlbm::launch_scatter(c->F, c->p.storage == LBM_STORE_F16, c->g, c->c, c->N, (step & 1) != 0, d,
-                              c->stream);
+    e = grlbm::launch_scatter(c->F, c->p.storage == LBM_STORE_F16, c->g, c->c, c->N, (step & 1) != 0,
+                              (const float*)d.p, c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-  (void)hipFree(d);
   if (e != hipSuccess) return fail(LBM_EDEVICE, "population restore failed: %s", hipGetErrorString(e));
   c->step = step;
   c->ready = true;
@@ -847,6 +823,7 @@ lbm_status lbm_destroy(lbm_ctx* c) {
   if (c->ring) (void)hipFree(c->ring);
   if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);
   delete c;
+  grlbm::copy_users(-1);
   return st;
 }
 

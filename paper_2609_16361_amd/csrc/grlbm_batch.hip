@@ -277,6 +277,7 @@ struct lbm_batch {
   grlbm::CheckItem* d_check = nullptr;  // items of the divergence check (grown on demand)
   size_t check_cap = 0;
   int32_t* d_flags = nullptr;           // one flag per live instance (max_inst)
+  unsigned* d_scales = nullptr;         // five words for the FP16 scales
   std::vector<HostInst> insts;
   int64_t clock = 0;
   int32_t graph_steps = 16;
@@ -724,6 +725,7 @@ lbm_status lbm_batch_create(size_t arena_bytes, int32_t max_instances, int32_t m
                 max_instances, max_tiles, graph_steps);
   lbm_batch* b = new (std::nothrow) lbm_batch();
   if (!b) return fail(LBM_ENOMEM, "host allocation failed");
+  grlbm::copy_users(1);
   auto bail = [&](lbm_status s) {
     lbm_batch_destroy(b);
     return s;
@@ -749,6 +751,7 @@ lbm_status lbm_batch_create(size_t arena_bytes, int32_t max_instances, int32_t m
       grlbm::dev_malloc((void**)&b->d_tiles, sizeof(BatchTile) * (size_t)max_tiles * kGroups) != hipSuccess ||
       grlbm::dev_malloc((void**)&b->d_multi, sizeof(BatchTile) * (size_t)max_tiles * kGroups) != hipSuccess ||
       grlbm::dev_malloc((void**)&b->d_runs, sizeof(b->runs)) != hipSuccess ||
+      grlbm::dev_malloc((void**)&b->d_scales, 5 * sizeof(unsigned)) != hipSuccess ||
       grlbm::dev_malloc((void**)&b->d_clock, sizeof(int64_t)) != hipSuccess ||
       grlbm::dev_malloc((void**)&b->d_flags, sizeof(int32_t) * (size_t)max_instances) != hipSuccess)
     return bail(fail(LBM_ENOMEM, "hipMalloc of the batch tables failed"));
@@ -818,25 +821,25 @@ lbm_status lbm_batch_add(lbm_batch* b, const lbm_params* p, const double* Q, int
   h.d.cells = (int32_t)grlbm::row_cells(h.d.g);
   h.d.inv_px = 1.0 / h.d.g.px;
   h.d.inv_ny = 1.0 / p->ny;
-  double* dq = nullptr;
-  if (grlbm::dev_malloc((void**)&dq, sizeof(double) * 5 * (size_t)N) != hipSuccess) {
+  const size_t field_bytes = sizeof(double) * 5 * (size_t)N;
+  grlbm::Scratch dq(b->spare, field_bytes);
+  if (!dq.p) {
     arena_free(b, off, bytes);
     return fail(LBM_ENOMEM, "staging allocation for the initial fields failed");
   }
-  hipError_t e = hipMemcpyAsync(dq, Q, sizeof(double) * 5 * (size_t)N, hipMemcpyHostToDevice, b->stream);
+  const double* Qd = (const double*)dq.p;
+  hipError_t e = grlbm::copy_in(dq.p, Q, field_bytes, b->stream);
   if (e == hipSuccess && p->storage == LBM_STORE_F16) {
-    st = grlbm::scales_from_fields(h.d.c, h.d.g, grlbm::make_init_coef(p), dq, N, b->stream);
+    st = grlbm::scales_from_fields(h.d.c, h.d.g, grlbm::make_init_coef(p), Qd, N, b->d_scales, b->stream);
     if (st != LBM_OK) {
-      (void)hipFree(dq);
       arena_free(b, off, bytes);
       return st;
     }
   }
   if (e == hipSuccess)
-    e = grlbm::launch_init(b->arena + off, p->storage == LBM_STORE_F16, h.d.g, h.d.c, grlbm::make_init_coef(p), dq,
+    e = grlbm::launch_init(b->arena + off, p->storage == LBM_STORE_F16, h.d.g, h.d.c, grlbm::make_init_coef(p), Qd,
                            N, b->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
-  (void)hipFree(dq);
   if (e != hipSuccess) {
     arena_free(b, off, bytes);
     return fail(LBM_EDEVICE, "instance initialisation failed: %s", hipGetErrorString(e));
@@ -870,15 +873,12 @@ lbm_status lbm_batch_moments(lbm_batch* b, int32_t id, double* Q_out) {
   const HostInst& h = b->insts[id];
   const int64_t N = (int64_t)h.p.nx * h.p.ny * h.p.nz;
   const int el = h.p.storage == LBM_STORE_F16 ? 2 : 4;
-  double* d = nullptr;
-  if (grlbm::dev_malloc((void**)&d, sizeof(double) * 5 * (size_t)N) != hipSuccess)
-    return fail(LBM_ENOMEM, "staging allocation for the moments failed");
+  const size_t bytes = sizeof(double) * 5 * (size_t)N;
+  grlbm::Scratch d(b->spare, bytes);
+  if (!d.p) return fail(LBM_ENOMEM, "staging allocation for the moments failed");
   hipError_t e = grlbm::launch_gather(b->arena + (size_t)h.d.off * el, h.p.storage == LBM_STORE_F16, h.d.g, h.d.c, N,
-                                      (completed_steps(b, h) & 1) != 0, 1, nullptr, d, b->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(Q_out, d, sizeof(double) * 5 * (size_t)N, hipMemcpyDeviceToHost, b->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
-  (void)hipFree(d);
+                                      (completed_steps(b, h) & 1) != 0, 1, nullptr, (double*)d.p, b->stream);
+  if (e == hipSuccess) e = grlbm::copy_out(Q_out, d.p, bytes, b->stream);
   if (e != hipSuccess) return fail(LBM_EDEVICE, "moments readout failed: %s", hipGetErrorString(e));
   return LBM_OK;
 }
@@ -890,16 +890,13 @@ lbm_status lbm_batch_populations(lbm_batch* b, int32_t id, float* f_out, int64_t
   const HostInst& h = b->insts[id];
   const int64_t N = (int64_t)h.p.nx * h.p.ny * h.p.nz;
   const int el = h.p.storage == LBM_STORE_F16 ? 2 : 4;
-  float* d = nullptr;
-  if (grlbm::dev_malloc((void**)&d, sizeof(float) * 35 * (size_t)N) != hipSuccess)
-    return fail(LBM_ENOMEM, "staging allocation for the populations failed");
+  const size_t bytes = sizeof(float) * 35 * (size_t)N;
+  grlbm::Scratch d(b->spare, bytes);
+  if (!d.p) return fail(LBM_ENOMEM, "staging allocation for the populations failed");
   const int64_t done = completed_steps(b, h);
   hipError_t e = grlbm::launch_gather(b->arena + (size_t)h.d.off * el, h.p.storage == LBM_STORE_F16, h.d.g, h.d.c, N,
-                                      (done & 1) != 0, 0, d, nullptr, b->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(f_out, d, sizeof(float) * 35 * (size_t)N, hipMemcpyDeviceToHost, b->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
-  (void)hipFree(d);
+                                      (done & 1) != 0, 0, (float*)d.p, nullptr, b->stream);
+  if (e == hipSuccess) e = grlbm::copy_out(f_out, d.p, bytes, b->stream);
   if (e != hipSuccess) return fail(LBM_EDEVICE, "population readout failed: %s", hipGetErrorString(e));
   if (step) *step = done;
   return LBM_OK;
@@ -1140,8 +1137,10 @@ lbm_status lbm_batch_destroy(lbm_batch* b) {
   if (b->d_clock) (void)hipFree(b->d_clock);
   if (b->d_check) (void)hipFree(b->d_check);
   if (b->d_flags) (void)hipFree(b->d_flags);
+  if (b->d_scales) (void)hipFree(b->d_scales);
   if (b->own_stream && b->stream) (void)hipStreamDestroy(b->stream);
   delete b;
+  grlbm::copy_users(-1);
   return st;
 }
 

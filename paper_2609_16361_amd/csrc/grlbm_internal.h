@@ -35,6 +35,23 @@ struct Spare {
 void take_spare(Spare& s, size_t bytes);
 void drop_spare(Spare& s);  // frees it, if s has one; its owner's work is done
 bool capturing(hipStream_t s);
+// Copies between host and device memory in order with the work on s; they return when
+// the copy is done.  copy_users counts the contexts and batches, for which pinned slots
+// are kept.
+hipError_t copy_out(void* host, const void* dev, size_t bytes, hipStream_t s);
+hipError_t copy_in(void* dev, const void* host, size_t bytes, hipStream_t s);
+void copy_users(int change);
+// Device memory of one call on a context's or batch's stream: its second buffer, held by
+// the lock, where that is large enough, else memory of its own.
+struct Scratch {
+  std::unique_lock<std::mutex> lock;
+  void* p = nullptr;
+  bool own = false;
+  Scratch(Spare& spare, size_t bytes);
+  ~Scratch();
+  Scratch(const Scratch&) = delete;
+  Scratch& operator=(const Scratch&) = delete;
+};
 // hipMalloc; out of memory, it first gives up the second buffers of the current device
 // (each after the work on its stream, but not where the stream is being captured).
 hipError_t dev_malloc(void** p, size_t bytes);
@@ -163,9 +180,10 @@ hipError_t launch_maxabs_pops(const float* f, int64_t N, unsigned* maxabs, hipSt
 void set_storage_scales(Coll& c, const unsigned maxabs_bits[5]);
 // Scales from the initial fields Q (device) or from canonical populations f
 // (device); synchronises the stream to read the maxima back.
+// d: five words of device memory.
 lbm_status scales_from_fields(Coll& c, const Grid& g, const InitCoef& ic, const double* Q_dev, int64_t N,
-                              hipStream_t s);
-lbm_status scales_from_pops(Coll& c, const float* f_dev, int64_t N, hipStream_t s);
+                              unsigned* d, hipStream_t s);
+lbm_status scales_from_pops(Coll& c, const float* f_dev, int64_t N, unsigned* d, hipStream_t s);
 hipError_t launch_copy(const void* a, void* b, int64_t bytes, hipStream_t s);
 
 }  // namespace grlbm
