@@ -461,14 +461,18 @@ def measured_traffic():
 
 def passes(first, steps, diag_every):
     """Passes over the state that lbm_step(steps, diag_every) makes from step `first`
-    on where it runs step pairs: two steps per pass from an odd step on, four steps at
-    a time, up to the next step with diagnostics; one step per pass otherwise."""
-    n, t, end = 0, first, first + steps
+    on where it runs step pairs: two steps per pass from an odd step on, up to the next
+    step with diagnostics (an even number of pairs, unless a single step of the same run
+    comes before them); one step per pass otherwise."""
+    n, t, end, after_single = 0, first, first + steps, False
     while t < end:
-        stop = end if not diag_every else min(end, t + diag_every - t % diag_every)
-        four = (stop - t) // 4 if t % 2 and not (diag_every and t % diag_every == 0) else 0
-        n += 2 * four if four else 1
-        t += 4 * four if four else 1
+        run = end - t if not diag_every else min(end - t, diag_every - t % diag_every)
+        pairs = run // 2 if t % 2 and not (diag_every and t % diag_every == 0) else 0
+        if pairs and not after_single:
+            pairs = pairs // 2 * 2
+        n += pairs or 1
+        t += 2 * pairs or 1
+        after_single = pairs == 0 and t % 2 == 1
     return n
 
 

@@ -162,7 +162,7 @@ lbm_status lbm_init_fields_device(lbm_ctx* ctx, const double* Q_dev);
 /* Enqueue n >= 0 collide-and-stream steps on the context's stream (asynchronous).
  * If diag_every > 0, every step whose index t (completed steps before it) satisfies
  * t % diag_every == 0 also produces a diagnostic record (see lbm_diagnostics).
- * ESTATE before initialisation.  A call of four steps or more may make several per
+ * ESTATE before initialisation.  A call of three steps or more may make several per
  * pass (above), up to the next step with diagnostics.  On a stream under capture the
  * steps are single. */
 lbm_status lbm_step(lbm_ctx* ctx, int64_t n, int32_t diag_every);

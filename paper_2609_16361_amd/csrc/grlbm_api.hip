@@ -668,46 +668,63 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n, int32_t diag_every) {
     if (st != LBM_OK) return st;
   }
   // Steps run several to a pass where a second buffer is there, up to the next step with
-  // diagnostics: tubes from an even step on, pairs from an odd one.  The passes of a run
-  // are even in number, so that the state is back in the context's own buffer.  Not with
+  // diagnostics: tubes from an even step on, pairs from an odd one.  The passes of a run,
+  // with the even step before it where that stores to the second buffer, are even in
+  // number, so that the state is back in the context's own buffer.  Not with
   // a source or with the direct odd step asked for, and not under capture: a captured
   // launch would keep the address of a buffer that may be given up later.
   std::unique_lock<std::mutex> use_spare(c->spare.mu, std::defer_lock);
   bool passes = false;
-  if (n >= 4 && !c->src && c->odd_lds && !c->single_steps && !grlbm::capturing(c->stream)) {
+  if (n >= 3 && !c->src && c->odd_lds && !c->single_steps && !grlbm::capturing(c->stream)) {
     use_spare.lock();
     passes = c->spare.buf != nullptr;
   }
+  // Steps from t up to the next one with diagnostics, t itself left out of account.
+  const auto run_from = [&](int64_t t, int64_t left) {
+    return diag_every > 0 ? std::min<int64_t>(left, diag_every - t % diag_every) : left;
+  };
+  bool moved = false;  // an even step has stored to the second buffer, for an odd number of pairs
   for (int64_t s = 0; s < n; ++s) {
     const int64_t t = c->step;
     const bool diag = diag_every > 0 && (t % diag_every) == 0;
-    if (passes && !diag && ((t & 1) == 0) == (c->tube.lanes > 0)) {
-      int64_t m = n - s;
-      if (diag_every > 0) m = std::min<int64_t>(m, diag_every - t % diag_every);
-      if (c->tube.lanes) {
-        m = c->tube.steps > 2 ? m / 2 * 2 : m / 4 * 4;  // at least two steps a launch
-        const int64_t launches = m >= 4 ? (m + 2 * c->tube.steps - 1) / (2 * c->tube.steps) * 2 : 0;
+    L.to = nullptr;
+    if (passes && c->tube.lanes && !diag && (t & 1) == 0) {
+      int64_t m = run_from(t, n - s);
+      m = c->tube.steps > 2 ? m / 2 * 2 : m / 4 * 4;  // at least two steps a launch
+      if (m >= 4) {
         void *from = c->F, *to = c->spare.buf;
         int64_t left = m / 2;  // in steps of two, dealt evenly
-        for (int64_t i = launches; i > 0; --i) {
-          const int two = (int)(left / i);
+        for (int64_t i = (m + 2 * c->tube.steps - 1) / (2 * c->tube.steps) * 2; i > 0; --i) {
+          const int64_t two = left / i;
+          HIP_TRY(grlbm::launch_tube(L, c->tube, c->cus, from, to, (int)(2 * two), t + m - 2 * left, c->stream));
           left -= two;
-          HIP_TRY(grlbm::launch_tube(L, c->tube, c->cus, from, to, 2 * two, t + m - 2 * (left + two), c->stream));
           std::swap(from, to);
         }
-        if (launches == 0) m = 0;
         c->step += m;
-      } else {
-        m = m / 4 * 4;
-        for (int64_t i = 0; i < m; i += 4) {
-          HIP_TRY(grlbm::launch_pair(L, c->pair, c->F, c->spare.buf, c->stream));
-          HIP_TRY(grlbm::launch_pair(L, c->pair, c->spare.buf, c->F, c->stream));
-          c->step += 4;
-        }
-      }
-      if (m > 0) {
         s += m - 1;
         continue;
+      }
+    }
+    if (passes && !c->tube.lanes) {
+      if ((t & 1) == 0) {
+        // pairs that would follow this step: an odd number of them starts from the second
+        // buffer and ends in the context's own
+        moved = run_from(t, n - s) >= 3 && ((run_from(t, n - s) - 1) / 2) % 2 != 0;
+        if (moved) L.to = c->spare.buf;
+      } else if (!diag) {
+        int64_t pairs = run_from(t, n - s) / 2;
+        if (!moved) pairs = pairs / 2 * 2;
+        void *from = moved ? c->spare.buf : c->F, *to = moved ? c->F : c->spare.buf;
+        moved = false;
+        for (int64_t i = 0; i < pairs; ++i) {
+          HIP_TRY(grlbm::launch_pair(L, c->pair, from, to, c->stream));
+          std::swap(from, to);
+        }
+        if (pairs > 0) {
+          c->step += 2 * pairs;
+          s += 2 * pairs - 1;
+          continue;
+        }
       }
     }
     L.odd = (t & 1) != 0;

@@ -478,10 +478,11 @@ __device__ __forceinline__ void add_source(float f[kPop], const float* __restric
 // One cell's AA half step: gather the post-stream populations, run the collision of
 // Algorithm 1 in registers, scatter the post-collision ones.  F points at slot 0 of
 // the instance's arrays.  With DIAG, vals[9] receives the cell's diagnostic densities.
-template <bool ODD, int COLL, typename T, bool ZG, bool DIAG, bool NT, bool SRC = false>
+// With TO the populations are stored to the arrays of D, of the same grid, instead.
+template <bool ODD, int COLL, typename T, bool ZG, bool DIAG, bool NT, bool SRC = false, bool TO = false>
 __device__ __forceinline__ void cell_update(T* __restrict__ F, const Grid& g, const Coll& c, int x,
                                             int y, int z, float* vals, uint32_t skey,
-                                            const float* __restrict__ src = nullptr) {
+                                            const float* __restrict__ src = nullptr, T* __restrict__ D = nullptr) {
   const Nbr b = make_nbr(g, x, y, z);
   const int64_t S = g.S;
   float f[kPop];
@@ -523,7 +524,7 @@ __device__ __forceinline__ void cell_update(T* __restrict__ F, const Grid& g, co
   }
 #pragma unroll
   for (int k = 0; k < kFields; ++k) {
-    T* Fk = F + (int64_t)(7 * k) * S;
+    T* Fk = (TO ? D : F) + (int64_t)(7 * k) * S;
     const float* fo = f + 7 * k;
     const int s0 = 7 * k;
     if constexpr (!ODD) {

@@ -79,6 +79,7 @@ InitCoef make_init_coef(const lbm_params* p);
 
 struct StepLaunch {
   void* F;           // population buffer
+  void* to = nullptr;  // even FP32 step without a source: where it stores, if not to F
   Grid g;
   Coll c;
   float* partials;   // per-block diagnostic partials (diag only)

@@ -106,6 +106,22 @@ __global__ void __launch_bounds__(1024) k_step(T* __restrict__ F, Grid g, Coll c
   if constexpr (DIAG) block_reduce_store(vals, partials);
 }
 
+// Even AA step from F to the second buffer D (FP32): lets a run of step pairs that is odd
+// in number start from D and end in F.  Bitwise the same values as k_step's even step.
+template <int COLL, bool ZG, bool DIAG, bool NT>
+__global__ void __launch_bounds__(1024) k_step_even_to(float* __restrict__ F, float* __restrict__ D, Grid g, Coll c,
+                                                        float* __restrict__ partials) {
+  const CellPos pos = block_cell(g);
+  float vals[kDiagVals];
+  if constexpr (DIAG) {
+#pragma unroll
+    for (int j = 0; j < kDiagVals; ++j) vals[j] = 0.0f;
+  }
+  if (pos.active)
+    cell_update<false, COLL, float, ZG, DIAG, NT, false, true>(F, g, c, pos.x, pos.y, pos.z, vals, 0u, nullptr, D);
+  if constexpr (DIAG) block_reduce_store(vals, partials);
+}
+
 // Even AA step for FP16 storage with two consecutive cells per lane
 // (pair_update_even); needs an even cell count and blocks of at most 256 threads
 // (two cells' populations in registers), and runs on grids of kPairMinCells and
@@ -487,6 +503,13 @@ static hipError_t launch_step_nt(const StepLaunch& L, hipStream_t s) {
     }
   }
   const int64_t blocks = step_blocks(g, L.block);
+  if constexpr (!ODD && sizeof(T) == 4 && !SRC) {
+    if (L.to) {
+      hipLaunchKernelGGL((k_step_even_to<COLL, ZG, DIAG, NT>), dim3((unsigned)blocks), dim3(L.block), L.lds, s, F,
+                         (float*)L.to, g, L.c, L.partials);
+      return hipGetLastError();
+    }
+  }
   hipLaunchKernelGGL((k_step<ODD, COLL, T, ZG, DIAG, NT, SRC>), dim3((unsigned)blocks), dim3(L.block), L.lds, s,
                      F, g, L.c, L.partials, L.src, L.skey);
   return hipGetLastError();

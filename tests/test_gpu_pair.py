@@ -40,7 +40,8 @@ def test_pairs_are_bitwise_single_steps(dims, bc, collision):
     assert np.array_equal(f.view(np.uint32), g.view(np.uint32))
 
 
-@pytest.mark.parametrize("calls,diag_every", [([4, 4, 7, 1, 22], 0), ([5, 33], 7), ([40], 10), ([1, 4, 3, 12], 4)])
+@pytest.mark.parametrize("calls,diag_every", [([4, 4, 7, 1, 22], 0), ([5, 33], 7), ([40], 10), ([1, 4, 3, 12], 4),
+                                              ([20, 3, 1, 8], 0), ([40], 20), ([2, 3, 31], 12), ([9, 6], 1), ([30], 3)])
 def test_pairs_between_calls_and_diagnostics(calls, diag_every):
     print("pairs", calls, diag_every, flush=True)
     case = inputs.random_smooth(96, 20, 12, seed=4, amp=0.05)
