@@ -58,7 +58,10 @@ __global__ void __launch_bounds__(kPairThreads) k_step_pair(const float* __restr
 // what neighbours share (512^3, 128 x 4 tiles: 4005 us per step with 64-plane segments,
 // 4376 with 128, 4599 with 512).  The weights were fitted to timings of 20 grids from
 // 64^3 to 512^3 in up to 60 tilings each: the choice ran within 1% of the best on
-// average, 3% at worst.  With `share`, cus is a grid's part of a card that others fill.
+// average, 3% at worst.  A tiling that leaves CUs free is preferred where it is nearly
+// as fast: on small grids it makes fewer collisions twice, and other streams can use
+// them (three contexts of 40^3 together: 3.0 us per step with 160 tiles of 40 x 10 x 1,
+// 4.3 with 240 of 40 x 7 x 1, one alone 5.8 and 5.9).  With `share`, cus is a grid's part of a card that others fill.
 PairTiles pair_tiles(const Grid& g, int cus, bool share) {
   PairTiles best{};
   double best_cost = 1e300;
@@ -72,7 +75,9 @@ PairTiles pair_tiles(const Grid& g, int cus, bool share) {
     const double row = w / 32.0 + (lines ? 0.0 : 1.0);
     const double reads = (h + (fully ? 0 : 2)) * row + (fullx ? 0.0 : 1.9 * h);
     const double memory = 8.7 * reads + 1.35 * h * row;
-    const double issue = 333.0 + 1.5 * (double)(2 * up((int64_t)w * h, 64) + up(halo, 64));
+    const int64_t inner = up((int64_t)w * h, 64), outer = up(halo, 64);
+    const double issue = inner + outer <= 4 ? 300.0 + 5.0 * (double)(inner + outer)  // a wave per SIMD
+                                            : 333.0 + 1.5 * (double)(2 * inner + outer);
     const int ntx = (int)up(g.nx, w), nty = (int)up(g.ny, h);
     const int64_t nxy = (int64_t)ntx * nty;
     int nseg = 0;
@@ -85,6 +90,11 @@ PairTiles pair_tiles(const Grid& g, int cus, bool share) {
         const double filled = turns > 1 || share ? 1.0 : (double)(nxy * nseg) / (8.0 * per);
         const double m = memory * std::sqrt(filled);
         double cost = (double)turns * (lz + 9) * (std::max(m, issue) + 0.11 * std::min(m, issue));
+        // the part of the card that other work could use meanwhile
+        cost *= 1.0 + 0.25 * std::min(1.0, (double)(nxy * nseg) / (share ? cus : 8 * per));
+        // tiles that cut aligned rows inside lines share the lines they store; beyond the
+        // Infinity Cache those cross HBM in pieces (288^3: 1054 us with 72 x 7, 754 with 96 x 5)
+        if (!lines && g.px % 32 == 0 && 140 * row_cells(g) >= (256ll << 20)) cost *= 1.25;
         if (turns > 1 && by_plane) cost *= 0.999;  // equal turns: all XCDs in one segment
         if (turns > 1 && lz > 64) cost *= 1.0 + 0.375 * std::min(2.0, lz / 128.0);
         if (cost < best_cost) {
