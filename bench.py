@@ -157,7 +157,9 @@ def bench_batch(count=64, steps=5000, seed=0, stream=None, tuning=None, sequenti
             errs.append(becker_linf(c, b.moments(i))[0])
     t_wall = time.perf_counter() - t_wall
     out["batched"] = {"solves_per_s": count / t_batch, "run_s": t_batch, "glups": cells * steps / t_batch / 1e9,
-                      "hbm_frac": 280.0 * cells * steps / t_batch / 1e9 / HBM_PEAK_GBS,
+                      # one-step traffic (280 B per update) over the HBM peak: above 1
+                      # where a pass over memory makes several steps
+                      "one_step_traffic_vs_peak": 280.0 * cells * steps / t_batch / 1e9 / HBM_PEAK_GBS,
                       "tuning": best, "tuned_us_per_step": best_us, "candidates": len(tried),
                       "wall_s_incl_init_readout": t_wall}
     out["linf_rel_error"] = {"median": float(np.median(errs)), "max": float(np.max(errs)),
@@ -316,7 +318,8 @@ FP16_MAX_STEPS = 12000
 # the batch: from about this size the single-context kernels, with plain access up
 # to 320 MB and nontemporal beyond, move a state faster than the batch kernel does
 # (the mix's vortices of 63^3-127^3 alone at 17.9-22.6 GLUP/s against 17.4 for all
-# of its vortices in one batch), while smaller states are launch-bound alone.
+# of its vortices in one batch, all in single steps), while smaller states are
+# launch-bound alone.
 SOLO_MIN_BYTES = 24 << 20
 
 
@@ -445,11 +448,13 @@ def bench_serve(stream, count=64, rate=50.0, seed=1, budget_bytes=200 * 10 ** 9,
     return out
 
 
-def measured_traffic():
-    """HBM bytes per launch of the collide-and-stream kernel from the committed
+def measured_traffic(paired=False):
+    """HBM bytes per launch of the collide-and-stream kernel (the step pair's, which
+    makes 96% of a paired run's steps, or a single step's) from the committed
     FETCH_SIZE/WRITE_SIZE counter runs, or None if the kernel sources changed since."""
     import hashlib
-    path = os.path.join(ROOT, "profiles", "k_step_tgv256_traffic.json")
+    name = "k_step_pair_tgv256_traffic.json" if paired else "k_step_tgv256_traffic.json"
+    path = os.path.join(ROOT, "profiles", name)
     if not os.path.exists(path):
         return None
     rec = json.load(open(path))
@@ -624,7 +629,7 @@ def main():
                    "parallelism": "single GPU"},
         "roofline": {"bound": "hbm", "achieved": round(achieved_gbs, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(achieved_gbs / HBM_PEAK_GBS, 4),
-                     "traffic": None if args.fp16 or args.n != 256 or paired else measured_traffic(),
+                     "traffic": None if args.fp16 or args.n != 256 else measured_traffic(paired),
                      "traffic_unit": "bytes per launch",
                      "bytes_per_lup": round(bytes_per_lup * launches / args.steps, 3),
                      "steps_per_launch": round(args.steps / launches, 4),

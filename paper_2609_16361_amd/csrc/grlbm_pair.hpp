@@ -36,7 +36,7 @@ __device__ __forceinline__ const T* at_byte(const T* base, uint32_t byte) {
 // the writes wrap.
 //
 // Bound by HBM: 140 + 140 B per cell and pair, the halo's lines come from L2 (at
-// 256^3 the counters show 145 + 140 B).  One block of 13 waves per CU at 118-125
+// 256^3 the counters show 148 + 140 B).  One block of 13 waves per CU at 118-125
 // registers; 5.3 TB/s, VALU 41% busy.  Measured on MI355X against two single steps
 // (us per step): 256^3 794 -> 449, 128^3 99.8 -> 59, 111^3 59.8 -> 48.5, 96^3 37.8
 // -> 25, 512^3 6845 -> 4100.  Loading the next plane ahead into registers gained
