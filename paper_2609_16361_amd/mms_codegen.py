@@ -6,8 +6,8 @@ state, flux with the Newtonian stress and the Fourier flux at constant mu and
 kappa, T = p/rho) and the fields of eq. 8 in SymPy, differentiates symbolically,
 eliminates common subexpressions, and prints a HIP kernel that evaluates the five
 components of S at every cell of an n^3 lattice in FP64 and stores them as FP32.
-The subexpressions that depend on one coordinate alone (all the sines and cosines)
-are evaluated once per coordinate of a block's tile and kept in LDS.
+What depends on one coordinate alone (all the sines and cosines, terms and factors)
+is evaluated once per coordinate of a block's tile and kept in LDS.
 The constants (rho0, U, P0, a, K, W, gamma, mu, kappa, lattice units) stay
 symbolic, so one kernel serves every resolution.
 
@@ -59,16 +59,61 @@ def ccode(e) -> str:
                                                (lambda b, n: n == -1, lambda b, n: f"(1.0/({b}))")]})
 
 
+def group_by_coordinate(subs, red, dep, axes):
+    """Inside expressions of several coordinates, the terms of a sum and the factors of
+    a product that depend on one coordinate become one value of that coordinate, with
+    the constants among them, so that a cell's own work is what mixes coordinates.  New
+    symbols are entered in dep and defined before use."""
+    known, out = {}, []
+    names = sp.numbered_symbols("g")
+
+    def of(e):
+        return set().union(*(dep[f] for f in e.free_symbols))
+
+    def value(e):
+        if e.is_Atom:
+            return e
+        if e not in known:
+            known[e] = next(names)
+            dep[known[e]] = of(e)
+            out.append((known[e], e))
+        return known[e]
+
+    def walk(e):
+        if len(of(e)) < 2:
+            return value(e)
+        if not (e.is_Add or e.is_Mul):
+            return e if e.is_Atom else e.func(*(walk(a) for a in e.args))
+        fixed = e.func(*(a for a in e.args if not of(a)))
+        rest = [walk(a) for a in e.args if len(of(a)) > 1]
+        for v in axes:
+            part = e.func(*(a for a in e.args if of(a) == {v}))
+            if part != e.identity:
+                part, fixed = e.func(part, fixed), e.identity
+                rest.append(value(part))
+        if fixed != e.identity:
+            rest.append(value(fixed))
+        return e.func(*rest, evaluate=False)
+
+    for s, e in subs:
+        out.append((s, walk(e) if len(dep[s]) > 1 else e))
+    return out, [walk(e) for e in red]
+
+
 def generate() -> str:
     axes, c, S = source_expressions()
     t = axes[3]
     axes = axes[:3]
     subs, red = sp.cse(S, symbols=sp.numbered_symbols("e"), optimizations="basic")
+    # one division serves a reciprocal and its square
+    recip = {e.base: s for s, e in subs if e.is_Pow and e.exp == -1}
+    subs = [(s, e.subs({b ** -2: r ** 2 for b, r in recip.items()})) for s, e in subs]
     # the coordinates each subexpression depends on
     dep = {v: {v} for v in axes}
     dep.update({v: set() for v in list(c.values()) + [t]})
     for sym, ex in subs:
         dep[sym] = set().union(*(dep[f] for f in ex.free_symbols))
+    subs, red = group_by_coordinate(subs, red, dep, axes)
     single = {v: [(s, e) for s, e in subs if dep[s] == {v}] for v in axes}
     common = [(s, e) for s, e in subs if not dep[s]]
     mixed = [(s, e) for s, e in subs if len(dep[s]) > 1]
@@ -77,7 +122,19 @@ def generate() -> str:
     keep = {v: [s for s, _ in single[v] if s in used] for v in axes}
 
     def code(pairs, indent):
-        return "\n".join(f"{indent}const double {s} = {ccode(e)};" for s, e in pairs)
+        # a sine and a cosine of the same argument come from one call
+        trig = {(type(e), e.args[0]): s for s, e in pairs if isinstance(e, (sp.sin, sp.cos))}
+        lines, done = [], set()
+        for s, e in pairs:
+            if s in done:
+                continue
+            sn, cs = (trig.get((f, e.args[0])) if isinstance(e, (sp.sin, sp.cos)) else None for f in (sp.sin, sp.cos))
+            if sn and cs:
+                lines.append(f"{indent}double {sn}, {cs};\n{indent}sincos({ccode(e.args[0])}, &{sn}, &{cs});")
+                done |= {sn, cs}
+            else:
+                lines.append(f"{indent}const double {s} = {ccode(e)};")
+        return "\n".join(lines)
 
     def needed(pairs, exprs):
         """The pairs that the expressions need, directly or through one another."""
@@ -97,8 +154,8 @@ def generate() -> str:
         parts[f"N{v}"] = str(len(keep[v]))
     parts["COMMON"] = code(needed(common, [e for _, e in mixed] + list(red)), "  ")
     parts["LOADX"] = "\n".join(f"  const double {s} = vx[{i}][lane];" for i, s in enumerate(keep[axes[0]]))
-    parts["LOADYZ"] = "\n".join(f"    const double {s} = v{v}[{i}][{'jy' if v == axes[1] else 'jz'}];"
-                                for v in axes[1:] for i, s in enumerate(keep[v]))
+    parts["LOADZ"] = "\n".join(f"  const double {s} = vz[{i}][jz];" for i, s in enumerate(keep[axes[2]]))
+    parts["LOADY"] = "\n".join(f"    const double {s} = vy[{i}][jy];" for i, s in enumerate(keep[axes[1]]))
     parts["MIXED"] = code(mixed, "    ")
     parts["OUT"] = "\n".join(f"    S[{f} * N + n] = (float)({ccode(red[f])});" for f in range(5))
     out = TEMPLATE
@@ -124,28 +181,32 @@ TEMPLATE = r'''// grlbm_mms.hip -- GENERATED by paper_2609_16361_amd/mms_codegen
 
 namespace {
 
-// A block of 4 waves takes a tile of 64 x 8 x tz cells, a wave one row of 64 at a time.
-// Every sine and cosine depends on one coordinate: one wave per axis evaluates the
-// tile's, into LDS, and a cell needs about 350 FP64 operations besides (squares are
-// products: pow(x, 2) is not simplified in FP64 and was half of the work).  Bound by
-// FP64 issue and its latency.  On MI355X 128^3 took 229 us with all of it evaluated per
-// cell, 130 us with pow, 36 us now; 64^3 35 and 9 us, 24^3 11 and 6 us.
-constexpr int TX = 64, TY = 8, TZ = 4;  // tz is at most TZ
+// A block of 4 waves takes a tile of 64 x ty x tz cells, a wave one row of 64 at a time,
+// all of its rows in one plane.  Every sine and cosine depends on one coordinate: one
+// wave per axis evaluates the tile's, into LDS, with all else that depends on that
+// coordinate alone (grouped by the generator); a lane keeps the values of its x and z
+// and needs about 200 FP64 operations per cell besides (squares are products: pow(x, 2)
+// is not simplified in FP64).  Bound by FP64 issue and its latency, at 188 registers.  On
+// MI355X 128^3 took 229 us with all of it evaluated per cell, 34 us with the sines and
+// cosines alone from LDS and about 350 operations per cell, 23 us now; 256^3 215 and 137
+// us in the last two forms, 24^3 11 us, 5.4 and 5.1.  At 168 registers it spills (33 us);
+// z values read per row instead of kept take 29 us.
+constexpr int TX = 64, TY = 16, TZ = 4;  // ty is 8 or TY; tz is 1, 2 or TZ
 
 __device__ __forceinline__ double sq(double v) { return v * v; }
 
-__global__ void __launch_bounds__(256, 3) k_mms_source(lbm_mms m, int32_t nx, int32_t ny, int32_t nz, int32_t tz,
-                                                        double t, float* __restrict__ S) {
+__global__ void __launch_bounds__(256, 2) k_mms_source(lbm_mms m, int32_t nx, int32_t ny, int32_t nz, int32_t ty,
+                                                        int32_t tz, double t, float* __restrict__ S) {
   __shared__ double vx[@Nx@][TX], vy[@Ny@][TY], vz[@Nz@][TZ];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int ntx = (nx + TX - 1) / TX, nty = (ny + TY - 1) / TY;
+  const int ntx = (nx + TX - 1) / TX, nty = (ny + ty - 1) / ty;
   const int r = (int)(blockIdx.x / ntx);
-  const int x0 = (int)(blockIdx.x % ntx) * TX, y0 = (r % nty) * TY, z0 = (r / nty) * tz;
+  const int x0 = (int)(blockIdx.x % ntx) * TX, y0 = (r % nty) * ty, z0 = (r / nty) * tz;
   const int i = lane;
   if (wave == 0) {
     const double x = (double)(x0 + i);
 @AXIS_x@
-  } else if (wave == 1 && i < TY) {
+  } else if (wave == 1 && i < ty) {
     const double y = (double)(y0 + i);
 @AXIS_y@
   } else if (wave == 2 && i < tz) {
@@ -157,11 +218,12 @@ __global__ void __launch_bounds__(256, 3) k_mms_source(lbm_mms m, int32_t nx, in
   const int64_t N = (int64_t)nx * ny * nz;
 @COMMON@
 @LOADX@
-  for (int row = wave; row < TY * tz; row += 4) {
-    const int jy = row % TY, jz = row / TY;
-    if (y0 + jy >= ny || z0 + jz >= nz) continue;
+  const int jz = wave % tz;
+  if (z0 + jz >= nz) return;
+@LOADZ@
+  for (int jy = wave / tz; jy < ty && y0 + jy < ny; jy += 4 / tz) {
     const int64_t n = x0 + lane + (int64_t)nx * (y0 + jy + (int64_t)ny * (z0 + jz));
-@LOADYZ@
+@LOADY@
 @MIXED@
 @OUT@
   }
@@ -175,15 +237,16 @@ extern "C" lbm_status lbm_mms_source(const lbm_mms* m, int32_t nx, int32_t ny, i
   if (nx < 1 || ny < 1 || nz < 1) return grlbm::fail(LBM_EINVAL, "empty lattice %d x %d x %d", nx, ny, nz);
   const int64_t N = (int64_t)nx * ny * nz;
   if (N > ((int64_t)1 << 31)) return grlbm::fail(LBM_EINVAL, "%lld cells exceed 2^31", (long long)N);
-  // the thickest tiles that still give 512 blocks: thicker ones share more of the
-  // sines and cosines (128^3: 36 us with 4 planes, 40 with 2), thinner ones leave a
-  // wave fewer rows to do one after another (64^3: 8.9 us with 2 planes, 12.4 with 4)
-  const int64_t xy = (((int64_t)nx + TX - 1) / TX) * (((int64_t)ny + TY - 1) / TY);
-  int tz = TZ;
-  while (tz > 1 && xy * (((int64_t)nz + tz - 1) / tz) < 512) tz /= 2;
-  const int64_t tiles = xy * (((int64_t)nz + tz - 1) / tz);
-  hipLaunchKernelGGL(k_mms_source, dim3((unsigned)tiles), dim3(256), 0, (hipStream_t)hip_stream, *m, nx, ny, nz, tz,
-                     t, S_dev);
+  // the largest tiles that still give 512 blocks, two for each CU: larger ones share more
+  // of the sines and cosines (128^3: 23 us with 16 rows, 25 with 8), smaller ones leave a
+  // wave fewer rows to do one after another (24^3: 5.1 us with 8 rows, 6.2 with 16)
+  int ty = TY, tz = TZ;
+  auto blocks = [&] {
+    return (((int64_t)nx + TX - 1) / TX) * (((int64_t)ny + ty - 1) / ty) * (((int64_t)nz + tz - 1) / tz);
+  };
+  while (blocks() < 512 && (tz > 1 || ty > 8)) (tz > 1 ? tz : ty) /= 2;
+  hipLaunchKernelGGL(k_mms_source, dim3((unsigned)blocks()), dim3(256), 0, (hipStream_t)hip_stream, *m, nx, ny, nz, ty,
+                     tz, t, S_dev);
   HIP_TRY(hipGetLastError());
   return LBM_OK;
 }
