@@ -143,7 +143,9 @@ hipError_t copy(void* dev, void* host, size_t bytes, bool out, hipStream_t s) {
   int device = 0;
   hipError_t e = hipGetDevice(&device);
   if (e != hipSuccess) return e;
-  const int n = (int)std::min<size_t>(kCopyThreads, (bytes + kChunk - 1) / kChunk);
+  // hipStreamPerThread is another stream in each worker, which would not wait for what
+  // the caller has enqueued: its copies stay in this thread
+  const int n = s == hipStreamPerThread ? 1 : (int)std::min<size_t>(kCopyThreads, (bytes + kChunk - 1) / kChunk);
   hipError_t each[kCopyThreads] = {};
   in_threads(n, [&](int i) { each[i] = move_chunks((char*)dev, (char*)host, bytes, out, s, device, i, n); });
   for (int i = 0; i < n; ++i)

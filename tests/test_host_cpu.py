@@ -1,0 +1,92 @@
+"""The library's host code on a machine without a GPU: which work it enqueues where, what
+it allocates and what it does when a call fails.  Each test runs the built library in a
+process of its own over fake_hip.cpp, a HIP runtime that notes every call, does copies at
+once and runs no kernel, so nothing here says what a kernel computes."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+PRELUDE = """
+import ctypes, re, sys, threading
+sys.modules["torch"] = None  # it would load the real runtime
+fake = ctypes.CDLL({lib!r}, ctypes.RTLD_GLOBAL)
+fake.fake_reset.argtypes = [ctypes.c_size_t]
+fake.fake_capture.argtypes = [ctypes.c_void_p, ctypes.c_int]
+fake.fake_fail.argtypes = [ctypes.c_char_p, ctypes.c_int]
+fake.fake_notes.restype = ctypes.c_char_p
+fake.fake_used.restype = fake.fake_allocs.restype = ctypes.c_size_t
+sys.path.insert(0, {root!r})
+import numpy as np
+from paper_2609_16361_amd import binding, inputs
+F32, F16 = binding.LBM_STORE_F32, binding.LBM_STORE_F16
+
+def notes(what=""):
+    "The calls noted since the last reset: (what, stream, thread, rest), of kind `what`."
+    out = []
+    for line in fake.fake_notes().decode().splitlines():
+        w, s, t, rest = line.split(" ", 3)
+        if not what or w == what:
+            out.append((w, int(s.split("=")[1], 16), int(t.split("=")[1]), rest))
+    return out
+
+def kernels():
+    "The launched kernels by name: k_step, k_step_pair, ..."
+    return [re.search(r"\\d(k_[a-z0-9_]+?)I?[LfD_]", n[3]).group(1) for n in notes("launch")]
+
+def value(rest, key):
+    return int(re.search(key + "=([0-9a-f]+)", rest).group(1), 16)
+
+def case(dims, **kw):
+    return inputs.random_smooth(*dims, seed=3, amp=0.03, **kw)
+
+def status(fn):
+    try:
+        fn()
+    except binding.LbmError as e:
+        return e.status
+    return 0
+
+fake.fake_reset(1 << 33)
+"""
+
+
+@pytest.fixture(scope="session")
+def run(tmp_path_factory):
+    lib = str(tmp_path_factory.mktemp("fake") / "libfake_hip.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    "-Wl,-soname,libamdhip64.so.7", os.path.join(HERE, "fake_hip.cpp"), "-o", lib, "-lpthread"],
+                   check=True)
+
+    def go(code):
+        prelude = PRELUDE.format(lib=lib, root=os.path.dirname(HERE))
+        r = subprocess.run([sys.executable, "-c", prelude + code], capture_output=True, text=True, timeout=300)
+        assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-4000:]
+
+    return go
+
+
+def test_copies_on_the_per_thread_stream_stay_in_the_callers_thread(run):
+    # handle 2 means another stream in every thread: what a worker enqueued there would
+    # not be ordered after the caller's kernels
+    run("""
+c = case((96, 64, 40))
+with binding.Solver(c.params, stream=2) as s, binding.Batch(1 << 26, stream=2) as b:
+    s.init(c.Q0)
+    s.step(3)
+    f, _ = s.populations()
+    s.moments()
+    s.set_populations(f, 3)
+    i = b.add(c.params, c.Q0, 5)
+    b.populations(i)
+    b.moments(i)
+assert len(notes("copy")) > 30
+assert all(t == 0 for _, _, t, _ in notes("copy"))
+fake.fake_reset(0)
+with binding.Solver(c.params) as s:  # on any other stream the workers share the copies
+    s.init(c.Q0)
+assert {t for _, _, t, _ in notes("copy")} == {0, 1, 2, 3}
+""")
