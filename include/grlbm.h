@@ -325,7 +325,8 @@ lbm_status lbm_batch_create(size_t arena_bytes, int32_t max_instances, int32_t m
 lbm_status lbm_batch_add(lbm_batch* b, const lbm_params* p, const double* Q, int64_t steps,
                          int32_t* id);
 
-/* Advance the batch by n >= 0 steps (asynchronous). */
+/* Advance the batch by n >= 0 steps (asynchronous).  On a stream under capture, and
+ * from then on, the steps are single. */
 lbm_status lbm_batch_run(lbm_batch* b, int64_t n);
 
 /* Steps an instance has completed and whether it has finished (both may be NULL). */

@@ -289,6 +289,7 @@ struct lbm_batch {
   grlbm::Spare spare;
   int32_t tube_lanes[kGroups] = {}, tube_steps[kGroups] = {};
   bool single_steps = false;  // lbm_batch_autotune times the single-step kernels
+  bool captured = false;      // a run has been captured by the caller
   // captured graphs of graph_steps steps, all single and fast, and what they hold
   struct Graph {
     hipGraphExec_t exec = nullptr;
@@ -606,7 +607,7 @@ lbm_status ready_graph(lbm_batch* b, bool fast) {
 int64_t fast_reach(const lbm_batch* b, int64_t clock) {
   bool any = false;
   for (int g = 0; g < kGroups; ++g) any |= b->runs[g][kPairTiles].count > 0 || b->runs[g][kWindows].count > 0;
-  if (!any || !b->spare.buf || b->single_steps) return 0;
+  if (!any || !b->spare.buf || b->single_steps || b->captured) return 0;
   int64_t reach = INT64_MAX;
   for (const HostInst& h : b->insts)
     if (h.live && h.how != kSingle && h.d.t_end > clock) reach = std::min(reach, h.d.t_end - clock);
@@ -622,6 +623,11 @@ lbm_status run_steps(lbm_batch* b, int64_t n) {
     b->graphs[1].exec = nullptr;
     b->dirty = true;
   }
+  // Under the caller's capture the steps are single: a launch kept in the caller's graph
+  // would name the second arena after it has been given up, and would step past the end
+  // of an instance when it is replayed.  Replays move the device's clock and not the
+  // host's, which fast runs rely on, so the steps stay single from then on.
+  if (n > 0 && grlbm::capturing(b->stream)) b->captured = true;
   lbm_status st = upload(b);
   if (st != LBM_OK) return st;
   if (active_groups(b) == 0 || n == 0) {

@@ -35,7 +35,11 @@ def notes(what=""):
 
 def kernels():
     "The launched kernels by name: k_step, k_step_pair, ..."
-    return [re.search(r"\\d(k_[a-z0-9_]+?)I?[LfD_]", n[3]).group(1) for n in notes("launch")]
+    out = []
+    for n in notes("launch"):
+        m = re.search(r"(\\d{{1,2}})(k_\\w+)", n[3])  # a mangled name: its length comes first
+        out.append(m.group(2)[:int(m.group(1))])
+    return out
 
 def value(rest, key):
     return int(re.search(key + "=([0-9a-f]+)", rest).group(1), 16)
@@ -89,4 +93,26 @@ fake.fake_reset(0)
 with binding.Solver(c.params) as s:  # on any other stream the workers share the copies
     s.init(c.Q0)
 assert {t for _, _, t, _ in notes("copy")} == {0, 1, 2, 3}
+""")
+
+
+def test_captured_batch_steps_are_single_and_stay_so(run):
+    # a graph of the caller's must not keep the second arena's address, which can be given
+    # up, nor passes of several steps, which check an instance's end once per pass
+    run("""
+with binding.Batch(1 << 26, graph_steps=64) as b:
+    for d, st in (((40, 36, 33), F32), ((300, 4, 4), F32), ((300, 4, 4), F16)):
+        c = case(d)
+        b.add(c.params, c.Q0, 1000, storage=st)
+    b.run(10)
+    assert {"k_batch_pair", "k_batch_tube"} <= set(kernels())
+    stream = notes("launch")[-1][1]
+    fake.fake_reset(0)
+    fake.fake_capture(stream, 1)
+    b.run(10)
+    assert set(kernels()) == {"k_batch_step", "k_batch_advance"}, set(kernels())
+    fake.fake_capture(stream, 0)
+    fake.fake_reset(0)
+    b.run(64)
+    assert set(kernels()) == {"k_batch_step", "k_batch_advance"}, set(kernels())
 """)
