@@ -678,7 +678,9 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n, int32_t diag_every) {
   // with the even step before it where that stores to the second buffer, are even in
   // number, so that the state is back in the context's own buffer.  Not with
   // a source or with the direct odd step asked for, and not under capture: a captured
-  // launch would keep the address of a buffer that may be given up later.
+  // launch would keep the address of a buffer that may be given up later.  Between its
+  // first launch and its last a run has no state to go on from (ready is off): where a
+  // launch in between fails, the context has to be set again.
   std::unique_lock<std::mutex> use_spare(c->spare.mu, std::defer_lock);
   bool passes = false;
   if (n >= 3 && !c->src && c->odd_lds && !c->single_steps && !grlbm::capturing(c->stream)) {
@@ -703,9 +705,11 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n, int32_t diag_every) {
         for (int64_t i = (m + 2 * c->tube.steps - 1) / (2 * c->tube.steps) * 2; i > 0; --i) {
           const int64_t two = left / i;
           HIP_TRY(grlbm::launch_tube(L, c->tube, c->cus, from, to, (int)(2 * two), t + m - 2 * left, c->stream));
+          c->ready = false;
           left -= two;
           std::swap(from, to);
         }
+        c->ready = true;
         c->step += m;
         s += m - 1;
         continue;
@@ -724,9 +728,11 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n, int32_t diag_every) {
         moved = false;
         for (int64_t i = 0; i < pairs; ++i) {
           HIP_TRY(grlbm::launch_pair(L, c->pair, from, to, c->stream));
+          c->ready = false;
           std::swap(from, to);
         }
         if (pairs > 0) {
+          c->ready = true;
           c->step += 2 * pairs;
           s += 2 * pairs - 1;
           continue;
@@ -744,6 +750,7 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n, int32_t diag_every) {
       L.partials = c->partials;
     }
     HIP_TRY(grlbm::launch_step(L, c->stream));
+    if (moved) c->ready = false;
     if (diag) {
       HIP_TRY(grlbm::launch_finalize(c->partials, grlbm::launch_blocks(L), c->ring + (size_t)c->ring_used * kDiagVals, c->stream));
       c->ring_steps.push_back(t);

@@ -290,6 +290,8 @@ struct lbm_batch {
   int32_t tube_lanes[kGroups] = {}, tube_steps[kGroups] = {};
   bool single_steps = false;  // lbm_batch_autotune times the single-step kernels
   bool captured = false;      // a run has been captured by the caller
+  bool lost = false;          // a launch failed inside a fast run
+  int64_t launches = 0;       // of step kernels, here or into a graph
   // captured graphs of graph_steps steps, all single and fast, and what they hold
   struct Graph {
     hipGraphExec_t exec = nullptr;
@@ -459,6 +461,13 @@ hipError_t for_group(int g, F fn) {
   }
 }
 
+// The last launch's error.
+hipError_t launched(lbm_batch* b) {
+  const hipError_t e = hipGetLastError();
+  if (e == hipSuccess) ++b->launches;
+  return e;
+}
+
 // One step of the tiles of a run of group g, in the arena.
 hipError_t launch_single(lbm_batch* b, int g, int run, int32_t j) {
   return for_group(g, [&](auto coll, auto zero) {
@@ -472,7 +481,7 @@ hipError_t launch_single(lbm_batch* b, int g, int run, int32_t j) {
       hipLaunchKernelGGL(kernel, dim3((unsigned)launch_grid(b, g, run)), dim3((unsigned)b->tune.block), lds, b->stream,
                          reinterpret_cast<T*>(b->arena), b->d_insts, b->d_tiles + (size_t)g * b->max_tiles,
                          b->d_runs + g * kRuns + run, b->d_clock, j);
-      return hipGetLastError();
+      return launched(b);
     };
     return b->tune.nontemporal ? go(grlbm::k_batch_step<C, T, true>) : go(grlbm::k_batch_step<C, T, false>);
   });
@@ -483,7 +492,7 @@ hipError_t launch_pairs(lbm_batch* b, int g, const void* from, void* to, int32_t
     hipLaunchKernelGGL(kernel, dim3((unsigned)rounded(b->runs[g][kPairTiles].count)), dim3(grlbm::kPairThreads),
                        grlbm::kPairLds, b->stream, (const char*)from, (char*)to, b->d_insts,
                        b->d_multi + (size_t)g * b->max_tiles, b->d_runs + g * kRuns + kPairTiles, b->d_clock, j);
-    return hipGetLastError();
+    return launched(b);
   };
   return g < 2 ? go(grlbm::k_batch_pair<0>) : go(grlbm::k_batch_pair<1>);
 }
@@ -499,7 +508,7 @@ hipError_t launch_tubes(lbm_batch* b, int g, const void* from, void* to, int32_t
                          grlbm::tube_lds(sh, rounded(count), b->num_cus), b->stream, (const char*)from, (char*)to,
                          b->d_insts, b->d_multi + (size_t)g * b->max_tiles, b->d_runs + g * kRuns + kWindows,
                          b->d_clock, j, steps);
-      return hipGetLastError();
+      return launched(b);
     };
     return sh.lanes == 256 ? go(grlbm::k_batch_tube<C, T, 256>) : go(grlbm::k_batch_tube<C, T, 512>);
   });
@@ -521,7 +530,8 @@ lbm_status enqueue_steps(lbm_batch* b, int32_t n) {
 
 // Enqueue n (even, >= 4) steps, several per pass where the instances can: tubes in an
 // even number of launches, the rest of FP32 as one step, pairs and the odd steps left.
-// The passes of each are even in number, so that all states end in the arena.
+// The passes of each are even in number, so that all states end in the arena; where one
+// cannot be launched, states are left between the two arenas.
 lbm_status enqueue_fast(lbm_batch* b, int32_t n) {
   for (int g = 0; g < kGroups; ++g) {
     const TileRun* runs = b->runs[g];
@@ -614,7 +624,13 @@ int64_t fast_reach(const lbm_batch* b, int64_t clock) {
   return reach;
 }
 
+lbm_status check_kept(const lbm_batch* b) {
+  return b->lost ? fail(LBM_ESTATE, "the batch's states were lost when a launch failed") : LBM_OK;
+}
+
 lbm_status run_steps(lbm_batch* b, int64_t n) {
+  lbm_status st = check_kept(b);
+  if (st != LBM_OK) return st;
   // the second arena stays where it is until everything that uses it is enqueued; where
   // it has been given up the lists and the graph that name it are made anew
   std::lock_guard<std::mutex> use(b->spare.mu);
@@ -628,7 +644,7 @@ lbm_status run_steps(lbm_batch* b, int64_t n) {
   // of an instance when it is replayed.  Replays move the device's clock and not the
   // host's, which fast runs rely on, so the steps stay single from then on.
   if (n > 0 && grlbm::capturing(b->stream)) b->captured = true;
-  lbm_status st = upload(b);
+  st = upload(b);
   if (st != LBM_OK) return st;
   if (active_groups(b) == 0 || n == 0) {
     // nothing to update: the clock still moves so instance windows stay consistent
@@ -653,7 +669,9 @@ lbm_status run_steps(lbm_batch* b, int64_t n) {
       HIP_TRY(hipGraphLaunch(b->graphs[fast ? 1 : 0].exec, b->stream));
     } else if (fast) {
       m = std::min(m, reach) / 2 * 2;
+      const int64_t before = b->launches;
       st = enqueue_fast(b, (int32_t)m);
+      b->lost = st != LBM_OK && b->launches != before;
     } else {
       st = enqueue_steps(b, (int32_t)m);
     }
@@ -876,6 +894,8 @@ lbm_status lbm_batch_moments(lbm_batch* b, int32_t id, double* Q_out) {
   lbm_status st = check_id(b, id);
   if (st != LBM_OK) return st;
   if (!Q_out) return fail(LBM_EINVAL, "Q_out is NULL");
+  st = check_kept(b);
+  if (st != LBM_OK) return st;
   const HostInst& h = b->insts[id];
   const int64_t N = (int64_t)h.p.nx * h.p.ny * h.p.nz;
   const int el = h.p.storage == LBM_STORE_F16 ? 2 : 4;
@@ -893,6 +913,8 @@ lbm_status lbm_batch_populations(lbm_batch* b, int32_t id, float* f_out, int64_t
   lbm_status st = check_id(b, id);
   if (st != LBM_OK) return st;
   if (!f_out) return fail(LBM_EINVAL, "f_out is NULL");
+  st = check_kept(b);
+  if (st != LBM_OK) return st;
   const HostInst& h = b->insts[id];
   const int64_t N = (int64_t)h.p.nx * h.p.ny * h.p.nz;
   const int el = h.p.storage == LBM_STORE_F16 ? 2 : 4;
@@ -912,6 +934,8 @@ lbm_status lbm_batch_nonfinite(lbm_batch* b, int32_t* ids, int32_t max, int32_t*
   if (!b || !count) return fail(LBM_EINVAL, "NULL argument");
   if (max < 0 || (max > 0 && !ids)) return fail(LBM_EINVAL, "bad id buffer (max %d)", max);
   *count = 0;
+  lbm_status st = check_kept(b);
+  if (st != LBM_OK) return st;
   std::vector<grlbm::CheckItem> items;
   std::vector<int32_t> which;  // flag index -> instance id
   for (int32_t id = 0; id < (int32_t)b->insts.size(); ++id) {

@@ -116,3 +116,38 @@ with binding.Batch(1 << 26, graph_steps=64) as b:
     b.run(64)
     assert set(kernels()) == {"k_batch_step", "k_batch_advance"}, set(kernels())
 """)
+
+
+@pytest.mark.parametrize("dims,kernel", [((40, 36, 33), b"k_step_pair"), ((300, 4, 4), b"k_step_tube")])
+@pytest.mark.parametrize("after", [0, 1, 2])
+def test_a_failed_pass_leaves_no_state_to_go_on_from(run, dims, kernel, after):
+    # 15 and 39 steps: an even step into the second buffer and seven pairs; four passes of
+    # a tube.  Only a tube's first pass leaves the state where it was.
+    run(f"""
+c = case({dims})
+with binding.Solver(c.params) as s:
+    s.init(c.Q0)
+    fake.fake_fail({kernel!r}, {after})
+    assert status(lambda: s.step(15 if {kernel!r} == b"k_step_pair" else 39)) == binding.LBM_EDEVICE
+    kept = {after} == 0 and {kernel!r} == b"k_step_tube"
+    for call in (lambda: s.step(1), s.moments, s.populations):
+        assert status(call) == (0 if kept else binding.LBM_ESTATE)
+    s.init(c.Q0)
+    s.step(39)
+    s.moments()
+""")
+
+
+@pytest.mark.parametrize("kernel,after,kept", [(b"k_batch_tube", 0, True), (b"k_batch_tube", 1, False),
+                                               (b"k_batch_pair", 0, False)])
+def test_a_failed_pass_ends_a_batch(run, kernel, after, kept):
+    run(f"""
+with binding.Batch(1 << 26, graph_steps=64) as b:
+    c = case((40, 36, 33) if {kernel!r} == b"k_batch_pair" else (300, 4, 4))
+    i = b.add(c.params, c.Q0, 1000)
+    fake.fake_fail({kernel!r}, {after})
+    assert status(lambda: b.run(30)) == binding.LBM_EDEVICE
+    for call in (lambda: b.run(1), lambda: b.moments(i), lambda: b.populations(i), b.nonfinite):
+        assert status(call) == (0 if {kept} else binding.LBM_ESTATE)
+    b.remove(i)
+""")
