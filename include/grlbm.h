@@ -158,7 +158,7 @@ lbm_status lbm_init_fields(lbm_ctx* ctx, const double* Q);
  * of two chosen here from the initial state (largest |value| mapped into
  * [32, 64), leaving 1024x headroom for populations that grow during the run),
  * which keeps the values in FP16's normal range; choosing it synchronises the
- * stream, and for states of 128 MiB or more the device.  The scale is invisible through this ABI. */
+ * stream.  The scale is invisible through this ABI. */
 lbm_status lbm_init_fields_device(lbm_ctx* ctx, const double* Q_dev);
 
 /* Enqueue n >= 0 collide-and-stream steps on the context's stream (asynchronous).

@@ -615,12 +615,6 @@ lbm_status lbm_set_source(lbm_ctx* c, const float* S_dev) {
 lbm_status lbm_init_fields_device(lbm_ctx* c, const double* Q_dev) {
   if (!c || !Q_dev) return fail(LBM_EINVAL, "ctx or Q is NULL");
   if (c->p.storage == LBM_STORE_F16) {
-    // An FP16 start waits for its stream anyway.  From half of the Infinity Cache on it
-    // waits for the device, so that solves in several contexts follow one another: two
-    // such states in turn drive each other out of the cache (three contexts of 128^3,
-    // 100 steps each: 5.45 ms a solve in turn, 5.73 interleaved; BGK 5.57 and 5.96), while
-    // smaller ones gain from running together (111^3 4.53 and 4.07, 64^3 2.32 and 1.48).
-    if (c->F_bytes >= (size_t(128) << 20) && hipDeviceSynchronize() != hipSuccess) (void)hipGetLastError();
     lbm_status st = grlbm::scales_from_fields(c->c, c->g, grlbm::make_init_coef(&c->p), Q_dev, c->N,
                                               scale_words(c), c->stream);
     if (st != LBM_OK) return st;

@@ -151,3 +151,17 @@ with binding.Batch(1 << 26, graph_steps=64) as b:
         assert status(call) == (0 if {kept} else binding.LBM_ESTATE)
     b.remove(i)
 """)
+
+
+def test_no_call_waits_for_the_device(run):
+    # other streams' work is none of a context's business, whatever the size of its state
+    run("""
+for storage, dims in ((F32, (128, 128, 72)), (F16, (128, 128, 130))):  # 165 and 149 MB of state
+    c = case(dims)
+    with binding.Solver(c.params, storage=storage) as s:
+        s.init(c.Q0)
+        s.step(5)
+        s.moments()
+assert binding.lbm_state_bytes(s.cparams) >= 128 << 20
+assert len(notes("sync")) > 4 and not notes("device-sync")
+""")
