@@ -165,3 +165,28 @@ for storage, dims in ((F32, (128, 128, 72)), (F16, (128, 128, 130))):  # 165 and
 assert binding.lbm_state_bytes(s.cparams) >= 128 << 20
 assert len(notes("sync")) > 4 and not notes("device-sync")
 """)
+
+
+def test_batch_runs_of_odd_length_upload_nothing_and_stay_fast(run):
+    run("""
+with binding.Batch(1 << 26, graph_steps=64) as b:
+    for d, st in (((40, 36, 33), F32), ((300, 4, 4), F32), ((300, 4, 4), F16), ((24, 24, 24), F16)):
+        c = case(d)
+        b.add(c.params, c.Q0, 1000, storage=st)
+    b.run(1)
+    fake.fake_reset(0)
+    for n in (1, 3, 7, 9, 1, 15):
+        b.run(n)
+    assert not notes("copy") and not notes("sync") and not notes("malloc")
+    fake.fake_reset(0)
+    b.run(9)  # from an odd step: one single step, then fast ones
+    assert kernels()[:3] == ["k_batch_step", "k_batch_step", "k_batch_advance"]  # a group each for FP32 and FP16
+    assert {"k_batch_pair", "k_batch_tube"} <= set(kernels())
+    # a later and smaller instance does not take the others out of fast runs
+    b.run(1)
+    c = case((50, 3, 3))
+    b.add(c.params, c.Q0, 1000)
+    fake.fake_reset(0)
+    b.run(21)
+    assert {"k_batch_pair", "k_batch_tube"} <= set(kernels())
+""")
