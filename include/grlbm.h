@@ -26,14 +26,16 @@
  * deviation f - w_i Q_ref from the equilibrium of a uniform reference state
  * (Sec. 2.2), Q_ref = (rho_ref, 0, 0, 0, E_ref).
  *
- * Several steps per pass.  A context also keeps a second buffer of the same size where
- * the card has room to spare (it stays at least half free, and these buffers together
- * below a quarter of it), if its grid gains from it: with FP32 storage lbm_step then
- * makes two steps per pass over memory, and on tubes (a cross-section of at most 25
- * cells, FP32 or FP16) up to ten, alternating between the two buffers and ending every
- * call in the first.  The results are bitwise those of single steps.  The second buffers
- * are given up when an allocation of this library fails, and the contexts go on in
- * single steps.
+ * Several steps per pass.  The first lbm_step that gains from it takes a second buffer of
+ * the same size where the card has room to spare (it stays at least half free, or the
+ * buffer takes at most an eighth of what is free, and these buffers together stay below
+ * a quarter of it).  With FP32 storage lbm_step then makes two steps per pass over
+ * memory, and on tubes (a cross-section of at most 25 cells, FP32 or FP16) up to ten,
+ * alternating between the two buffers and ending every call in the first.  The results
+ * are bitwise those of single steps.  The second buffers are given up when an allocation
+ * of this library fails, and the contexts go on in single steps.  Another allocator in
+ * the process cannot ask for them: lbm_set_passes declines a context's or gives it back,
+ * lbm_batch_set_passes a batch's.
  *
  * Threading.  A context is not internally locked: use one context per host thread
  * at a time.  lbm_last_error is thread-local.
@@ -214,6 +216,17 @@ lbm_status lbm_set_populations(lbm_ctx* ctx, const float* f, int64_t step);
 lbm_status lbm_set_launch(lbm_ctx* ctx, int32_t block, int32_t nontemporal, int32_t blocks_per_cu,
                           int32_t odd_lds);
 
+/* Several steps per pass off (0) or on (1, the default).  Off frees the second buffer after
+ * the work on the stream (EDEVICE where that failed, ESTATE on a stream under capture) and
+ * takes none again; all steps are single then.  On takes one with the next call that
+ * gains from it, also after it had been given up. */
+lbm_status lbm_set_passes(lbm_ctx* ctx, int32_t on);
+
+/* Steps that lbm_step has made with this context, the passes over the populations it
+ * took for them (as many, in single steps), and the bytes of the second buffer it holds
+ * now.  Each may be NULL. */
+lbm_status lbm_get_passes(lbm_ctx* ctx, int64_t* steps, int64_t* passes, size_t* second_bytes);
+
 /* A launch shape as lbm_set_launch takes it. */
 typedef struct {
   int32_t block, nontemporal, blocks_per_cu, odd_lds;
@@ -285,7 +298,7 @@ lbm_status lbm_step_noalloc(const lbm_params* p, void* F_dev, int64_t step, int6
  * added, advances with each lbm_batch_run step until it has made the number of
  * steps it was added with, then stays frozen until removed.  As in a context, tubes and
  * FP32 grids make several steps per pass where a second arena (of at most 4 GiB, for
- * the front of the first) could be had.  Results are bitwise
+ * the front of the first) could be had when the first such instance was added.  Results are bitwise
  * those of the same instance run alone in a context (lbm_create/lbm_step).  All
  * calls use the batch's stream; calls that touch host memory synchronise it. */
 typedef struct lbm_batch lbm_batch; /* opaque */
@@ -330,6 +343,13 @@ lbm_status lbm_batch_add(lbm_batch* b, const lbm_params* p, const double* Q, int
 /* Advance the batch by n >= 0 steps (asynchronous).  On a stream under capture, and
  * from then on, the steps are single. */
 lbm_status lbm_batch_run(lbm_batch* b, int64_t n);
+
+/* As lbm_set_passes, for a batch and its second arena. */
+lbm_status lbm_batch_set_passes(lbm_batch* b, int32_t on);
+
+/* Steps the batch has run, those of them in runs in which its tubes and FP32 grids made
+ * several per pass, and the bytes of the second arena it holds now.  Each may be NULL. */
+lbm_status lbm_batch_get_passes(lbm_batch* b, int64_t* steps, int64_t* fast_steps, size_t* second_bytes);
 
 /* Steps an instance has completed and whether it has finished (both may be NULL). */
 lbm_status lbm_batch_query(lbm_batch* b, int32_t id, int64_t* done_steps, int32_t* finished);

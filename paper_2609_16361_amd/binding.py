@@ -107,6 +107,8 @@ SIGNATURES = {
     "lbm_set_populations": (ctypes.c_int, [_vp, _P(ctypes.c_float), ctypes.c_int64]),
     "lbm_set_launch": (ctypes.c_int, [_vp, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32]),
     "lbm_get_launch": (ctypes.c_int, [_vp, _P(lbm_launch)]),
+    "lbm_set_passes": (ctypes.c_int, [_vp, ctypes.c_int32]),
+    "lbm_get_passes": (ctypes.c_int, [_vp, _P(ctypes.c_int64), _P(ctypes.c_int64), _P(ctypes.c_size_t)]),
     "lbm_autotune": (ctypes.c_int, [_vp, ctypes.c_int32, _P(lbm_launch), _P(ctypes.c_float), _P(lbm_launch),
                                     _P(ctypes.c_float), ctypes.c_int32, _P(ctypes.c_int32)]),
     "lbm_set_source": (ctypes.c_int, [_vp, _vp]),
@@ -123,6 +125,8 @@ SIGNATURES = {
     "lbm_batch_add": (ctypes.c_int, [_vp, _P(lbm_params), _P(ctypes.c_double), ctypes.c_int64,
                                      _P(ctypes.c_int32)]),
     "lbm_batch_run": (ctypes.c_int, [_vp, ctypes.c_int64]),
+    "lbm_batch_set_passes": (ctypes.c_int, [_vp, ctypes.c_int32]),
+    "lbm_batch_get_passes": (ctypes.c_int, [_vp, _P(ctypes.c_int64), _P(ctypes.c_int64), _P(ctypes.c_size_t)]),
     "lbm_batch_query": (ctypes.c_int, [_vp, ctypes.c_int32, _P(ctypes.c_int64), _P(ctypes.c_int32)]),
     "lbm_batch_moments": (ctypes.c_int, [_vp, ctypes.c_int32, _P(ctypes.c_double)]),
     "lbm_batch_populations": (ctypes.c_int, [_vp, ctypes.c_int32, _P(ctypes.c_float), _P(ctypes.c_int64)]),
@@ -273,6 +277,19 @@ def lbm_set_launch(ctx: int, block: int, nontemporal: bool, blocks_per_cu: int =
            "lbm_set_launch")
 
 
+def lbm_set_passes(ctx: int, on: bool) -> None:
+    """Several steps per pass, and the second buffer they need, on or off."""
+    _check(load().lbm_set_passes(ctx, int(bool(on))), "lbm_set_passes")
+
+
+def lbm_get_passes(ctx: int) -> dict:
+    """Steps made, the passes over memory they took, and the bytes of the second buffer."""
+    steps, passes, held = ctypes.c_int64(0), ctypes.c_int64(0), ctypes.c_size_t(0)
+    _check(load().lbm_get_passes(ctx, ctypes.byref(steps), ctypes.byref(passes), ctypes.byref(held)),
+           "lbm_get_passes")
+    return dict(steps=steps.value, passes=passes.value, second_bytes=held.value)
+
+
 def lbm_get_step(ctx: int) -> int:
     s = ctypes.c_int64(0)
     _check(load().lbm_get_step(ctx, ctypes.byref(s)), "lbm_get_step")
@@ -339,7 +356,7 @@ class Solver:
 
     def __init__(self, params: dict, stream: int | None = None, storage: int | None = None,
                  block: int | None = None, nontemporal: bool | None = None, layout_pad: int = 0,
-                 blocks_per_cu: int | None = None, odd_lds: bool = True):
+                 blocks_per_cu: int | None = None, odd_lds: bool = True, passes: bool = True):
         self.params = dict(params)
         self.cparams = make_params(params, storage=storage, layout_pad=layout_pad)
         self.shape = (self.cparams.nz, self.cparams.ny, self.cparams.nx)
@@ -350,6 +367,8 @@ class Solver:
             lbm_set_launch(self.ctx, d["block"] if block is None else block,
                            d["nontemporal"] if nontemporal is None else bool(nontemporal),
                            d["blocks_per_cu"] if blocks_per_cu is None else blocks_per_cu, odd_lds)
+        if not passes:
+            lbm_set_passes(self.ctx, False)
 
     def init(self, Q):
         lbm_init_fields(self.ctx, np.asarray(Q, dtype=np.float64).reshape((5,) + self.shape))
@@ -366,6 +385,12 @@ class Solver:
 
     def launch(self):
         return lbm_get_launch(self.ctx)
+
+    def set_passes(self, on):
+        lbm_set_passes(self.ctx, on)
+
+    def passes(self):
+        return lbm_get_passes(self.ctx)
 
     def moments(self):
         return lbm_moments(self.ctx, self.shape)
@@ -420,6 +445,18 @@ def lbm_batch_add(batch: int, params: lbm_params, Q: np.ndarray, steps: int) -> 
 
 def lbm_batch_run(batch: int, n: int) -> None:
     _check(load().lbm_batch_run(batch, int(n)), "lbm_batch_run")
+
+
+def lbm_batch_set_passes(batch: int, on: bool) -> None:
+    _check(load().lbm_batch_set_passes(batch, int(bool(on))), "lbm_batch_set_passes")
+
+
+def lbm_batch_get_passes(batch: int) -> dict:
+    """Steps run, those of them in fast runs, and the bytes of the second arena."""
+    steps, fast, held = ctypes.c_int64(0), ctypes.c_int64(0), ctypes.c_size_t(0)
+    _check(load().lbm_batch_get_passes(batch, ctypes.byref(steps), ctypes.byref(fast), ctypes.byref(held)),
+           "lbm_batch_get_passes")
+    return dict(steps=steps.value, fast_steps=fast.value, second_bytes=held.value)
 
 
 def lbm_batch_query(batch: int, inst: int):
@@ -489,9 +526,11 @@ class Batch:
     """Owns one lbm_batch; instances are added from parameter dicts."""
 
     def __init__(self, arena_bytes: int, max_instances: int = 1024, max_tiles: int = 1 << 20,
-                 graph_steps: int = 16, stream: int | None = None):
+                 graph_steps: int = 16, stream: int | None = None, passes: bool = True):
         self.h = lbm_batch_create(arena_bytes, max_instances, max_tiles, graph_steps, stream)
         self.shapes = {}
+        if not passes:
+            lbm_batch_set_passes(self.h, False)
 
     def add(self, params: dict, Q, steps: int, storage: int | None = None) -> int:
         p = make_params(params, storage=storage)
@@ -501,6 +540,12 @@ class Batch:
 
     def run(self, n: int) -> None:
         lbm_batch_run(self.h, n)
+
+    def set_passes(self, on: bool) -> None:
+        lbm_batch_set_passes(self.h, on)
+
+    def passes(self) -> dict:
+        return lbm_batch_get_passes(self.h)
 
     def query(self, i: int):
         return lbm_batch_query(self.h, i)

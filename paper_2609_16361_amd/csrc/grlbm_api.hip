@@ -200,19 +200,30 @@ bool capturing(hipStream_t s) {
   return hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone;
 }
 
-static std::mutex g_spare_mu;           // taken before any Spare::mu
-static std::vector<Spare*> g_spares;    // those that hold a buffer
-static size_t g_spare_bytes = 0;
+static std::mutex g_spare_mu;      // taken before any Spare::mu
+static Spare* g_spares = nullptr;  // those that hold a buffer
+
+// In a step's enqueueing: an allocation there must not break a capture that another
+// thread, or this one, has going on another stream.
+struct RelaxedCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
 
 void take_spare(Spare& s, size_t bytes) {
-  size_t free_bytes = 0, total = 0;
+  if (s.off || s.asked) return;
+  s.asked = true;
+  size_t free_bytes = 0, total = 0, held = 0;
+  const RelaxedCapture relaxed;
   std::lock_guard<std::mutex> lock(g_spare_mu);
   if (hipMemGetInfo(&free_bytes, &total) != hipSuccess) {
     (void)hipGetLastError();
     return;
   }
-  if (bytes > free_bytes || g_spare_bytes + bytes > total / 4 ||
-      (free_bytes - bytes < total / 2 && bytes > free_bytes / 8))
+  for (const Spare* o = g_spares; o; o = o->next)
+    if (o->device == s.device) held += o->bytes;
+  if (bytes > free_bytes || held + bytes > total / 4 || (free_bytes - bytes < total / 2 && bytes > free_bytes / 8))
     return;
   void* b = nullptr;
   if (hipMalloc(&b, bytes) != hipSuccess) {
@@ -221,15 +232,16 @@ void take_spare(Spare& s, size_t bytes) {
   }
   s.buf = b;
   s.bytes = bytes;
-  g_spare_bytes += bytes;
-  g_spares.push_back(&s);
+  s.next = g_spares;
+  g_spares = &s;
 }
 
 static void drop_spare_locked(Spare& s) {
   (void)hipFree(s.buf);
   s.buf = nullptr;
-  g_spare_bytes -= s.bytes;
-  g_spares.erase(std::find(g_spares.begin(), g_spares.end(), &s));
+  Spare** at = &g_spares;
+  while (*at != &s) at = &(*at)->next;
+  *at = s.next;
 }
 
 void drop_spare(Spare& s) {
@@ -237,16 +249,30 @@ void drop_spare(Spare& s) {
   if (s.buf) drop_spare_locked(s);
 }
 
+lbm_status switch_spare(Spare& s, bool on) {
+  if (!on && s.buf) {
+    if (capturing(s.stream)) return fail(LBM_ESTATE, "the stream is being captured");
+    HIP_TRY(hipStreamSynchronize(s.stream));
+    drop_spare(s);
+  }
+  s.off = !on;
+  s.asked = false;
+  return LBM_OK;
+}
+
 static bool give_up_spares() {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return false;
   std::lock_guard<std::mutex> lock(g_spare_mu);
-  const std::vector<Spare*> all = g_spares;
   bool any = false;
-  for (Spare* s : all) {
+  for (Spare *s = g_spares, *next; s; s = next) {
+    next = s->next;
     if (s->device != dev) continue;
     std::lock_guard<std::mutex> use(s->mu);
-    if (capturing(s->stream) || hipStreamSynchronize(s->stream) != hipSuccess) continue;
+    // from here hipStreamPerThread is not the owner's stream
+    if (capturing(s->stream) || (s->stream == hipStreamPerThread ? hipDeviceSynchronize()
+                                                                 : hipStreamSynchronize(s->stream)) != hipSuccess)
+      continue;
     drop_spare_locked(*s);
     any = true;
   }
@@ -332,6 +358,8 @@ struct lbm_ctx {
   // several steps per pass: the second population buffer, the tube's windows
   // (launch_tube) or else the grid's tiles (launch_pair)
   grlbm::Spare spare;
+  bool multi = false;  // the grid gains from several steps per pass
+  int64_t steps_made = 0, passes_made = 0;
   int cus = 0;
   grlbm::TubeShape tube{};
   grlbm::PairTiles pair{};
@@ -460,7 +488,7 @@ lbm_status create_common(const lbm_params* p, void* buf, size_t bytes, void* str
   c->ring_steps.reserve(kRingCap);
   c->spare.device = c->device;
   c->spare.stream = c->stream;
-  if (plan_passes(c)) grlbm::take_spare(c->spare, c->F_bytes);
+  c->multi = plan_passes(c);
   *out = c;
   return LBM_OK;
 }
@@ -500,6 +528,21 @@ lbm_status lbm_set_launch(lbm_ctx* c, int32_t block, int32_t nontemporal, int32_
   c->odd_lds = odd_lds != 0;
   c->bpc = blocks_per_cu;
   c->lds = lds_for_blocks_per_cu(blocks_per_cu);
+  return LBM_OK;
+}
+
+lbm_status lbm_set_passes(lbm_ctx* c, int32_t on) {
+  if (!c) return fail(LBM_EINVAL, "ctx is NULL");
+  if (on != 0 && on != 1) return fail(LBM_EINVAL, "on = %d must be 0 or 1", on);
+  return grlbm::switch_spare(c->spare, on != 0);
+}
+
+lbm_status lbm_get_passes(lbm_ctx* c, int64_t* steps, int64_t* passes, size_t* second_bytes) {
+  if (!c) return fail(LBM_EINVAL, "ctx is NULL");
+  if (steps) *steps = c->steps_made;
+  if (passes) *passes = c->passes_made;
+  std::lock_guard<std::mutex> use(c->spare.mu);
+  if (second_bytes) *second_bytes = c->spare.buf ? c->spare.bytes : 0;
   return LBM_OK;
 }
 
@@ -677,7 +720,8 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n, int32_t diag_every) {
   // launch in between fails, the context has to be set again.
   std::unique_lock<std::mutex> use_spare(c->spare.mu, std::defer_lock);
   bool passes = false;
-  if (n >= 3 && !c->src && c->odd_lds && !c->single_steps && !grlbm::capturing(c->stream)) {
+  if (n >= 3 && (diag_every == 0 || diag_every >= 3) && c->multi && !c->src && c->odd_lds && !c->single_steps && !grlbm::capturing(c->stream)) {
+    grlbm::take_spare(c->spare, c->F_bytes);
     use_spare.lock();
     passes = c->spare.buf != nullptr;
   }
@@ -700,10 +744,12 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n, int32_t diag_every) {
           const int64_t two = left / i;
           HIP_TRY(grlbm::launch_tube(L, c->tube, c->cus, from, to, (int)(2 * two), t + m - 2 * left, c->stream));
           c->ready = false;
+          ++c->passes_made;
           left -= two;
           std::swap(from, to);
         }
         c->ready = true;
+        c->steps_made += m;
         c->step += m;
         s += m - 1;
         continue;
@@ -727,6 +773,8 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n, int32_t diag_every) {
         }
         if (pairs > 0) {
           c->ready = true;
+          c->steps_made += 2 * pairs;
+          c->passes_made += pairs;
           c->step += 2 * pairs;
           s += 2 * pairs - 1;
           continue;
@@ -745,6 +793,8 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n, int32_t diag_every) {
     }
     HIP_TRY(grlbm::launch_step(L, c->stream));
     if (moved) c->ready = false;
+    ++c->steps_made;
+    ++c->passes_made;
     if (diag) {
       HIP_TRY(grlbm::launch_finalize(c->partials, grlbm::launch_blocks(L), c->ring + (size_t)c->ring_used * kDiagVals, c->stream));
       c->ring_steps.push_back(t);

@@ -292,6 +292,7 @@ struct lbm_batch {
   bool single_steps = false;  // lbm_batch_autotune times the single-step kernels
   bool captured = false;      // a run has been captured by the caller
   bool lost = false;          // a launch failed inside a fast run
+  int64_t fast_steps = 0;     // steps of fast runs
   int64_t launches = 0;       // of step kernels, here or into a graph
   // captured graphs of graph_steps steps, all single and fast, and what they hold
   struct Graph {
@@ -307,6 +308,14 @@ int64_t inst_tiles(const lbm_params* p, int block) {
   return (n + block - 1) / block;
 }
 
+// How an instance that the second arena reaches steps in fast runs.
+int fast_way(const lbm_params& p, const grlbm::Grid& g) {
+  if ((int64_t)p.ny * p.nz <= grlbm::kTubeCross) return kWindows;
+  return p.storage != LBM_STORE_F16 && g.S < (int64_t(1) << 29) && grlbm::pair_worth(g) ? kPaired : kSingle;
+}
+
+size_t spare_bytes(const lbm_batch* b) { return std::min(b->arena_bytes, kSpareArena); }
+
 // Chooses how each live instance makes its steps in fast runs.  Tubes and FP32 grids do
 // several per pass if they lie in reach of the second arena and at the same parity as
 // most of them (by cells): a fast run starts with all of them at an even step.
@@ -317,9 +326,9 @@ void plan_passes(lbm_batch* b) {
   if (!b->spare.buf) return;
   const auto way = [&](const HostInst& h) {
     const bool f16 = h.p.storage == LBM_STORE_F16;
-    if (!h.live || h.d.t_end <= b->clock || (size_t)h.d.off * (f16 ? 2 : 4) + h.bytes > b->spare.bytes) return kSingle;
-    if ((int64_t)h.p.ny * h.p.nz <= grlbm::kTubeCross) return kWindows;
-    return !f16 && h.d.g.S < (int64_t(1) << 29) && grlbm::pair_worth(h.d.g) ? kPaired : kSingle;
+    if (!h.live || h.d.t_end <= b->clock || (size_t)h.d.off * (f16 ? 2 : 4) + h.bytes > b->spare.bytes)
+      return (int)kSingle;
+    return fast_way(h.p, h.d.g);
   };
   const auto cells_of = [](const HostInst& h) { return (double)h.p.nx * h.p.ny * h.p.nz; };
   const auto odd_now = [&](const HostInst& h) { return ((b->clock - h.d.t_start) & 1) != 0; };
@@ -642,6 +651,9 @@ lbm_status check_kept(const lbm_batch* b) {
 lbm_status run_steps(lbm_batch* b, int64_t n) {
   lbm_status st = check_kept(b);
   if (st != LBM_OK) return st;
+  if (b->dirty && !b->spare.asked && !grlbm::capturing(b->stream))
+    for (const HostInst& h : b->insts)
+      if (h.live && fast_way(h.p, h.d.g) != kSingle) grlbm::take_spare(b->spare, spare_bytes(b));
   // the second arena stays where it is until everything that uses it is enqueued; where
   // it has been given up the lists and the graph that name it are made anew
   std::lock_guard<std::mutex> use(b->spare.mu);
@@ -694,6 +706,7 @@ lbm_status run_steps(lbm_batch* b, int64_t n) {
       st = enqueue_steps(b, (int32_t)m);
     }
     if (st != LBM_OK) return st;
+    if (fast) b->fast_steps += m;
     if (m % 2 != 0) b->odd = !b->odd;
     left -= m;
   }
@@ -811,10 +824,8 @@ lbm_status lbm_batch_create(size_t arena_bytes, int32_t max_instances, int32_t m
   b->tune.nontemporal = 0;
   b->tune.blocks_per_cu = 2;
   b->tune.grid = 0;
-  // a second arena for what lies at the front of the first, where instances go first
   b->spare.device = dev;
   b->spare.stream = b->stream;
-  grlbm::take_spare(b->spare, std::min(b->arena_bytes, kSpareArena));
   *out = b;
   return LBM_OK;
 }
@@ -862,6 +873,9 @@ lbm_status lbm_batch_add(lbm_batch* b, const lbm_params* p, const double* Q, int
   h.d.cells = (int32_t)grlbm::row_cells(h.d.g);
   h.d.inv_px = 1.0 / h.d.g.px;
   h.d.inv_ny = 1.0 / p->ny;
+  // a second arena for what lies at the front of the first, where instances go first; the
+  // first instance that can use it brings it, and its fields are staged there
+  if (fast_way(h.p, h.d.g) != kSingle) grlbm::take_spare(b->spare, spare_bytes(b));
   const size_t field_bytes = sizeof(double) * 5 * (size_t)N;
   grlbm::Scratch dq(b->spare, field_bytes);
   if (!dq.p) {
@@ -896,6 +910,25 @@ lbm_status lbm_batch_run(lbm_batch* b, int64_t n) {
   if (!b) return fail(LBM_EINVAL, "batch is NULL");
   if (n < 0) return fail(LBM_EINVAL, "n < 0");
   return run_steps(b, n);
+}
+
+lbm_status lbm_batch_set_passes(lbm_batch* b, int32_t on) {
+  if (!b) return fail(LBM_EINVAL, "batch is NULL");
+  if (on != 0 && on != 1) return fail(LBM_EINVAL, "on = %d must be 0 or 1", on);
+  lbm_status st = grlbm::switch_spare(b->spare, on != 0);
+  if (st != LBM_OK) return st;
+  drop_graphs(b);  // one names the second arena
+  b->dirty = true;
+  return LBM_OK;
+}
+
+lbm_status lbm_batch_get_passes(lbm_batch* b, int64_t* steps, int64_t* fast_steps, size_t* second_bytes) {
+  if (!b) return fail(LBM_EINVAL, "batch is NULL");
+  if (steps) *steps = b->clock;
+  if (fast_steps) *fast_steps = b->fast_steps;
+  std::lock_guard<std::mutex> use(b->spare.mu);
+  if (second_bytes) *second_bytes = b->spare.buf ? b->spare.bytes : 0;
+  return LBM_OK;
 }
 
 lbm_status lbm_batch_query(lbm_batch* b, int32_t id, int64_t* done_steps, int32_t* finished) {

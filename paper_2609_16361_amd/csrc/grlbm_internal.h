@@ -28,12 +28,19 @@ struct Spare {
   size_t bytes = 0;
   int device = 0;
   hipStream_t stream = nullptr;
+  bool off = false;       // its owner declines one (lbm_set_passes)
+  bool asked = false;     // one has been asked for, and is not again
+  Spare* next = nullptr;  // in the list of those that hold a buffer
 };
-// Takes a buffer for s (device and stream are set) if the card has room to spare: at
-// least half of it stays free or the buffer is at most an eighth of what is free, and
-// all second buffers together stay below a quarter of the card.
+// Called by the owner, without mu, before the first work that uses a buffer: takes one
+// for s (device and stream are set) if the card has room to spare: at least half of it
+// stays free or the buffer is at most an eighth of what is free, and all second buffers
+// on it together stay below a quarter of the card.
 void take_spare(Spare& s, size_t bytes);
 void drop_spare(Spare& s);  // frees it, if s has one; its owner's work is done
+// The owner declines a buffer, and frees the one it has after the work on its stream, or
+// takes one again.
+lbm_status switch_spare(Spare& s, bool on);
 bool capturing(hipStream_t s);
 // Copies between host and device memory in order with the work on s; they return when
 // the copy is done.  copy_users counts the contexts and batches, for which pinned slots

@@ -139,7 +139,10 @@ class Server:
         # state is allocated by the factory, outside the batch's arena, and counts
         # against the same byte budget and cell cap: the device must hold the arena
         # and the solo states together (the benchmark's cell cap of 8 Mi cells keeps
-        # them below 1.2 GB beside its 200 GB arena).
+        # them below 1.2 GB beside its 200 GB arena).  The second buffers that solo
+        # contexts and the batch step with (as much again for the solo states, at most
+        # 4 GiB for the batch) are not counted: the library takes them from memory to
+        # spare only and gives them up when one of its allocations needs the room.
         self.solo_factory = solo_factory
         self.solo_min = solo_min_bytes if solo_factory is not None else None
         self.stop_diverged = bool(stop_diverged)

@@ -190,3 +190,126 @@ with binding.Batch(1 << 26, graph_steps=64) as b:
     b.run(21)
     assert {"k_batch_pair", "k_batch_tube"} <= set(kernels())
 """)
+
+
+def test_second_buffers_are_taken_by_the_first_steps_that_use_them(run):
+    run("""
+grid, tube = case((40, 36, 33)), case((300, 4, 4))
+S = ctypes.create_string_buffer(5 * 4 * grid.cells)
+def held(s):
+    return s.passes()["second_bytes"]
+with binding.Solver(grid.params) as s:
+    n = fake.fake_allocs()
+    assert n == 2 and held(s) == 0  # the populations and the diagnostic ring
+    s.init(grid.Q0)
+    s.step(2)
+    s.step(40, 1)
+    s.step(40, 2)
+    s.set_source(ctypes.addressof(S))
+    s.step(8)
+    s.set_source(None)
+    stream = notes("launch")[-1][1]
+    fake.fake_capture(stream, 1)
+    s.step(8)
+    fake.fake_capture(stream, 0)
+    s.autotune(4)
+    assert held(s) == 0 and s.passes()["passes"] == s.passes()["steps"]
+    before = s.passes()
+    s.step(9)
+    assert held(s) == binding.lbm_state_bytes(s.cparams)
+    after = s.passes()
+    assert after["steps"] - before["steps"] == 9 and after["passes"] - before["passes"] == 5
+for kw in (dict(odd_lds=False), dict(passes=False), dict(storage=F16)):
+    with binding.Solver(grid.params, **kw) as s:
+        s.init(grid.Q0)
+        s.step(20)
+        assert held(s) == 0 and s.passes() == dict(steps=20, passes=20, second_bytes=0)
+with binding.Batch(1 << 26) as b:
+    b.add(grid.params, grid.Q0, 100, storage=F16)
+    b.run(20)
+    assert b.passes() == dict(steps=20, fast_steps=0, second_bytes=0)
+    b.add(tube.params, tube.Q0, 100, storage=F16)
+    b.run(20)
+    assert b.passes() == dict(steps=40, fast_steps=20, second_bytes=1 << 26)
+assert fake.fake_used() == 0
+""")
+
+
+def test_second_buffers_can_be_declined_and_given_back(run):
+    run("""
+c = case((40, 36, 33))
+with binding.Solver(c.params) as s, binding.Batch(1 << 26) as b:
+    s.init(c.Q0)
+    i = b.add(c.params, c.Q0, 1000)
+    own = fake.fake_used()
+    for _ in range(2):
+        s.step(21)
+        b.run(20)
+        full = fake.fake_used()
+        assert s.passes()["second_bytes"] > 0 and b.passes()["second_bytes"] == 1 << 26
+        s.set_passes(False)
+        b.set_passes(False)
+        assert fake.fake_used() == full - binding.lbm_state_bytes(s.cparams) - (1 << 26)
+        fake.fake_reset(0)
+        s.step(21)
+        b.run(20)
+        s.moments()
+        b.moments(i)
+        assert not {"k_step_pair", "k_step_even_to", "k_batch_pair"} & set(kernels())
+        assert s.passes()["second_bytes"] == b.passes()["second_bytes"] == 0
+        s.set_passes(True)
+        b.set_passes(True)
+    assert status(lambda: binding._check(binding.load().lbm_set_passes(s.ctx, 2), "")) == binding.LBM_EINVAL
+assert fake.fake_used() == 0
+""")
+
+
+def test_taking_a_second_buffer_breaks_no_capture(run):
+    run("""
+c = case((40, 36, 33))
+with binding.Solver(c.params) as s:
+    s.init(c.Q0)
+    fake.fake_capture(0x777, 1)  # another stream's, in global mode
+    s.step(9)
+    fake.fake_capture(0x777, 0)
+    assert s.passes()["second_bytes"] > 0 and not notes("BROKEN-CAPTURE")
+""")
+
+
+def test_second_buffers_go_to_allocations_from_any_thread(run):
+    # one thread steps and reads out while the other's contexts need the room: each buffer
+    # goes after a wait for its owner's stream, and no step uses it after that
+    run("""
+fake.fake_reset(520 << 20)
+c, big = case((64, 64, 64)), case((96, 96, 96))
+stop = threading.Event()
+errors = []
+with binding.Solver(c.params) as s:
+    s.init(c.Q0)
+    s.step(9)
+    second = [value(n[3], "p") for n in notes("malloc") if value(n[3], "bytes") == s.passes()["second_bytes"]][-1]
+    def work():
+        try:
+            while not stop.is_set():
+                s.step(9)
+                s.moments()
+        except Exception as e:
+            errors.append(e)
+    t = threading.Thread(target=work)
+    t.start()
+    others = [binding.Solver(big.params) for _ in range(4)]  # 4 x 118 MiB beside 35 + 35
+    stop.set()
+    t.join()
+    assert not errors and s.passes()["second_bytes"] == 0
+    log = notes()
+    freed = max(i for i, n in enumerate(log) if n[0] == "free" and value(n[3], "p") == second)
+    stream = [n for n in log if n[0] == "launch"][0][1]
+    waits = [i for i, n in enumerate(log) if n[0] == "sync" and n[1] == stream and n[2] == 0 and i < freed]
+    assert waits
+    last = max(waits)
+    for n in log[last:]:
+        assert n[0] != "launch" or second not in (value(n[3], "a0"), value(n[3], "a1"))
+    for o in others:
+        o.close()
+assert fake.fake_used() == 0
+""")
