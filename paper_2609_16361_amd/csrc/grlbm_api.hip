@@ -268,7 +268,7 @@ static bool give_up_spares() {
   for (Spare *s = g_spares, *next; s; s = next) {
     next = s->next;
     if (s->device != dev) continue;
-    std::lock_guard<std::mutex> use(s->mu);
+    const std::unique_lock<std::mutex> use = s->hold();
     // from here hipStreamPerThread is not the owner's stream
     if (capturing(s->stream) || (s->stream == hipStreamPerThread ? hipDeviceSynchronize()
                                                                  : hipStreamSynchronize(s->stream)) != hipSuccess)
@@ -288,7 +288,7 @@ hipError_t dev_malloc(void** p, size_t bytes) {
   return e;
 }
 
-Scratch::Scratch(Spare& spare, size_t bytes) : lock(spare.mu) {
+Scratch::Scratch(Spare& spare, size_t bytes) : lock(spare.hold()) {
   if (spare.buf && bytes <= spare.bytes) {
     p = spare.buf;
     return;
@@ -541,7 +541,7 @@ lbm_status lbm_get_passes(lbm_ctx* c, int64_t* steps, int64_t* passes, size_t* s
   if (!c) return fail(LBM_EINVAL, "ctx is NULL");
   if (steps) *steps = c->steps_made;
   if (passes) *passes = c->passes_made;
-  std::lock_guard<std::mutex> use(c->spare.mu);
+  const std::unique_lock<std::mutex> use = c->spare.hold();
   if (second_bytes) *second_bytes = c->spare.buf ? c->spare.bytes : 0;
   return LBM_OK;
 }
@@ -718,11 +718,11 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n, int32_t diag_every) {
   // launch would keep the address of a buffer that may be given up later.  Between its
   // first launch and its last a run has no state to go on from (ready is off): where a
   // launch in between fails, the context has to be set again.
-  std::unique_lock<std::mutex> use_spare(c->spare.mu, std::defer_lock);
+  std::unique_lock<std::mutex> use_spare;
   bool passes = false;
   if (n >= 3 && (diag_every == 0 || diag_every >= 3) && c->multi && !c->src && c->odd_lds && !c->single_steps && !grlbm::capturing(c->stream)) {
     grlbm::take_spare(c->spare, c->F_bytes);
-    use_spare.lock();
+    use_spare = c->spare.hold();
     passes = c->spare.buf != nullptr;
   }
   // Steps from t up to the next one with diagnostics, t itself left out of account.

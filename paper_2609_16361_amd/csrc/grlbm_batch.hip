@@ -656,7 +656,7 @@ lbm_status run_steps(lbm_batch* b, int64_t n) {
       if (h.live && fast_way(h.p, h.d.g) != kSingle) grlbm::take_spare(b->spare, spare_bytes(b));
   // the second arena stays where it is until everything that uses it is enqueued; where
   // it has been given up the lists and the graph that name it are made anew
-  std::lock_guard<std::mutex> use(b->spare.mu);
+  const std::unique_lock<std::mutex> use = b->spare.hold();
   if (b->graphs[1].exec && !b->spare.buf) {
     (void)hipGraphExecDestroy(b->graphs[1].exec);
     b->graphs[1].exec = nullptr;
@@ -926,7 +926,7 @@ lbm_status lbm_batch_get_passes(lbm_batch* b, int64_t* steps, int64_t* fast_step
   if (!b) return fail(LBM_EINVAL, "batch is NULL");
   if (steps) *steps = b->clock;
   if (fast_steps) *fast_steps = b->fast_steps;
-  std::lock_guard<std::mutex> use(b->spare.mu);
+  const std::unique_lock<std::mutex> use = b->spare.hold();
   if (second_bytes) *second_bytes = b->spare.buf ? b->spare.bytes : 0;
   return LBM_OK;
 }

@@ -23,7 +23,7 @@ lbm_status validate(const lbm_params* p);
 // The second population buffer of a context or a batch: workspace, without which its
 // owner makes one step per pass.  The owner uses it with mu held, in work on its stream.
 struct Spare {
-  std::mutex mu;
+  std::mutex mu, turn;
   void* buf = nullptr;
   size_t bytes = 0;
   int device = 0;
@@ -31,6 +31,12 @@ struct Spare {
   bool off = false;       // its owner declines one (lbm_set_passes)
   bool asked = false;     // one has been asked for, and is not again
   Spare* next = nullptr;  // in the list of those that hold a buffer
+  // mu, in turn: an owner that steps without a pause does not keep out an allocation that
+  // needs its buffer
+  std::unique_lock<std::mutex> hold() {
+    std::lock_guard<std::mutex> first(turn);
+    return std::unique_lock<std::mutex>(mu);
+  }
 };
 // Called by the owner, without mu, before the first work that uses a buffer: takes one
 // for s (device and stream are set) if the card has room to spare: at least half of it
