@@ -134,8 +134,19 @@ hipError_t move_chunks(char* dev, char* host, size_t bytes, bool out, hipStream_
   return e;
 }
 
+// Memory that the runtime knows (pinned, managed, another device's): it moves that itself,
+// without a copy by the host.
+bool known(const void* host) {
+  hipPointerAttribute_t a{};
+  if (hipPointerGetAttributes(&a, host) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return a.type != hipMemoryTypeUnregistered;
+}
+
 hipError_t copy(void* dev, void* host, size_t bytes, bool out, hipStream_t s) {
-  if (bytes < kThreadedBytes) {
+  if (bytes < kThreadedBytes || known(host)) {
     const hipError_t e = out ? hipMemcpyAsync(host, dev, bytes, hipMemcpyDeviceToHost, s)
                              : hipMemcpyAsync(dev, host, bytes, hipMemcpyHostToDevice, s);
     return e == hipSuccess ? hipStreamSynchronize(s) : e;

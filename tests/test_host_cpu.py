@@ -315,3 +315,24 @@ with binding.Solver(c.params) as s:
         o.close()
 assert fake.fake_used() == 0
 """)
+
+
+def test_pinned_user_memory_is_copied_directly(run):
+    run("""
+c = case((96, 64, 40))
+lib, p = binding.load(), ctypes.c_void_p()
+size = 35 * 4 * c.cells
+fake.hipHostMalloc(ctypes.byref(p), ctypes.c_size_t(size), 0)
+f, step = ctypes.cast(p, ctypes.POINTER(ctypes.c_float)), ctypes.c_int64()
+q = ctypes.cast(p, ctypes.POINTER(ctypes.c_double))
+with binding.Solver(c.params) as s:
+    s.init(c.Q0)
+    ctypes.memmove(p, np.ascontiguousarray(c.Q0).ctypes.data, 5 * 8 * c.cells)
+    for call, n in ((lambda: lib.lbm_get_populations(s.ctx, f, ctypes.byref(step)), size),
+                    (lambda: lib.lbm_set_populations(s.ctx, f, 0), size),
+                    (lambda: lib.lbm_moments(s.ctx, q), 5 * 8 * c.cells)):
+        fake.fake_reset(0)
+        assert call() == 0
+        (copy,) = notes("copy")
+        assert value(copy[3], "bytes") == n and p.value in (value(copy[3], "dst"), value(copy[3], "src"))
+""")
