@@ -417,6 +417,9 @@ bool plan_passes(lbm_ctx* c) {
   return true;
 }
 
+// The context's next steps can use a second buffer.
+bool gains(const lbm_ctx* c) { return c->multi && !c->src && c->odd_lds && !c->single_steps; }
+
 unsigned* scale_words(lbm_ctx* c) { return reinterpret_cast<unsigned*>(c->ring + (size_t)kRingCap * kDiagVals); }
 
 lbm_status drain_ring(lbm_ctx* c) {
@@ -720,7 +723,8 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n, int32_t diag_every) {
   // launch in between fails, the context has to be set again.
   std::unique_lock<std::mutex> use_spare;
   bool passes = false;
-  if (n >= 3 && (diag_every == 0 || diag_every >= 3) && c->multi && !c->src && c->odd_lds && !c->single_steps && !grlbm::capturing(c->stream)) {
+  const int least = c->tube.lanes ? c->tube.least : 3;  // fewest steps of a run that gains
+  if (n >= least && (diag_every == 0 || diag_every >= least) && gains(c) && !grlbm::capturing(c->stream)) {
     grlbm::take_spare(c->spare, c->F_bytes);
     use_spare = c->spare.hold();
     passes = c->spare.buf != nullptr;
@@ -737,7 +741,7 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n, int32_t diag_every) {
     if (passes && c->tube.lanes && !diag && (t & 1) == 0) {
       int64_t m = run_from(t, n - s);
       m = c->tube.steps > 2 ? m / 2 * 2 : m / 4 * 4;  // at least two steps a launch
-      if (m >= 4) {
+      if (m >= c->tube.least) {
         void *from = c->F, *to = c->spare.buf;
         int64_t left = m / 2;  // in steps of two, dealt evenly
         for (int64_t i = (m + 2 * c->tube.steps - 1) / (2 * c->tube.steps) * 2; i > 0; --i) {

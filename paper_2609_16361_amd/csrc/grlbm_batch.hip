@@ -368,7 +368,7 @@ void plan_passes(lbm_batch* b) {
         }
         if (blocks == 0 || blocks >= INT32_MAX) continue;
         const int width = (int)(lanes / cross);
-        const double cost = grlbm::tube_price({lanes, width, width - 2 * steps, steps}, cross, blocks, f16, b->num_cus);
+        const double cost = grlbm::tube_price({lanes, width, width - 2 * steps, steps, 0}, cross, blocks, f16, b->num_cus);
         if (cost < best) {
           best = cost;
           b->tube_lanes[g] = lanes;
@@ -379,7 +379,7 @@ void plan_passes(lbm_batch* b) {
       HostInst& h = b->insts[id];
       if (!b->tube_lanes[g]) continue;
       const int width = b->tube_lanes[g] / (h.p.ny * h.p.nz);
-      h.d.tube = {b->tube_lanes[g], width, width - 2 * b->tube_steps[g], b->tube_steps[g]};
+      h.d.tube = {b->tube_lanes[g], width, width - 2 * b->tube_steps[g], b->tube_steps[g], 0};
       h.how = kWindows;
     }
   }
@@ -522,7 +522,7 @@ hipError_t launch_tubes(lbm_batch* b, int g, const void* from, void* to, int32_t
     using T = decltype(zero);
     constexpr int C = decltype(coll)::value;
     const int32_t count = b->runs[g][kWindows].count;
-    const grlbm::TubeShape sh{b->tube_lanes[g], 0, 0, 0};
+    const grlbm::TubeShape sh{b->tube_lanes[g], 0, 0, 0, 0};
     auto go = [&](auto kernel) {
       hipLaunchKernelGGL(kernel, dim3((unsigned)rounded(count)), dim3(sh.lanes),
                          grlbm::tube_lds(sh, rounded(count), b->num_cus), b->stream, (const char*)from, (char*)to,
@@ -548,7 +548,7 @@ lbm_status enqueue_steps(lbm_batch* b, int32_t n) {
   return LBM_OK;
 }
 
-// Enqueue n (even, >= 4) steps, several per pass where the instances can: tubes in an
+// Enqueue n (even, >= fast_least) steps, several per pass where the instances can: tubes in an
 // even number of launches, the rest of FP32 as one step, pairs and the odd steps left.
 // The passes of each are even in number, so that all states end in the arena; where one
 // cannot be launched, states are left between the two arenas.
@@ -644,6 +644,16 @@ int64_t fast_reach(const lbm_batch* b, int64_t clock) {
   return reach;
 }
 
+// The fewest steps of a fast run.  With pairs, which leave two of its steps single and
+// split them from the other instances' launches, fewer than eight gain nothing (batches of
+// vortices alone 0.99 of the time of single steps at 6 steps, 0.78 at 8; with tubes 1.05
+// and 0.82); tubes gain from four (0.6-0.7).
+int64_t fast_least(const lbm_batch* b) {
+  for (int g = 0; g < kGroups; ++g)
+    if (b->runs[g][kPairTiles].count > 0) return 8;
+  return 4;
+}
+
 lbm_status check_kept(const lbm_batch* b) {
   return b->lost ? fail(LBM_ESTATE, "the batch's states were lost when a launch failed") : LBM_OK;
 }
@@ -681,7 +691,8 @@ lbm_status run_steps(lbm_batch* b, int64_t n) {
   // instances anew after each odd run, as before, took an upload and a wait for the
   // stream: runs of one step of 14 instances 39 -> 63 us, of three 37 -> 45 us a step.)
   int64_t left = n;
-  if (b->odd && n > 4 && fast_reach(b, b->clock + 1) >= 4) {
+  const int64_t least = fast_least(b);
+  if (b->odd && n > least && fast_reach(b, b->clock + 1) >= least) {
     st = enqueue_steps(b, 1);
     if (st != LBM_OK) return st;
     b->odd = false;
@@ -692,7 +703,7 @@ lbm_status run_steps(lbm_batch* b, int64_t n) {
     const int64_t reach = b->odd ? 0 : fast_reach(b, clock);
     const bool graph = b->graph_steps > 1 && left >= b->graph_steps;
     int64_t m = graph ? b->graph_steps : std::min<int64_t>(left, 1 << 20);
-    bool fast = reach >= 4 && m >= 4 && (graph ? m % 2 == 0 && m <= reach : true);
+    bool fast = reach >= least && m >= least && (graph ? m % 2 == 0 && m <= reach : true);
     if (graph) {
       st = ready_graph(b, fast);
       if (st != LBM_OK) return st;

@@ -166,6 +166,7 @@ constexpr int kTubeCross = 25;  // most cells of a cross-section
 constexpr int kTubeSteps = 10;  // most steps per launch
 struct TubeShape {
   int lanes, width, inner, steps;
+  int least;  // shorter runs of a context make single steps
 };
 TubeShape tube_shape(const Grid& g, bool f16, int cus);
 // Estimated us per step of tubes cut into `blocks` windows of sh, from one launch.

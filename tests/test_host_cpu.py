@@ -336,3 +336,38 @@ with binding.Solver(c.params) as s:
         (copy,) = notes("copy")
         assert value(copy[3], "bytes") == n and p.value in (value(copy[3], "dst"), value(copy[3], "src"))
 """)
+
+
+@pytest.mark.parametrize("dims,storage,least", [((256, 4, 4), "F16", 4), ((2000, 1, 1), "F16", 4),
+                                                ((3000, 4, 4), "F16", 8), ((8192, 4, 4), "F16", 10),
+                                                ((256, 4, 4), "F32", 4), ((4000, 5, 5), "F32", 6),
+                                                ((20000, 4, 4), "F32", 6)])
+def test_short_runs_of_tubes_are_single(run, dims, storage, least):
+    run(f"""
+c = case({dims})
+with binding.Solver(c.params, storage={storage}) as s:
+    s.init(c.Q0)
+    for n in (1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12):
+        s.step(s.step_count % 2)
+        fake.fake_reset(0)
+        s.step(n)
+        passes = "k_step_tube" in kernels()
+        assert passes == (n >= {least}), (n, kernels())
+""")
+
+
+def test_short_batch_runs_are_single(run):
+    run("""
+tubes = [((300, 4, 4), F32), ((300, 4, 4), F16)]
+cubes = [((40, 36, 33), F32), ((24, 24, 24), F16)]
+for insts, least in ((tubes, 4), (cubes, 8), (tubes + cubes, 8)):
+    with binding.Batch(1 << 26, graph_steps=64) as b:
+        for d, st in insts:
+            c = case(d)
+            b.add(c.params, c.Q0, 1000, storage=st)
+        for n in (2, 4, 6, 8, 10):
+            fake.fake_reset(0)
+            b.run(n)
+            fast = bool({"k_batch_pair", "k_batch_tube"} & set(kernels()))
+            assert fast == (n >= least), (insts, n)
+""")
