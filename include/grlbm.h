@@ -26,16 +26,17 @@
  * deviation f - w_i Q_ref from the equilibrium of a uniform reference state
  * (Sec. 2.2), Q_ref = (rho_ref, 0, 0, 0, E_ref).
  *
- * Several steps per pass.  The first lbm_step that gains from it takes a second buffer of
- * the same size where the card has room to spare (it stays at least half free, or the
- * buffer takes at most an eighth of what is free, and these buffers together stay below
- * a quarter of it).  With FP32 storage lbm_step then makes two steps per pass over
- * memory, and on tubes (a cross-section of at most 25 cells, FP32 or FP16) up to ten,
- * alternating between the two buffers and ending every call in the first.  The results
- * are bitwise those of single steps.  The second buffers are given up when an allocation
- * of this library fails, and the contexts go on in single steps.  Another allocator in
- * the process cannot ask for them: lbm_set_passes declines a context's or gives it back,
- * lbm_batch_set_passes a batch's.
+ * Several steps per pass.  The first lbm_step that gains from it, or the first upload of
+ * fields or populations from host memory before it, takes a second buffer of the same size
+ * where the card has room to spare (it stays at least half free, or the buffer takes at
+ * most an eighth of what is free, and these buffers together stay below a quarter of it).
+ * With FP32 storage lbm_step then makes two steps per pass over memory, and on tubes (a
+ * cross-section of at most 25 cells, FP32 or FP16) up to ten, alternating between the two
+ * buffers and ending every call in the first.  The results are bitwise those of single
+ * steps.  The second buffers are given up when an allocation of this library fails, and
+ * the contexts go on in single steps.  Another allocator in the process cannot ask for
+ * them: lbm_set_passes declines a context's or gives it back, lbm_batch_set_passes a
+ * batch's.
  *
  * Threading.  A context is not internally locked: use one context per host thread
  * at a time.  lbm_last_error is thread-local.

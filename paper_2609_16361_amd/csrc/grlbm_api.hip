@@ -680,6 +680,7 @@ lbm_status lbm_init_fields(lbm_ctx* c, const double* Q) {
   lbm_status st0 = grlbm::check_fields(&c->p, Q);
   if (st0 != LBM_OK) return st0;
   const size_t bytes = (size_t)5 * c->N * sizeof(double);
+  if (gains(c)) grlbm::take_spare(c->spare, c->F_bytes);  // the steps to come need it too
   grlbm::Scratch d(c->spare, bytes);
   if (!d.p) return fail(LBM_ENOMEM, "hipMalloc of %zu bytes (initial fields) failed", bytes);
   lbm_status st = LBM_OK;
@@ -864,6 +865,7 @@ lbm_status lbm_set_populations(lbm_ctx* c, const float* f, int64_t step) {
   if (!c || !f) return fail(LBM_EINVAL, "ctx or f is NULL");
   if (step < 0) return fail(LBM_EINVAL, "step < 0");
   const size_t bytes = (size_t)35 * c->N * sizeof(float);
+  if (gains(c)) grlbm::take_spare(c->spare, c->F_bytes);
   grlbm::Scratch d(c->spare, bytes);
   if (!d.p) return fail(LBM_ENOMEM, "hipMalloc of %zu bytes (populations) failed", bytes);
   hipError_t e = grlbm::copy_in(d.p, f, bytes, c->stream);

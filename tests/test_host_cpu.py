@@ -201,7 +201,7 @@ def held(s):
 with binding.Solver(grid.params) as s:
     n = fake.fake_allocs()
     assert n == 2 and held(s) == 0  # the populations and the diagnostic ring
-    s.init(grid.Q0)
+    binding.lbm_init_fields_device(s.ctx, np.ascontiguousarray(grid.Q0).ctypes.data)
     s.step(2)
     s.step(40, 1)
     s.step(40, 2)
@@ -219,6 +219,9 @@ with binding.Solver(grid.params) as s:
     assert held(s) == binding.lbm_state_bytes(s.cparams)
     after = s.passes()
     assert after["steps"] - before["steps"] == 9 and after["passes"] - before["passes"] == 5
+with binding.Solver(grid.params) as s:
+    s.init(grid.Q0)  # staged there, and the steps to come use it
+    assert held(s) > 0
 for kw in (dict(odd_lds=False), dict(passes=False), dict(storage=F16)):
     with binding.Solver(grid.params, **kw) as s:
         s.init(grid.Q0)
