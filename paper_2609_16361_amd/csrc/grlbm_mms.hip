@@ -432,6 +432,112 @@ __global__ void __launch_bounds__(256, 2) k_mms_source(lbm_mms m, int32_t nx, in
   }
 }
 
+// One lane per cell, all of it evaluated there: for lattices whose rows are a fraction of a
+// tile's 64 cells (rule and times in lbm_mms_source), and for any size.
+__global__ void __launch_bounds__(256) k_mms_source_cells(lbm_mms m, int32_t nx, int32_t ny, int32_t nz, double t,
+                                                           float* __restrict__ S) {
+  const int64_t N = (int64_t)nx * ny * nz;
+  const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (n >= N) return;
+  const int64_t row = n / nx;
+  const double x = (double)(n - row * nx);
+  const double z = (double)(row / ny);
+  const double y = (double)(row % ny);
+  const double e0 = m.K*z;
+  const double e1 = m.W*t;
+  const double e2 = e0 + e1;
+  double e3, e26;
+  sincos(e2, &e3, &e26);
+  const double e4 = 4*e3;
+  const double e5 = m.K*x;
+  double e24, e6;
+  sincos(e5, &e24, &e6);
+  const double e7 = 200*m.a;
+  const double e8 = m.K*y;
+  double e9, e25;
+  sincos(e8, &e9, &e25);
+  const double e10 = e5 + 2.0/5.0;
+  double e23, e11;
+  sincos(e10, &e23, &e11);
+  const double e12 = 7*e11 + e7 + 5*e9;
+  double e56, e13;
+  sincos(e0, &e56, &e13);
+  const double e14 = e8 + 9.0/10.0;
+  double e15, e30;
+  sincos(e14, &e15, &e30);
+  const double e16 = 5*e13 + 7*e15 + e7;
+  const double e17 = m.K*m.U;
+  const double e18 = e0 + 17.0/10.0;
+  double e29, e19;
+  sincos(e18, &e29, &e19);
+  const double e20 = e1 + e5;
+  double e21, e62;
+  sincos(e20, &e21, &e62);
+  const double e22 = 5*e19 + 3*e21 + e7;
+  const double e27 = 5*e24 + 3*e25 + 2*e26 + 100;
+  const double e28 = e17*e27;
+  const double e31 = e5 + 6.0/5.0;
+  double e32, e73;
+  sincos(e31, &e32, &e73);
+  const double e33 = e32*m.P0;
+  const double e34 = sq(m.K);
+  const double e35 = sq(m.U);
+  const double e36 = sq(e12);
+  const double e37 = e12*e3;
+  const double e38 = m.U*m.W*m.rho0;
+  const double e39 = (3.0/50.0)*e38;
+  const double e40 = e35*m.rho0;
+  const double e41 = e40*m.K;
+  const double e42 = (9.0/20000.0)*e41*e9;
+  const double e43 = (3.0/10000.0)*e41;
+  const double e44 = e27*e40;
+  const double e45 = e44*m.K;
+  const double e46 = e12*e45;
+  const double e47 = (3.0/4000.0)*e29;
+  const double e48 = e1 + e8;
+  double e74, e49;
+  sincos(e48, &e74, &e49);
+  const double e50 = sq(e16);
+  const double e51 = e3*e39;
+  const double e52 = e3*e43;
+  const double e53 = e16*e22;
+  const double e54 = e16*e45;
+  const double e55 = (21.0/20000.0)*e23;
+  const double e57 = e22*e45;
+  const double e58 = e0 + 3.0/5.0;
+  double e72, e59;
+  sincos(e58, &e72, &e59);
+  const double e60 = e34*m.mu;
+  const double e61 = e60*m.U;
+  const double e63 = sq(e22);
+  const double e64 = e22*e29;
+  const double e65 = e35*e60;
+  const double e66 = (1.0/(m.gamma - 1));
+  const double e67 = 7*e23;
+  const double e68 = 7*e30;
+  const double e69 = 5*e29;
+  const double e70 = e40*(e36 + e50 + e63);
+  const double e71 = e3*e70;
+  const double e75 = 2*e72 + 5*e73 + 3*e74 + 100;
+  const double e76 = 80000*m.P0;
+  const double e77 = e75*e76;
+  const double e78 = e27*e70 + e66*e77 + e77;
+  const double e79 = e17*e78;
+  const double e80 = (1.0/(e27));
+  const double e81 = e75*e80;
+  const double e82 = e75*sq(e80);
+  const double e83 = e34*e80*m.P0*m.kappa/m.rho0;
+  const double e84 = 240000*e49*m.P0;
+  const double e85 = 2*e44;
+  const double e86 = 400000*e33;
+  const double e87 = e59*e76;
+  S[0 * N + n] = (float)((1.0/200.0)*m.rho0*((1.0/20.0)*e12*e6*m.K*m.U - 3.0/100.0*e16*e17*e9 - 1.0/50.0*e17*e22*e3 - 7.0/100.0*e23*e28 + (7.0/100.0)*e27*e30*m.K*m.U - 1.0/20.0*e28*e29 - e4*m.W));
+  S[1 * N + n] = (float)((7.0/150.0)*e11*e34*m.U*m.mu - 1.0/600.0*e12*e16*e42 + (7.0/4000000.0)*e12*e27*e30*e35*m.K*m.rho0 + (1.0/800000.0)*e16*e25*e27*e35*m.K*m.rho0 - 1.0/600.0*e22*e37*e43 - 7.0/2000000.0*e23*e46 - 1.0/20.0*e33*m.K + (1.0/40.0)*e34*e9*m.U*m.mu + (1.0/800000.0)*e35*e36*e6*m.K*m.rho0 - 1.0/600.0*e37*e39 - 1.0/600.0*e46*e47);
+  S[2 * N + n] = (float)((1.0/800000.0)*e12*e16*e35*e6*m.K*m.rho0 + (1.0/40.0)*e13*e34*m.U*m.mu + (7.0/150.0)*e15*e34*m.U*m.mu + (7.0/2000000.0)*e16*e27*e30*e35*m.K*m.rho0 - 1.0/600.0*e16*e51 - 1.0/600.0*e42*e50 - 1.0/600.0*e47*e54 + (3.0/100.0)*e49*m.K*m.P0 - 1.0/600.0*e52*e53 - 1.0/600.0*e54*e55 - 1.0/800000.0*e56*e57);
+  S[3 * N + n] = (float)((1.0/800000.0)*e12*e22*e41*e6 + (1.0/30.0)*e19*e61 + (3.0/200.0)*e21*e61 - 1.0/600.0*e22*e51 + (3.0/20000.0)*e27*e38*e62 + (7.0/4000000.0)*e30*e57 - 1.0/600.0*e42*e53 - 1.0/400000.0*e45*e64 + (3.0/4000000.0)*e46*e62 - 1.0/600.0*e52*e63 - 1.0/600.0*e55*e57 + (1.0/50.0)*e59*m.K*m.P0);
+  S[4 * N + n] = (float)((7.0/30000.0)*e11*e12*e34*e35*m.mu - 1.0/1600000000.0*e12*e17*(-5*e6*e70 + e66*e86 - e85*(-e12*e67 + 3*e22*e62) + e86) + (1.0/8000.0)*e12*e34*e35*e9*m.mu + (1.0/8000.0)*e13*e16*e34*e35*m.mu + (7.0/30000.0)*e15*e16*e34*e35*m.mu + (1.0/1600000000.0)*e16*m.K*m.U*(e66*e84 - 3*e70*e9 + e84 + e85*(5*e12*e25 + e16*e68)) + (1.0/6000.0)*e19*e22*e34*e35*m.mu + (3.0/40000.0)*e21*e22*e34*e35*m.mu + (3.0/4000000.0)*e22*e27*e35*e62*m.W*m.rho0 + (1.0/800000000.0)*e22*m.K*m.U*(-5*e44*(e16*e56 + e64) + e66*e87 - e71 + e87) - 7.0/60000.0*e23*e65*(14*e23 + e68 - e69) - 7.0/1600000000.0*e23*e79 - 1.0/1600.0*sq(e25)*e65 - 1.0/12000.0*e29*e65*(10*e29 - e67 + e68) - 1.0/320000000.0*e29*e79 - 7.0/60000.0*e30*e65*(14*e30 + e67 + e69) + (7.0/1600000000.0)*e30*e78*m.K*m.U + (3.0/100.0)*e49*e66*m.P0*m.W - 1.0/1600.0*sq(e56)*e65 - 9.0/40000.0*sq(e62)*e65 - 1.0/4000000.0*e71*m.W - 5*e83*(e24*e81 + 10*e32*e6*e80 + 10*sq(e6)*e82 - e73) - 3*e83*(e25*e81 + 6*e49*e80*e9 - e74 + 6*e82*sq(e9)) - 2*e83*(e26*e81 + 4*sq(e3)*e82 + e4*e59*e80 - e72));
+}
+
 }  // namespace
 
 extern "C" lbm_status lbm_mms_source(const lbm_mms* m, int32_t nx, int32_t ny, int32_t nz, double t,
@@ -448,8 +554,20 @@ extern "C" lbm_status lbm_mms_source(const lbm_mms* m, int32_t nx, int32_t ny, i
     return (((int64_t)nx + TX - 1) / TX) * (((int64_t)ny + ty - 1) / ty) * (((int64_t)nz + tz - 1) / tz);
   };
   while (blocks() < 512 && (tz > 1 || ty > 8)) (tz > 1 ? tz : ty) /= 2;
-  hipLaunchKernelGGL(k_mms_source, dim3((unsigned)blocks()), dim3(256), 0, (hipStream_t)hip_stream, *m, nx, ny, nz, ty,
-                     tz, t, S_dev);
+  // Beyond one turn of blocks a tile costs the card 3-5 ns for its tables and 0.4-0.6 ns
+  // for each wave's row, however few cells the row has, and a cell evaluated by itself 0.031
+  // ns, so rows of up to 14 cells, and single rows, are evaluated per cell: 1 x 1024 x 1024
+  // cells 38 us (tiles 486, before the tiles 112), 8 x 512 x 512 65 us (148, 220), 3000000
+  // x 1 x 1 92 us (269, 313); 16 x 512 x 512 would take 132 us against 120 in tiles, 300 x 5
+  // x 300 17 against 12.  A launch holds fewer than 2^24 blocks, and lattices with more
+  // tiles, those near 2^31 cells along one axis among them, are evaluated per cell as well.
+  const int64_t wave_rows = ((int64_t)nx + TX - 1) / TX * ny * nz;
+  if (blocks() > 512 && (blocks() >= (1 << 24) || N < 100 * blocks() + 13 * wave_rows))
+    hipLaunchKernelGGL(k_mms_source_cells, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, (hipStream_t)hip_stream, *m,
+                       nx, ny, nz, t, S_dev);
+  else
+    hipLaunchKernelGGL(k_mms_source, dim3((unsigned)blocks()), dim3(256), 0, (hipStream_t)hip_stream, *m, nx, ny, nz,
+                       ty, tz, t, S_dev);
   HIP_TRY(hipGetLastError());
   return LBM_OK;
 }

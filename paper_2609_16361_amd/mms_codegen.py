@@ -7,7 +7,8 @@ kappa, T = p/rho) and the fields of eq. 8 in SymPy, differentiates symbolically,
 eliminates common subexpressions, and prints a HIP kernel that evaluates the five
 components of S at every cell of an n^3 lattice in FP64 and stores them as FP32.
 What depends on one coordinate alone (all the sines and cosines, terms and factors)
-is evaluated once per coordinate of a block's tile and kept in LDS.
+is evaluated once per coordinate of a block's tile and kept in LDS.  A second kernel
+evaluates all of it per cell, for lattices that fill the tiles badly.
 The constants (rho0, U, P0, a, K, W, gamma, mu, kappa, lattice units) stay
 symbolic, so one kernel serves every resolution.
 
@@ -113,6 +114,7 @@ def generate() -> str:
     dep.update({v: set() for v in list(c.values()) + [t]})
     for sym, ex in subs:
         dep[sym] = set().union(*(dep[f] for f in ex.free_symbols))
+    per_cell = subs, red
     subs, red = group_by_coordinate(subs, red, dep, axes)
     single = {v: [(s, e) for s, e in subs if dep[s] == {v}] for v in axes}
     common = [(s, e) for s, e in subs if not dep[s]]
@@ -158,6 +160,8 @@ def generate() -> str:
     parts["LOADY"] = "\n".join(f"    const double {s} = vy[{i}][jy];" for i, s in enumerate(keep[axes[1]]))
     parts["MIXED"] = code(mixed, "    ")
     parts["OUT"] = "\n".join(f"    S[{f} * N + n] = (float)({ccode(red[f])});" for f in range(5))
+    parts["CELL"] = code(per_cell[0], "  ")
+    parts["CELLOUT"] = "\n".join(f"  S[{f} * N + n] = (float)({ccode(per_cell[1][f])});" for f in range(5))
     out = TEMPLATE
     for k, body in parts.items():
         for n in CONSTS:
@@ -229,6 +233,21 @@ __global__ void __launch_bounds__(256, 2) k_mms_source(lbm_mms m, int32_t nx, in
   }
 }
 
+// One lane per cell, all of it evaluated there: for lattices whose rows are a fraction of a
+// tile's 64 cells (rule and times in lbm_mms_source), and for any size.
+__global__ void __launch_bounds__(256) k_mms_source_cells(lbm_mms m, int32_t nx, int32_t ny, int32_t nz, double t,
+                                                           float* __restrict__ S) {
+  const int64_t N = (int64_t)nx * ny * nz;
+  const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (n >= N) return;
+  const int64_t row = n / nx;
+  const double x = (double)(n - row * nx);
+  const double z = (double)(row / ny);
+  const double y = (double)(row % ny);
+@CELL@
+@CELLOUT@
+}
+
 }  // namespace
 
 extern "C" lbm_status lbm_mms_source(const lbm_mms* m, int32_t nx, int32_t ny, int32_t nz, double t,
@@ -245,8 +264,20 @@ extern "C" lbm_status lbm_mms_source(const lbm_mms* m, int32_t nx, int32_t ny, i
     return (((int64_t)nx + TX - 1) / TX) * (((int64_t)ny + ty - 1) / ty) * (((int64_t)nz + tz - 1) / tz);
   };
   while (blocks() < 512 && (tz > 1 || ty > 8)) (tz > 1 ? tz : ty) /= 2;
-  hipLaunchKernelGGL(k_mms_source, dim3((unsigned)blocks()), dim3(256), 0, (hipStream_t)hip_stream, *m, nx, ny, nz, ty,
-                     tz, t, S_dev);
+  // Beyond one turn of blocks a tile costs the card 3-5 ns for its tables and 0.4-0.6 ns
+  // for each wave's row, however few cells the row has, and a cell evaluated by itself 0.031
+  // ns, so rows of up to 14 cells, and single rows, are evaluated per cell: 1 x 1024 x 1024
+  // cells 38 us (tiles 486, before the tiles 112), 8 x 512 x 512 65 us (148, 220), 3000000
+  // x 1 x 1 92 us (269, 313); 16 x 512 x 512 would take 132 us against 120 in tiles, 300 x 5
+  // x 300 17 against 12.  A launch holds fewer than 2^24 blocks, and lattices with more
+  // tiles, those near 2^31 cells along one axis among them, are evaluated per cell as well.
+  const int64_t wave_rows = ((int64_t)nx + TX - 1) / TX * ny * nz;
+  if (blocks() > 512 && (blocks() >= (1 << 24) || N < 100 * blocks() + 13 * wave_rows))
+    hipLaunchKernelGGL(k_mms_source_cells, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, (hipStream_t)hip_stream, *m,
+                       nx, ny, nz, t, S_dev);
+  else
+    hipLaunchKernelGGL(k_mms_source, dim3((unsigned)blocks()), dim3(256), 0, (hipStream_t)hip_stream, *m, nx, ny, nz,
+                       ty, tz, t, S_dev);
   HIP_TRY(hipGetLastError());
   return LBM_OK;
 }

@@ -374,3 +374,20 @@ for insts, least in ((tubes, 4), (cubes, 8), (tubes + cubes, 8)):
             fast = bool({"k_batch_pair", "k_batch_tube"} & set(kernels()))
             assert fast == (n >= least), (insts, n)
 """)
+
+
+@pytest.mark.parametrize("dims,cells", [((128, 128, 128), False), ((24, 24, 24), False), ((1, 64, 64), False),
+                                        ((16, 512, 512), False), ((14, 512, 512), True),
+                                        ((2 ** 31 - 1, 1, 1), True), ((1, 2 ** 31 - 1, 1), True),
+                                        ((1, 1, 2 ** 31 - 1), True), ((2 ** 16, 2 ** 15, 1), False), ((2 ** 26, 2, 16), False),
+                                        ((1, 2 ** 16, 2 ** 15), True)])
+def test_source_kernel_of_a_lattice(run, dims, cells):
+    # narrow ones are evaluated per cell; every size up to 2^31 cells can be launched, and
+    # tiles are taken only where coordinates a tile past the end fit 32 bits
+    run(f"""
+dims, cells = {dims}, {cells}
+m = inputs.mms(n=64).meta["mms"]
+binding.lbm_mms_source(m, *dims, 0.5, 256)
+assert kernels() == ["k_mms_source_cells" if cells else "k_mms_source"], kernels()
+assert cells or max(dims) < 2 ** 31 - 64
+""")
