@@ -358,17 +358,20 @@ void plan_passes(lbm_batch* b) {
     double best = 4.0 + tube_cells[g] / (f16 ? 24000.0 : 18000.0);
     for (int lanes : {256, 512})
       for (int steps = 2; steps <= grlbm::kTubeSteps; steps += 2) {
-        int64_t blocks = 0, cross = 0;
+        int64_t blocks = 0;
+        double lines = 0.0;
         for (int32_t id : tubes[g]) {
           const lbm_params& p = b->insts[id].p;
-          cross = (int64_t)p.ny * p.nz;
-          const int inner = (int)(lanes / cross) - 2 * steps;
+          const int64_t cross = (int64_t)p.ny * p.nz;
+          const int width = (int)(lanes / cross), inner = width - 2 * steps;
           if (inner < 2) blocks = INT32_MAX;
-          if (blocks < INT32_MAX) blocks += (p.nx + inner - 1) / inner;
+          if (blocks >= INT32_MAX) break;
+          const int64_t windows = ((int64_t)p.nx + inner - 1) / inner;
+          blocks += windows;
+          lines += (double)windows * grlbm::tube_lines(cross, width, f16);
         }
         if (blocks == 0 || blocks >= INT32_MAX) continue;
-        const int width = (int)(lanes / cross);
-        const double cost = grlbm::tube_price({lanes, width, width - 2 * steps, steps, 0}, cross, blocks, f16, b->num_cus);
+        const double cost = grlbm::tube_price({lanes, 0, 0, steps, 0}, lines / (double)blocks, blocks, f16, b->num_cus);
         if (cost < best) {
           best = cost;
           b->tube_lanes[g] = lanes;

@@ -169,8 +169,11 @@ struct TubeShape {
   int least;  // shorter runs of a context make single steps
 };
 TubeShape tube_shape(const Grid& g, bool f16, int cus);
-// Estimated us per step of tubes cut into `blocks` windows of sh, from one launch.
-double tube_price(const TubeShape& sh, int64_t cross, int64_t blocks, bool f16, int cus);
+// Bytes of the lines that a window of `width` columns takes in a population array.
+double tube_lines(int64_t cross, int width, bool f16);
+// Estimated us per step of tubes cut into `blocks` windows with sh's lanes and steps, which
+// take `lines` bytes of an array on average, from one launch.
+double tube_price(const TubeShape& sh, double lines, int64_t blocks, bool f16, int cus);
 int tube_lds(const TubeShape& sh, int64_t blocks, int cus);
 // `steps` (even, at most sh.steps) steps from the even step t0 on, from A to B; both hold
 // the even-parity layout.  Bitwise that many launch_step calls.

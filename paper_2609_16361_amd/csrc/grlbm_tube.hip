@@ -27,14 +27,15 @@ __global__ void __launch_bounds__(L, 4) k_step_tube(const T* __restrict__ A, T* 
 // windows through HBM at 8 TB/s, counted in whole lines, partly under the other blocks'
 // arithmetic.  Within 20% of the timings over tubes of 256 to 283000 columns with
 // cross-sections of 1 to 25 cells.
-double tube_price(const TubeShape& sh, int64_t cross, int64_t blocks, bool f16, int cus) {
+double tube_lines(int64_t cross, int width, bool f16) { return (double)cross * ((width - 1) * (f16 ? 2.0 : 4.0) + 128.0); }
+
+double tube_price(const TubeShape& sh, double lines, int64_t blocks, bool f16, int cus) {
   const int resident = 1024 / sh.lanes;
   const int64_t slots = (int64_t)cus * resident;
   const double turns = (double)((blocks + slots - 1) / slots);
   const double waves = (double)std::min<int64_t>(resident, (blocks + cus - 1) / cus) * sh.lanes / 256.0;
   const double issue = sh.steps * (f16 ? 1.45 + 0.65 * waves : 0.55 + 0.56 * waves);
-  const double el = f16 ? 2.0 : 4.0, line = (sh.width - 1) * el + 128.0;  // bytes of a row's lines
-  const double memory = 70.0 * cross * line * (double)std::min<int64_t>(blocks, slots) / 8.0e6;
+  const double memory = 70.0 * lines * (double)std::min<int64_t>(blocks, slots) / 8.0e6;
   return (3.6 + turns * (std::max(issue, memory) + 0.25 * std::min(issue, memory))) / sh.steps;
 }
 
@@ -55,7 +56,7 @@ TubeShape tube_shape(const Grid& g, bool f16, int cus) {
     const int width = (int)(lanes / cross);
     for (int steps = 2; steps <= kTubeSteps && width - 2 * steps >= 2; steps += 2) {
       const TubeShape sh{lanes, width, width - 2 * steps, steps, 0};
-      const double cost = tube_price(sh, cross, (g.nx + sh.inner - 1) / sh.inner, f16, cus);
+      const double cost = tube_price(sh, tube_lines(cross, width, f16), (g.nx + sh.inner - 1) / sh.inner, f16, cus);
       if (cost < best_cost) {
         best_cost = cost;
         best = sh;

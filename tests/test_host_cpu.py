@@ -391,3 +391,21 @@ binding.lbm_mms_source(m, *dims, 0.5, 256)
 assert kernels() == ["k_mms_source_cells" if cells else "k_mms_source"], kernels()
 assert cells or max(dims) < 2 ** 31 - 64
 """)
+
+
+@pytest.mark.parametrize("storage", ["F32", "F16"])
+@pytest.mark.parametrize("many,few,n", [((8000, 1, 1), (600, 5, 5), 12), ((3000, 4, 4), (1000, 5, 5), 12),
+                                        ((1000, 5, 5), (9000, 2, 2), 12), ((1000, 5, 5), (3000, 4, 4), 6)])
+def test_a_groups_windows_do_not_depend_on_the_order_of_its_tubes(run, many, few, n, storage):
+    run(f"""
+seen = []
+for dims in ([{many}] * {n} + [{few}], [{few}] + [{many}] * {n}):
+    with binding.Batch(1 << 29, graph_steps=64) as b:
+        for d in dims:
+            c = case(d)
+            b.add(c.params, c.Q0, 1000, storage={storage})
+        fake.fake_reset(0)
+        b.run(30)
+        seen.append([(value(n[3], "block"), value(n[3], "grid")) for n in notes("launch") if "k_batch_tube" in n[3]])
+assert seen[0] and seen[0] == seen[1], seen
+""")
