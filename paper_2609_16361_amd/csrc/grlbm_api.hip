@@ -10,7 +10,6 @@
 #include <deque>
 #include <mutex>
 #include <new>
-#include <string>
 #include <vector>
 
 #include "../../include/grlbm.h"
@@ -22,15 +21,13 @@ using grlbm::fail;
 
 namespace grlbm {
 
-thread_local std::string g_err;
+thread_local char g_err[512] = "";
 
 lbm_status fail(lbm_status st, const char* fmt, ...) {
-  char buf[512];
   va_list ap;
   va_start(ap, fmt);
-  vsnprintf(buf, sizeof buf, fmt, ap);
+  vsnprintf(g_err, sizeof g_err, fmt, ap);
   va_end(ap);
-  g_err = buf;
   return st;
 }
 
@@ -1049,6 +1046,6 @@ lbm_status lbm_step_noalloc(const lbm_params* p, void* F_dev, int64_t step, int6
   return LBM_OK;
 }
 
-const char* lbm_last_error(void) { return grlbm::g_err.c_str(); }
+const char* lbm_last_error(void) { return grlbm::g_err; }
 
 }  // extern "C"

@@ -337,18 +337,11 @@ void plan_passes(lbm_batch* b) {
     if (way(h) != kSingle) at[odd_now(h)] += cells_of(h);
   b->odd = at[1] > at[0];
   double pair_cells[kGroups] = {}, tube_cells[kGroups] = {};
-  std::vector<int32_t> tubes[kGroups];
-  for (int32_t id = 0; id < (int32_t)b->insts.size(); ++id) {
-    HostInst& h = b->insts[id];
+  for (HostInst& h : b->insts) {
     const int how = way(h);
     if (how == kSingle || odd_now(h) != b->odd) continue;
-    if (how == kWindows) {
-      tubes[h.group].push_back(id);
-      tube_cells[h.group] += cells_of(h);
-    } else {
-      h.how = kPaired;
-      pair_cells[h.group] += cells_of(h);
-    }
+    h.how = how;
+    (how == kWindows ? tube_cells : pair_cells)[h.group] += cells_of(h);
   }
   for (int g = 0; g < kGroups; ++g) {
     // the tubes of a group share a launch, hence its lanes and steps: the cheapest for
@@ -360,8 +353,9 @@ void plan_passes(lbm_batch* b) {
       for (int steps = 2; steps <= grlbm::kTubeSteps; steps += 2) {
         int64_t blocks = 0;
         double lines = 0.0;
-        for (int32_t id : tubes[g]) {
-          const lbm_params& p = b->insts[id].p;
+        for (const HostInst& h : b->insts) {
+          if (h.how != kWindows || h.group != g) continue;
+          const lbm_params& p = h.p;
           const int64_t cross = (int64_t)p.ny * p.nz;
           const int width = (int)(lanes / cross), inner = width - 2 * steps;
           if (inner < 2) blocks = INT32_MAX;
@@ -378,12 +372,14 @@ void plan_passes(lbm_batch* b) {
           b->tube_steps[g] = steps;
         }
       }
-    for (int32_t id : tubes[g]) {
-      HostInst& h = b->insts[id];
-      if (!b->tube_lanes[g]) continue;
+    for (HostInst& h : b->insts) {
+      if (h.how != kWindows || h.group != g) continue;
+      if (!b->tube_lanes[g]) {
+        h.how = kSingle;
+        continue;
+      }
       const int width = b->tube_lanes[g] / (h.p.ny * h.p.nz);
       h.d.tube = {b->tube_lanes[g], width, width - 2 * b->tube_steps[g], b->tube_steps[g], 0};
-      h.how = kWindows;
     }
   }
   for (HostInst& h : b->insts) {
@@ -923,7 +919,11 @@ lbm_status lbm_batch_add(lbm_batch* b, const lbm_params* p, const double* Q, int
 lbm_status lbm_batch_run(lbm_batch* b, int64_t n) {
   if (!b) return fail(LBM_EINVAL, "batch is NULL");
   if (n < 0) return fail(LBM_EINVAL, "n < 0");
-  return run_steps(b, n);
+  try {
+    return run_steps(b, n);
+  } catch (const std::bad_alloc&) {  // the lists of a changed batch; nothing is enqueued yet
+    return fail(LBM_ENOMEM, "host allocation of the tile lists failed");
+  }
 }
 
 lbm_status lbm_batch_set_passes(lbm_batch* b, int32_t on) {

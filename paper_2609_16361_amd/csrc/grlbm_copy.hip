@@ -10,12 +10,9 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <atomic>
 #include <cmath>
 #include <cstring>
-#include <system_error>
 #include <thread>
-#include <vector>
 
 #include "grlbm_internal.h"
 
@@ -26,7 +23,7 @@ namespace {
 constexpr size_t kChunk = size_t(2) << 20;      // bytes of a slot
 constexpr size_t kThreadedBytes = 2 * kChunk;   // smaller copies stay with the runtime
 constexpr int kCopyThreads = 4;
-constexpr size_t kMaxSlots = 16;                // pinned memory: at most 32 MiB in a process
+constexpr int kMaxSlots = 16;                   // pinned memory: at most 32 MiB in a process
 
 struct Slot {
   void* buf = nullptr;
@@ -36,8 +33,9 @@ struct Slot {
 
 // Idle slots, kept while a context or a batch lives.
 std::mutex g_mu;
-std::vector<Slot> g_idle;
-size_t g_slots = 0;  // idle and in use
+Slot g_idle[kMaxSlots];
+int g_nidle = 0;
+int g_slots = 0;  // idle and in use
 int g_users = 0;
 
 void free_slot(Slot& s) {
@@ -49,11 +47,10 @@ void free_slot(Slot& s) {
 // A slot of the current device `dev`; buf is nullptr if none can be had.
 Slot take_slot(int dev) {
   std::lock_guard<std::mutex> lock(g_mu);
-  for (size_t i = 0; i < g_idle.size(); ++i)
+  for (int i = 0; i < g_nidle; ++i)
     if (g_idle[i].device == dev) {
-      const Slot s = g_idle[i];
-      g_idle.erase(g_idle.begin() + (long)i);
-      return s;
+      std::swap(g_idle[i], g_idle[--g_nidle]);
+      return g_idle[g_nidle];
     }
   Slot s;
   if (g_slots >= kMaxSlots) return s;
@@ -72,28 +69,28 @@ void give_slot(Slot& s) {
   if (!s.buf) return;
   std::lock_guard<std::mutex> lock(g_mu);
   if (g_users > 0) {
-    g_idle.push_back(s);
+    g_idle[g_nidle++] = s;
   } else {
     free_slot(s);
   }
 }
 
-// fn(i) for i in [0, n), each in a thread of its own (the last in this one).  Where a
-// thread cannot be had its part runs here.
+// fn(i) for i in [0, n), n <= kCopyThreads, each in a thread of its own (the last in this
+// one).  Where a thread cannot be had, for want of one or of memory, its part runs here.
 template <typename Fn>
 void in_threads(int n, Fn fn) {
-  std::vector<std::thread> ts;
-  ts.reserve((size_t)n);
+  std::thread ts[kCopyThreads];
   int i = 0;
   for (; i + 1 < n; ++i) {
     try {
-      ts.emplace_back(fn, i);
-    } catch (const std::system_error&) {
+      ts[i] = std::thread(fn, i);
+    } catch (...) {
       break;
     }
   }
+  const int started = i;
   for (; i < n; ++i) fn(i);
-  for (std::thread& t : ts) t.join();
+  for (i = 0; i < started; ++i) ts[i].join();
 }
 
 // The chunks i, i + n, ... of a copy, through two slots in turn.
@@ -170,8 +167,7 @@ void copy_users(int change) {
   std::lock_guard<std::mutex> lock(g_mu);
   g_users += change;
   if (g_users > 0) return;
-  for (Slot& s : g_idle) free_slot(s);
-  g_idle.clear();
+  while (g_nidle > 0) free_slot(g_idle[--g_nidle]);
 }
 
 hipError_t copy_out(void* host, const void* dev, size_t bytes, hipStream_t s) {
@@ -194,7 +190,8 @@ lbm_status check_fields(const lbm_params* p, const double* Q) {
   constexpr int64_t kRun = 4096;
   const int64_t runs = (N + kRun - 1) / kRun;
   const int threads = (int)std::min<int64_t>(kCopyThreads, (runs + 7) / 8);
-  std::vector<int64_t> first((size_t)threads, runs);
+  int64_t first[kCopyThreads] = {runs, runs, runs, runs};
+  static_assert(kCopyThreads == 4, "one entry of first for each thread");
   in_threads(threads, [&](int i) {
     for (int64_t r = runs * i / threads; r < runs * (i + 1) / threads; ++r) {
       const int64_t end = std::min(N, (r + 1) * kRun);
@@ -206,12 +203,12 @@ lbm_status check_fields(const lbm_params* p, const double* Q) {
         bad |= (int)!(z == 0.0) | (int)!(rho > 0.0) | (int)!(pressure(n) > 0.0);
       }
       if (bad) {
-        first[(size_t)i] = r;
+        first[i] = r;
         return;
       }
     }
   });
-  const int64_t r = threads > 0 ? *std::min_element(first.begin(), first.end()) : runs;
+  const int64_t r = *std::min_element(first, first + kCopyThreads);
   for (int64_t n = r * kRun; r < runs && n < std::min(N, (r + 1) * kRun); ++n) {
     for (int k = 0; k < 5; ++k)
       if (!std::isfinite(Q[k * N + n]))

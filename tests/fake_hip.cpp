@@ -3,6 +3,24 @@
 // from a card of fake_card() bytes; copies are done at once; kernels are not run.  Every
 // call of interest is noted as one line of text: what, the stream, the calling thread
 // (0 is the one that called fake_reset) and its arguments.
+//
+// Compiled with FAIL_NEW it is another library instead: an operator new whose calls fail on
+// request.
+#ifdef FAIL_NEW
+#include <cstdlib>
+#include <new>
+
+static int fail_after = -1;
+extern "C" void fake_fail_new(int after) { fail_after = after; }
+extern "C" int fake_new_left() { return fail_after; }
+void* operator new(std::size_t n) {
+  if (fail_after == 0) throw std::bad_alloc();
+  if (fail_after > 0) --fail_after;
+  return std::malloc(n);
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, std::size_t) noexcept { std::free(p); }
+#else
 #include <hip/hip_runtime_api.h>
 
 #include <algorithm>
@@ -300,3 +318,4 @@ hipError_t hipGetLastError() {
 const char* hipGetErrorString(hipError_t) { return "fake error"; }
 
 }  // extern "C"
+#endif

@@ -13,6 +13,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 PRELUDE = """
 import ctypes, re, sys, threading
 sys.modules["torch"] = None  # it would load the real runtime
+fail_new = ctypes.CDLL({new!r}, ctypes.RTLD_GLOBAL)
 fake = ctypes.CDLL({lib!r}, ctypes.RTLD_GLOBAL)
 fake.fake_reset.argtypes = [ctypes.c_size_t]
 fake.fake_capture.argtypes = [ctypes.c_void_p, ctypes.c_int]
@@ -60,13 +61,16 @@ fake.fake_reset(1 << 33)
 
 @pytest.fixture(scope="session")
 def run(tmp_path_factory):
-    lib = str(tmp_path_factory.mktemp("fake") / "libfake_hip.so")
-    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
-                    "-Wl,-soname,libamdhip64.so.7", os.path.join(HERE, "fake_hip.cpp"), "-o", lib, "-lpthread"],
-                   check=True)
+    at = tmp_path_factory.mktemp("fake")
+    lib, new = str(at / "libfake_hip.so"), str(at / "libfail_new.so")
+    cc = ["g++", "-std=c++17", "-O1", "-shared", "-fPIC", os.path.join(HERE, "fake_hip.cpp")]
+    # its own allocations do not fail: it holds its own operator new
+    subprocess.run(cc + ["-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-Wl,-soname,libamdhip64.so.7", "-Wl,-Bsymbolic",
+                         "-static-libstdc++", "-Wl,--exclude-libs,ALL", "-o", lib, "-lpthread"], check=True)
+    subprocess.run(cc + ["-DFAIL_NEW", "-o", new], check=True)
 
     def go(code):
-        prelude = PRELUDE.format(lib=lib, root=os.path.dirname(HERE))
+        prelude = PRELUDE.format(lib=lib, new=new, root=os.path.dirname(HERE))
         r = subprocess.run([sys.executable, "-c", prelude + code], capture_output=True, text=True, timeout=300)
         assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-4000:]
 
@@ -408,4 +412,46 @@ for dims in ([{many}] * {n} + [{few}], [{few}] + [{many}] * {n}):
         b.run(30)
         seen.append([(value(n[3], "block"), value(n[3], "grid")) for n in notes("launch") if "k_batch_tube" in n[3]])
 assert seen[0] and seen[0] == seen[1], seen
+""")
+
+
+def test_no_host_allocation_failure_leaves_a_call(run):
+    # every operator new of a call fails in turn, and all after it: copies and checks go on
+    # in the calling thread, a batch's run says so and can be made again
+    run("""
+c = case((96, 64, 40))
+tubes = [case((300 + 50 * i, 4, 4)) for i in range(3)]
+with binding.Solver(c.params) as s, binding.Batch(1 << 27, graph_steps=8) as b:
+    f, Q = s.init(c.Q0) or (s.populations()[0], s.moments())
+    ids = [b.add(t.params, t.Q0, 100) for t in tubes]
+    b.run(8)
+    calls = [(lambda: s.init(c.Q0), 0), (s.populations, 0), (s.moments, 0), (lambda: s.set_populations(f, 0), 0),
+             (lambda: b.populations(ids[0]), 0), (lambda: b.run(9), binding.LBM_ENOMEM)]
+    b.remove(ids.pop())
+    for call, other in calls:
+        for k in (range(6) if other == 0 else [0]):
+            fail_new.fake_fail_new(k)
+            st = status(call)
+            fail_new.fake_fail_new(-1)
+            assert st == other, (call, k, st)
+    b.run(9)
+    assert b.query(ids[0])[0] == 17
+""")
+
+
+def test_copies_without_pinned_slots(run):
+    # none, fewer than the threads want, and one slot of two
+    run("""
+c = case((96, 64, 40))
+for slots in (0, 1, 3, 16):
+    fake.fake_slots(slots)
+    with binding.Solver(c.params) as s:
+        s.init(c.Q0)
+        fake.fake_reset(0)
+        f, _ = s.populations()
+        q = s.moments()
+        assert sum(value(n[3], "bytes") for n in notes("copy")) == (35 * 4 + 5 * 8) * c.cells
+        # no kernel has run: both readouts hold what init left in the staging buffer
+        assert np.array_equal(q, c.Q0) and np.array_equal(f.reshape(-1).view(np.float64)[:q.size], c.Q0.reshape(-1))
+assert fake.fake_used() == 0
 """)
