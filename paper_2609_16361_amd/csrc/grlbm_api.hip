@@ -194,7 +194,11 @@ lbm_status scales_from_pops(Coll& c, const float* f_dev, int64_t N, unsigned* d,
 
 bool capturing(hipStream_t s) {
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  return hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  return st != hipStreamCaptureStatusNone;
 }
 
 static std::mutex g_spare_mu;      // taken before any Spare::mu
@@ -282,6 +286,7 @@ hipError_t dev_malloc(void** p, size_t bytes) {
     (void)hipGetLastError();
     e = hipMalloc(p, bytes);
   }
+  if (e != hipSuccess) (void)hipGetLastError();  // reported here, and not by the next launch
   return e;
 }
 

@@ -455,3 +455,17 @@ for slots in (0, 1, 3, 16):
         assert np.array_equal(q, c.Q0) and np.array_equal(f.reshape(-1).view(np.float64)[:q.size], c.Q0.reshape(-1))
 assert fake.fake_used() == 0
 """)
+
+
+def test_a_failed_allocation_is_reported_once(run):
+    # the step after it, in another context, does not find its error
+    run("""
+fake.fake_reset(300 << 20)
+c, big = case((40, 36, 33)), case((128, 128, 128))
+with binding.Solver(c.params) as s, binding.Batch(1 << 26) as b:
+    s.init(c.Q0)
+    b.add(c.params, c.Q0, 100)
+    for step in (lambda: s.step(9), lambda: b.run(9), lambda: s.step(1)):
+        assert status(lambda: binding.Solver(big.params)) == binding.LBM_ENOMEM
+        assert status(step) == 0
+""")
