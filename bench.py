@@ -150,6 +150,7 @@ def bench_batch(count=64, steps=5000, seed=0, stream=None, tuning=None, sequenti
         e1.record(stream)
         torch.cuda.synchronize()
         t_batch = e0.elapsed_time(e1) * 1e-3
+        fast = b.passes()["fast_steps"]
         errs = []
         for i, c in zip(ids, cases):
             done, fin = b.query(i)
@@ -160,8 +161,10 @@ def bench_batch(count=64, steps=5000, seed=0, stream=None, tuning=None, sequenti
                       # one-step traffic (280 B per update) over the HBM peak: above 1
                       # where a pass over memory makes several steps
                       "one_step_traffic_vs_peak": 280.0 * cells * steps / t_batch / 1e9 / HBM_PEAK_GBS,
+                      # the tuned shape is that of single steps; fast steps, several per
+                      # pass, are not launched in it
                       "tuning": best, "tuned_us_per_step": best_us, "candidates": len(tried),
-                      "wall_s_incl_init_readout": t_wall}
+                      "fast_steps": fast, "wall_s_incl_init_readout": t_wall}
     out["linf_rel_error"] = {"median": float(np.median(errs)), "max": float(np.max(errs)),
                              "mach_of_max": float(cases[int(np.argmax(errs))].meta["mach"])}
     if not sequential:
@@ -464,23 +467,6 @@ def measured_traffic(paired=False):
     return rec["traffic_bytes_per_launch"] if h.hexdigest() == rec["sources_sha256"] else None
 
 
-def passes(first, steps, diag_every):
-    """Passes over the state that lbm_step(steps, diag_every) makes from step `first`
-    on where it runs step pairs: two steps per pass from an odd step on, up to the next
-    step with diagnostics (an even number of pairs, unless a single step of the same run
-    comes before them); one step per pass otherwise."""
-    n, t, end, after_single = 0, first, first + steps, False
-    while t < end:
-        run = end - t if not diag_every else min(end - t, diag_every - t % diag_every)
-        pairs = run // 2 if t % 2 and not (diag_every and t % diag_every == 0) else 0
-        if pairs and not after_single:
-            pairs = pairs // 2 * 2
-        n += pairs or 1
-        t += 2 * pairs or 1
-        after_single = pairs == 0 and t % 2 == 1
-    return n
-
-
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -579,6 +565,7 @@ def main():
     ev0 = torch.cuda.Event(enable_timing=True)
     ev1 = torch.cuda.Event(enable_timing=True)
     torch.cuda.synchronize()
+    before = solver.passes()
     t_host = time.perf_counter()
     ev0.record(stream)
     solver.step(args.steps, args.diag_every)
@@ -589,6 +576,8 @@ def main():
 
     recs, status = solver.diagnostics()
     assert status == binding.LBM_OK and all(r["nonfinite"] == 0 for r in recs), "state diverged"
+    # the library's own count of passes: two steps each where it runs step pairs
+    launches = solver.passes()["passes"] - before["passes"]
     solver.close()
     if tuned is not None:
         launch["autotuned"] = tuned
@@ -597,8 +586,7 @@ def main():
     # lbm_step reduces the diagnostics on the steps t with t % diag_every == 0
     diag_timed = (sum(1 for t in range(args.warmup, args.warmup + args.steps) if t % args.diag_every == 0)
                   if args.diag_every > 0 else 0)
-    paired = not args.fp16 and args.odd_lds
-    launches = passes(args.warmup, args.steps, args.diag_every) if paired else args.steps
+    paired = launches < args.steps
     avg_launch_ms = ms / launches
     achieved_gbs = bytes_per_lup * cells / (avg_launch_ms * 1e-3) / 1e9
 

@@ -469,3 +469,27 @@ with binding.Solver(c.params) as s, binding.Batch(1 << 26) as b:
         assert status(lambda: binding.Solver(big.params)) == binding.LBM_ENOMEM
         assert status(step) == 0
 """)
+
+
+@pytest.mark.parametrize("dims,storage", [((40, 36, 33), "F32"), ((300, 4, 4), "F16"), ((40, 36, 33), "F16")])
+def test_passes_are_counted_as_launched(run, dims, storage):
+    # what the benchmark divides its time and traffic by; also where no second buffer fits
+    run(f"""
+c = case({dims})
+for room in (1 << 33, 40 << 20) if c.cells > 40000 else (1 << 33,):
+    fake.fake_reset(room)
+    with binding.Solver(c.params, storage={storage}) as s:
+        big = binding.Solver(case((64, 64, 57)).params) if room < 1 << 33 else None  # 33 MB: the card is full
+        s.init(c.Q0)
+        for n, every in ((1, 0), (2, 0), (15, 0), (40, 7), (40, 20), (9, 1), (33, 3), (64, 0), (50, 50)):
+            before = s.passes()
+            fake.fake_reset(0)
+            s.step(n, every)
+            after = s.passes()
+            steps = [k for k in kernels() if k.startswith("k_step")]
+            assert after["steps"] - before["steps"] == n
+            assert after["passes"] - before["passes"] == len(steps), (n, every, steps)
+            assert not big or (after["second_bytes"] == 0 and len(steps) == n)
+        if big:
+            big.close()
+""")
