@@ -483,6 +483,8 @@ def main():
     ap.add_argument("--layout-pad", type=int, default=0)
     ap.add_argument("--odd-lds", type=int, default=1,
                     help="1: odd step shifts the +-x populations in LDS (default); 0: direct")
+    ap.add_argument("--passes", type=int, default=1,
+                    help="1: several steps per pass over memory where the grid gains (default); 0: single steps")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-bw-probe", action="store_true")
     ap.add_argument("--no-batch", action="store_true", help="skip the batched Becker workload")
@@ -549,7 +551,7 @@ def main():
     solver = binding.Solver(case.params, stream=stream.cuda_stream, block=args.block,
                             nontemporal=None if args.nontemporal is None else bool(args.nontemporal),
                             layout_pad=args.layout_pad, storage=storage, odd_lds=bool(args.odd_lds),
-                            blocks_per_cu=args.blocks_per_cu)
+                            blocks_per_cu=args.blocks_per_cu, passes=bool(args.passes))
     solver.init(case.Q0)
     del case.Q0
 
@@ -617,7 +619,8 @@ def main():
                    "parallelism": "single GPU"},
         "roofline": {"bound": "hbm", "achieved": round(achieved_gbs, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(achieved_gbs / HBM_PEAK_GBS, 4),
-                     "traffic": None if args.fp16 or args.n != 256 else measured_traffic(paired),
+                     "traffic": (measured_traffic(paired) if args.n == 256 and not args.fp16 and args.odd_lds
+                                 else None),
                      "traffic_unit": "bytes per launch",
                      "bytes_per_lup": round(bytes_per_lup * launches / args.steps, 3),
                      "steps_per_launch": round(args.steps / launches, 4),

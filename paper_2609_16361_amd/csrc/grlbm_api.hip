@@ -251,7 +251,12 @@ void drop_spare(Spare& s) {
 }
 
 lbm_status switch_spare(Spare& s, bool on) {
-  if (!on && s.buf) {
+  bool has = false;
+  {
+    const std::unique_lock<std::mutex> use = s.hold();
+    has = s.buf != nullptr;
+  }
+  if (!on && has) {
     if (capturing(s.stream)) return fail(LBM_ESTATE, "the stream is being captured");
     HIP_TRY(hipStreamSynchronize(s.stream));
     drop_spare(s);

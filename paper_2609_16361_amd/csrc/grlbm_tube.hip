@@ -64,13 +64,13 @@ TubeShape tube_shape(const Grid& g, bool f16, int cus) {
     }
   }
   // A run shorter than its shape's launches loads windows for few steps.  Measured against
-  // single steps at 4, 6, 8 and 10 steps: FP16 in 256-lane blocks 0.9 of their time at 4, in
-  // 512-lane blocks 1.2-1.4, 1.0-1.1 and 0.85-0.96 with a block per CU, 1.5, 1.2, 1.05 and
-  // 0.96 with two; FP32 0.55-0.9 at 4 but 1.03-1.27 in narrow windows (25 cells across) or
-  // several turns of blocks, and 0.75 at 6.
+  // single steps at 4, 6, 8 and 10 steps: FP16 in 256-lane blocks 0.9 of their time at 4; in
+  // 512-lane blocks 1.2-1.4, 1.0-1.1 (0.97 with up to six steps a launch) and 0.85-0.96 with
+  // a block per CU, 1.5, 1.2, 1.05 and 0.96 with two; FP32 0.55-0.9 at 4 but 1.03-1.27 in
+  // narrow windows (25 cells across) or several turns of blocks, and 0.75 at 6.
   const int64_t blocks = best.lanes ? (g.nx + best.inner - 1) / best.inner : 0;
   if (f16) {
-    best.least = best.lanes == 256 ? 4 : (blocks <= cus ? 8 : 10);
+    best.least = best.lanes == 256 ? 4 : (blocks > cus ? 10 : (best.steps > 6 ? 8 : 6));
   } else {
     best.least = cross > 20 || blocks > 2 * cus ? 6 : 4;
   }

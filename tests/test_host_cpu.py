@@ -346,7 +346,8 @@ with binding.Solver(c.params) as s:
 
 
 @pytest.mark.parametrize("dims,storage,least", [((256, 4, 4), "F16", 4), ((2000, 1, 1), "F16", 4),
-                                                ((3000, 4, 4), "F16", 8), ((8192, 4, 4), "F16", 10),
+                                                ((3000, 4, 4), "F16", 8), ((4097, 4, 4), "F16", 6),
+                                                ((8192, 4, 4), "F16", 10),
                                                 ((256, 4, 4), "F32", 4), ((4000, 5, 5), "F32", 6),
                                                 ((20000, 4, 4), "F32", 6)])
 def test_short_runs_of_tubes_are_single(run, dims, storage, least):
