@@ -36,7 +36,9 @@
  * steps.  The second buffers are given up when an allocation of this library fails, and
  * the contexts go on in single steps.  Another allocator in the process cannot ask for
  * them: lbm_set_passes declines a context's or gives it back, lbm_batch_set_passes a
- * batch's.
+ * batch's; and a program that makes and destroys contexts of 100 MB and more for a few
+ * dozen steps each may decline, as freed memory is cleared at some 55 GB/s, for which
+ * frees then wait.
  *
  * Threading.  A context is not internally locked: use one context per host thread
  * at a time.  lbm_last_error is thread-local.
@@ -298,8 +300,8 @@ lbm_status lbm_step_noalloc(const lbm_params* p, void* F_dev, int64_t step, int6
  * HIP graph.  Every instance keeps its own step count: it is at its step 0 when
  * added, advances with each lbm_batch_run step until it has made the number of
  * steps it was added with, then stays frozen until removed.  As in a context, tubes and
- * FP32 grids make several steps per pass where a second arena (of at most 4 GiB, for
- * the front of the first) could be had when the first such instance was added.  Results are bitwise
+ * FP32 grids make several steps per pass where a second arena could be had, which is
+ * as large as they need at the front of the first, at most 4 GiB.  Results are bitwise
  * those of the same instance run alone in a context (lbm_create/lbm_step).  All
  * calls use the batch's stream; calls that touch host memory synchronise it. */
 typedef struct lbm_batch lbm_batch; /* opaque */

@@ -239,7 +239,8 @@ using grlbm::fail;
 namespace {
 
 constexpr int kGroups = 4;  // (collision, storage) pairs
-constexpr size_t kSpareArena = size_t(4) << 30;  // most of the arena that has a second one
+constexpr size_t kSpareArena = size_t(4) << 30;  // most of the arena that has a second one ...
+constexpr size_t kSpareFirst = size_t(64) << 20;  // ... and what it starts with
 
 int group_of(const lbm_params* p) { return p->collision * 2 + (p->storage == LBM_STORE_F16 ? 1 : 0); }
 
@@ -297,6 +298,7 @@ struct lbm_batch {
   // captured graphs of graph_steps steps, all single and fast, and what they hold
   struct Graph {
     hipGraphExec_t exec = nullptr;
+    const void* to = nullptr;  // the second arena that a fast one names
     int32_t plan[kGroups * (kRuns + 2)] = {};
   } graphs[2];
 };
@@ -314,7 +316,21 @@ int fast_way(const lbm_params& p, const grlbm::Grid& g) {
   return p.storage != LBM_STORE_F16 && g.S < (int64_t(1) << 29) && grlbm::pair_worth(g) ? kPaired : kSingle;
 }
 
-size_t spare_bytes(const lbm_batch* b) { return std::min(b->arena_bytes, kSpareArena); }
+// The second arena that the instances need which step several times per pass (0: none
+// does): up to the end of the last one in the first arena, and a power of two, so that it
+// is seldom taken anew.  (A driver that clears freed memory makes a process wait that
+// frees gigabytes for nothing: a batch of 20 MB in an arena of 4 GiB took 112 ms to
+// destroy with a second arena of 4 GiB, 0.4 without.)
+size_t spare_need(const lbm_batch* b) {
+  size_t end = 0;
+  for (const HostInst& h : b->insts)
+    if (h.live && fast_way(h.p, h.d.g) != kSingle)
+      end = std::max(end, (size_t)h.d.off * (h.p.storage == LBM_STORE_F16 ? 2 : 4) + h.bytes);
+  if (end == 0) return 0;
+  size_t need = kSpareFirst;
+  while (need < end && need < kSpareArena) need *= 2;
+  return std::min(need, b->arena_bytes);
+}
 
 // Chooses how each live instance makes its steps in fast runs.  Tubes and FP32 grids do
 // several per pass if they lie in reach of the second arena and at the same parity as
@@ -626,6 +642,7 @@ lbm_status ready_graph(lbm_batch* b, bool fast) {
     gr.exec = nullptr;
     return fail(LBM_EDEVICE, "hipGraphInstantiate failed: %s", hipGetErrorString(e));
   }
+  gr.to = fast ? b->spare.buf : nullptr;
   std::memcpy(gr.plan, plan, sizeof plan);
   return LBM_OK;
 }
@@ -660,13 +677,15 @@ lbm_status check_kept(const lbm_batch* b) {
 lbm_status run_steps(lbm_batch* b, int64_t n) {
   lbm_status st = check_kept(b);
   if (st != LBM_OK) return st;
-  if (b->dirty && !b->spare.asked && !grlbm::capturing(b->stream))
-    for (const HostInst& h : b->insts)
-      if (h.live && fast_way(h.p, h.d.g) != kSingle) grlbm::take_spare(b->spare, spare_bytes(b));
+  if (b->dirty && !grlbm::capturing(b->stream))
+    if (const size_t need = spare_need(b)) {
+      grlbm::take_spare(b->spare, need);
+      grlbm::grow_spare(b->spare, need);
+    }
   // the second arena stays where it is until everything that uses it is enqueued; where
-  // it has been given up the lists and the graph that name it are made anew
+  // it has been given up or replaced the lists and the graph that name it are made anew
   const std::unique_lock<std::mutex> use = b->spare.hold();
-  if (b->graphs[1].exec && !b->spare.buf) {
+  if (b->graphs[1].exec && b->graphs[1].to != b->spare.buf) {
     (void)hipGraphExecDestroy(b->graphs[1].exec);
     b->graphs[1].exec = nullptr;
     b->dirty = true;
@@ -885,7 +904,7 @@ lbm_status lbm_batch_add(lbm_batch* b, const lbm_params* p, const double* Q, int
   h.d.inv_ny = 1.0 / p->ny;
   // a second arena for what lies at the front of the first, where instances go first; the
   // first instance that can use it brings it, and its fields are staged there
-  if (fast_way(h.p, h.d.g) != kSingle) grlbm::take_spare(b->spare, spare_bytes(b));
+  if (fast_way(h.p, h.d.g) != kSingle) grlbm::take_spare(b->spare, std::min(b->arena_bytes, kSpareFirst));
   const size_t field_bytes = sizeof(double) * 5 * (size_t)N;
   grlbm::Scratch dq(b->spare, field_bytes);
   if (!dq.p) {

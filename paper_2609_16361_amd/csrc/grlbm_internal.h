@@ -43,6 +43,9 @@ struct Spare {
 // stays free or the buffer is at most an eighth of what is free, and all second buffers
 // on it together stay below a quarter of the card.
 void take_spare(Spare& s, size_t bytes);
+// Called likewise: has one of at least `bytes` in place of a smaller one, after the work on
+// its stream.
+void grow_spare(Spare& s, size_t bytes);
 void drop_spare(Spare& s);  // frees it, if s has one; its owner's work is done
 // The owner declines a buffer, and frees the one it has after the work on its stream, or
 // takes one again.

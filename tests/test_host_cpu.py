@@ -494,3 +494,50 @@ for room in (1 << 33, 40 << 20) if c.cells > 40000 else (1 << 33,):
         if big:
             big.close()
 """)
+
+
+def test_the_second_arena_is_as_large_as_its_instances_need(run):
+    run("""
+small, large, plain = case((300, 4, 4)), case((60, 60, 60)), case((64, 64, 64))
+with binding.Batch(1 << 29, graph_steps=8) as b:
+    def held():
+        return b.passes()["second_bytes"] >> 20
+    for _ in range(3):
+        b.add(plain.params, plain.Q0, 1000, storage=F16)  # 18 MB each, in single steps
+    b.run(8)
+    assert held() == 0
+    b.add(small.params, small.Q0, 1000)
+    assert held() == 64
+    b.run(8)
+    assert held() == 64
+    ids = [b.add(large.params, large.Q0, 1000) for _ in range(4)]  # 30 MB each
+    fake.fake_reset(0)
+    b.run(16)
+    assert held() == 256 and b.passes()["fast_steps"] == 24
+    log = notes()
+    freed = [i for i, n in enumerate(log) if n[0] == "free"]
+    assert len(freed) == 1 and any(n[0] == "sync" for n in log[:freed[0]])
+    assert any(n[0] == "destroy-graph" for n in log)  # the one that names the old arena
+    seconds = {x for n in notes("launch") for x in (value(n[3], "a0"), value(n[3], "a1")) if "k_batch_pair" in n[3]}
+    gone = value(log[freed[0]][3], "p")
+    assert len(seconds) == 2 and gone not in seconds
+    for i in ids:
+        b.remove(i)
+    b.run(8)
+    assert held() == 256  # kept
+assert fake.fake_used() == 0
+""")
+
+
+def test_short_solves_in_new_contexts_take_no_second_buffer(run):
+    run("""
+for dims, steps, takes in (((64, 64, 64), 40, False), ((64, 64, 64), 70, True), ((128, 128, 64), 16, True),
+                           ((40, 36, 33), 4, True)):
+    c = case(dims)
+    for parts in ((steps,), (steps // 2, steps - steps // 2)):
+        with binding.Solver(c.params) as s:
+            binding.lbm_init_fields_device(s.ctx, np.ascontiguousarray(c.Q0).ctypes.data)
+            for n in parts:
+                s.step(n)
+            assert (s.passes()["second_bytes"] > 0) == takes or parts[-1] < 3, (dims, parts)
+""")
