@@ -45,8 +45,8 @@
  *
  * Errors.  Every call returns an lbm_status; on failure lbm_last_error() describes
  * it.  No call aborts the process.  Where a launch fails between the passes of several
- * steps (EDEVICE), the state is lost: a context has to be initialised or restored again,
- * a batch's runs and readouts fail (ESTATE).
+ * steps (EDEVICE), or between the launches of a batch's run, the state is lost: a context
+ * has to be initialised or restored again, a batch's runs and readouts fail (ESTATE).
  */
 #ifndef GRLBM_H
 #define GRLBM_H

@@ -123,3 +123,27 @@ def test_small_grids_and_batches_take_passes():
             b.add(case.params, case.Q0, 1000, storage=st)
         b.run(40)
         assert b.passes()["fast_steps"] == 40
+
+
+def test_a_first_pass_beside_a_capture_leaves_it_whole():
+    # the step that takes the second buffer allocates while another stream is captured
+    case = inputs.random_smooth(40, 36, 33, seed=5, amp=0.05)
+    Q = torch.as_tensor(case.Q0).cuda()
+    x = torch.zeros(1000, device="cuda")
+    side = torch.cuda.Stream()
+    with binding.Solver(case.params) as s, binding.Solver(case.params, passes=False) as ref:
+        binding.lbm_init_fields_device(s.ctx, Q.data_ptr())
+        binding.lbm_init_fields_device(ref.ctx, Q.data_ptr())
+        ref.step(9)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=side):
+            x.add_(1.0)
+            s.step(9)
+            x.mul_(2.0)
+        assert s.passes()["second_bytes"] > 0 and s.passes()["passes"] == 5
+        for want in (2.0, 6.0, 14.0):
+            g.replay()
+            torch.cuda.synchronize()
+            assert bool((x == want).all())
+        assert (s.populations()[0] == ref.populations()[0]).all()

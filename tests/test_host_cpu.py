@@ -541,3 +541,34 @@ for dims, steps, takes in (((64, 64, 64), 40, False), ((64, 64, 64), 70, True), 
                 s.step(n)
             assert (s.passes()["second_bytes"] > 0) == takes or parts[-1] < 3, (dims, parts)
 """)
+
+
+def test_a_batchs_clock_is_the_devices_where_a_run_fails(run):
+    # a graph of eight steps is on its way when the rest of the run fails: they count
+    run("""
+c = case((24, 24, 24))
+for storage, after, done, kept in ((F16, 0, 16, True), (F16, 3, 16, False)):
+    with binding.Batch(1 << 26, graph_steps=8) as b:
+        i = b.add(c.params, c.Q0, 1000, storage=storage)
+        b.run(8)
+        fake.fake_fail(b"k_batch_step", after)
+        assert status(lambda: b.run(13)) == binding.LBM_EDEVICE
+        assert b.query(i)[0] == done and b.info()["clock"] == done
+        assert status(lambda: b.run(1)) == (0 if kept else binding.LBM_ESTATE)
+""")
+
+
+def test_instances_that_finish_before_a_failure_are_listed_no_more(run):
+    run("""
+c, d = case((24, 24, 24)), case((30, 30, 30))
+with binding.Batch(1 << 26, graph_steps=8) as b:
+    i, j = b.add(c.params, c.Q0, 16, storage=F16), b.add(d.params, d.Q0, 1000, storage=F16)
+    b.run(8)
+    fake.fake_fail(b"k_batch_step", 0)
+    assert status(lambda: b.run(13)) == binding.LBM_EDEVICE
+    assert b.query(i) == (16, True) and b.query(j) == (16, False)
+    fake.fake_reset(0)
+    b.run(8)
+    assert notes("copy")  # the lists, without the finished one
+    assert b.query(j)[0] == 24
+""")
