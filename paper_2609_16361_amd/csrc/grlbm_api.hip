@@ -204,14 +204,6 @@ bool capturing(hipStream_t s) {
 static std::mutex g_spare_mu;      // taken before any Spare::mu
 static Spare* g_spares = nullptr;  // those that hold a buffer
 
-// In a step's enqueueing: an allocation there must not break a capture that another
-// thread, or this one, has going on another stream.
-struct RelaxedCapture {
-  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-  RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
-  ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
-};
-
 void take_spare(Spare& s, size_t bytes) {
   if (s.off || s.asked) return;
   s.asked = true;

@@ -272,7 +272,8 @@ struct lbm_batch {
   int32_t max_tiles = 0;
   BatchInst* d_insts = nullptr;
   BatchTile* d_tiles = nullptr;      // kGroups segments of max_tiles: tiles of single steps
-  BatchTile* d_multi = nullptr;      // the same for pair tiles and tube windows
+  BatchTile* d_multi = nullptr;      // the same for pair tiles and tube windows, from the
+                                     // first instance on that has some
   TileRun* d_runs = nullptr;         // kGroups times kRuns
   int64_t* d_clock = nullptr;
   grlbm::CheckItem* d_check = nullptr;  // items of the divergence check (grown on demand)
@@ -332,6 +333,22 @@ size_t spare_need(const lbm_batch* b) {
   return std::min(need, b->arena_bytes);
 }
 
+// The second arena, of at least `bytes`, and the lists of its tiles; without either the
+// steps are single.
+void prepare_fast(lbm_batch* b, size_t bytes) {
+  grlbm::take_spare(b->spare, bytes);
+  grlbm::grow_spare(b->spare, bytes);
+  {
+    const std::unique_lock<std::mutex> use = b->spare.hold();
+    if (b->d_multi || !b->spare.buf) return;
+  }
+  const grlbm::RelaxedCapture relaxed;
+  if (hipMalloc((void**)&b->d_multi, sizeof(BatchTile) * (size_t)b->max_tiles * kGroups) != hipSuccess) {
+    (void)hipGetLastError();
+    b->d_multi = nullptr;
+  }
+}
+
 // Chooses how each live instance makes its steps in fast runs.  Tubes and FP32 grids do
 // several per pass if they lie in reach of the second arena and at the same parity as
 // most of them (by cells): a fast run starts with all of them at an even step.
@@ -339,7 +356,7 @@ void plan_passes(lbm_batch* b) {
   for (HostInst& h : b->insts) h.how = kSingle;
   for (int g = 0; g < kGroups; ++g) b->tube_lanes[g] = 0;
   b->odd = false;
-  if (!b->spare.buf) return;
+  if (!b->spare.buf || !b->d_multi) return;
   const auto way = [&](const HostInst& h) {
     const bool f16 = h.p.storage == LBM_STORE_F16;
     if (!h.live || h.d.t_end <= b->clock || (size_t)h.d.off * (f16 ? 2 : 4) + h.bytes > b->spare.bytes)
@@ -678,10 +695,7 @@ lbm_status run_steps(lbm_batch* b, int64_t n) {
   lbm_status st = check_kept(b);
   if (st != LBM_OK) return st;
   if (b->dirty && !grlbm::capturing(b->stream))
-    if (const size_t need = spare_need(b)) {
-      grlbm::take_spare(b->spare, need);
-      grlbm::grow_spare(b->spare, need);
-    }
+    if (const size_t need = spare_need(b)) prepare_fast(b, need);
   // the second arena stays where it is until everything that uses it is enqueued; where
   // it has been given up or replaced the lists and the graph that name it are made anew
   const std::unique_lock<std::mutex> use = b->spare.hold();
@@ -826,7 +840,6 @@ lbm_status lbm_batch_create(size_t arena_bytes, int32_t max_instances, int32_t m
   b->max_tiles = max_tiles;
   if (grlbm::dev_malloc((void**)&b->d_insts, sizeof(BatchInst) * (size_t)max_instances) != hipSuccess ||
       grlbm::dev_malloc((void**)&b->d_tiles, sizeof(BatchTile) * (size_t)max_tiles * kGroups) != hipSuccess ||
-      grlbm::dev_malloc((void**)&b->d_multi, sizeof(BatchTile) * (size_t)max_tiles * kGroups) != hipSuccess ||
       grlbm::dev_malloc((void**)&b->d_runs, sizeof(b->runs)) != hipSuccess ||
       grlbm::dev_malloc((void**)&b->d_scales, 5 * sizeof(unsigned)) != hipSuccess ||
       grlbm::dev_malloc((void**)&b->d_clock, sizeof(int64_t)) != hipSuccess ||
@@ -898,7 +911,7 @@ lbm_status lbm_batch_add(lbm_batch* b, const lbm_params* p, const double* Q, int
   h.d.inv_ny = 1.0 / p->ny;
   // a second arena for what lies at the front of the first, where instances go first; the
   // first instance that can use it brings it, and its fields are staged there
-  if (fast_way(h.p, h.d.g) != kSingle) grlbm::take_spare(b->spare, std::min(b->arena_bytes, kSpareFirst));
+  if (fast_way(h.p, h.d.g) != kSingle) prepare_fast(b, std::min(b->arena_bytes, kSpareFirst));
   const size_t field_bytes = sizeof(double) * 5 * (size_t)N;
   grlbm::Scratch dq(b->spare, field_bytes);
   if (!dq.p) {

@@ -51,6 +51,13 @@ void drop_spare(Spare& s);  // frees it, if s has one; its owner's work is done
 // takes one again.
 lbm_status switch_spare(Spare& s, bool on);
 bool capturing(hipStream_t s);
+// In a step's enqueueing: an allocation there must not break a capture that another
+// thread, or this one, has going on another stream.
+struct RelaxedCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
 // Copies between host and device memory in order with the work on s; they return when
 // the copy is done.  copy_users counts the contexts and batches, for which pinned slots
 // are kept.

@@ -572,3 +572,22 @@ with binding.Batch(1 << 26, graph_steps=8) as b:
     assert notes("copy")  # the lists, without the finished one
     assert b.query(j)[0] == 24
 """)
+
+
+def test_batches_of_single_steps_hold_one_tile_list(run):
+    run("""
+fp16, fp32 = case((24, 24, 24)), case((40, 36, 33))
+for room in (1 << 33, 130 << 20):  # the second list of 100 MB does not fit beside the first
+    fake.fake_reset(room)
+    with binding.Batch(1 << 22, max_tiles=3 << 20) as b:
+        own = fake.fake_used()
+        assert own < 110 << 20
+        b.add(fp16.params, fp16.Q0, 1000, storage=F16)
+        b.run(8)
+        assert fake.fake_used() == own
+    with binding.Batch(1 << 23, max_tiles=3 << 20) as b:
+        b.add(fp32.params, fp32.Q0, 1000)
+        b.run(32)
+        assert b.passes()["fast_steps"] == (32 if room > 1 << 30 else 0)
+assert fake.fake_used() == 0
+""")
