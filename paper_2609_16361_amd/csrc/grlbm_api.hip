@@ -205,11 +205,13 @@ static std::mutex g_spare_mu;      // taken before any Spare::mu
 static Spare* g_spares = nullptr;  // those that hold a buffer
 
 void take_spare(Spare& s, size_t bytes) {
-  if (s.off || s.asked) return;
+  int dev = -1;
+  if (s.off || s.asked || hipGetDevice(&dev) != hipSuccess || dev != s.device) return;
   s.asked = true;
   size_t free_bytes = 0, total = 0, held = 0;
   const RelaxedCapture relaxed;
   std::lock_guard<std::mutex> lock(g_spare_mu);
+  if (s.buf) return;
   if (hipMemGetInfo(&free_bytes, &total) != hipSuccess) {
     (void)hipGetLastError();
     return;

@@ -338,9 +338,10 @@ size_t spare_need(const lbm_batch* b) {
 void prepare_fast(lbm_batch* b, size_t bytes) {
   grlbm::take_spare(b->spare, bytes);
   grlbm::grow_spare(b->spare, bytes);
+  int dev = -1;
   {
     const std::unique_lock<std::mutex> use = b->spare.hold();
-    if (b->d_multi || !b->spare.buf) return;
+    if (b->d_multi || !b->spare.buf || hipGetDevice(&dev) != hipSuccess || dev != b->spare.device) return;
   }
   const grlbm::RelaxedCapture relaxed;
   if (hipMalloc((void**)&b->d_multi, sizeof(BatchTile) * (size_t)b->max_tiles * kGroups) != hipSuccess) {
@@ -694,8 +695,12 @@ lbm_status check_kept(const lbm_batch* b) {
 lbm_status run_steps(lbm_batch* b, int64_t n) {
   lbm_status st = check_kept(b);
   if (st != LBM_OK) return st;
-  if (b->dirty && !grlbm::capturing(b->stream))
-    if (const size_t need = spare_need(b)) prepare_fast(b, need);
+  if ((b->dirty || !b->spare.asked) && !grlbm::capturing(b->stream))
+    if (const size_t need = spare_need(b)) {
+      const bool asked = b->spare.asked;
+      prepare_fast(b, need);
+      if (b->spare.asked != asked) b->dirty = true;  // lists with fast steps
+    }
   // the second arena stays where it is until everything that uses it is enqueued; where
   // it has been given up or replaced the lists and the graph that name it are made anew
   const std::unique_lock<std::mutex> use = b->spare.hold();

@@ -39,9 +39,10 @@ struct Spare {
   }
 };
 // Called by the owner, without mu, before the first work that uses a buffer: takes one
-// for s (device and stream are set) if the card has room to spare: at least half of it
-// stays free or the buffer is at most an eighth of what is free, and all second buffers
-// on it together stay below a quarter of the card.
+// for s (device and stream are set; not while another device is current), which has none,
+// if the card has room to spare: at least half of it stays free or the buffer is at most
+// an eighth of what is free, and all second buffers on it together stay below a quarter
+// of the card.
 void take_spare(Spare& s, size_t bytes);
 // Called likewise: has one of at least `bytes` in place of a smaller one, after the work on
 // its stream.

@@ -50,6 +50,7 @@ void (*on_sync)(void*) = nullptr;
 thread_local hipError_t last = hipSuccess;
 thread_local hipStreamCaptureMode mode = hipStreamCaptureModeGlobal;
 thread_local std::vector<size_t> config;
+thread_local int current = 0;
 
 int me() {
   const auto it = threads.emplace(std::this_thread::get_id(), (int)threads.size());
@@ -297,10 +298,13 @@ hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) {
   return hipSuccess;
 }
 hipError_t hipGetDevice(int* d) {
-  *d = 0;
+  *d = current;
   return hipSuccess;
 }
-hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipSetDevice(int d) {
+  current = d;
+  return hipSuccess;
+}
 hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) {
   *v = 256;
   return hipSuccess;

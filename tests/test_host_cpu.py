@@ -591,3 +591,35 @@ for room in (1 << 33, 130 << 20):  # the second list of 100 MB does not fit besi
         assert b.passes()["fast_steps"] == (32 if room > 1 << 30 else 0)
 assert fake.fake_used() == 0
 """)
+
+
+def test_a_second_buffer_is_taken_once_and_on_its_own_device(run):
+    run("""
+c = case((40, 36, 33))
+with binding.Solver(c.params) as s, binding.Batch(1 << 26) as b:
+    s.init(c.Q0)
+    b.add(c.params, c.Q0, 1000)
+    s.step(9)
+    b.run(16)
+    own = fake.fake_used()
+    for _ in range(2):
+        s.set_passes(True)  # it is on already
+        b.set_passes(True)
+        s.step(9)
+        b.run(16)
+        assert fake.fake_used() == own
+    s.set_passes(False)
+    b.set_passes(False)
+    less = fake.fake_used()
+    s.set_passes(True)
+    b.set_passes(True)
+    fake.hipSetDevice(1)  # the caller's other device
+    s.step(9)
+    b.run(16)
+    assert fake.fake_used() == less
+    fake.hipSetDevice(0)
+    s.step(9)
+    b.run(16)
+    assert fake.fake_used() == own
+assert fake.fake_used() == 0
+""")
